@@ -211,9 +211,11 @@ size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int6
     }
     G->verts = P.take<double>(3 * std::max<int64_t>(nv_max, 3));
     G->tris = P.take<int32_t>(3 * std::max<int64_t>(nt_max, 1));
+    G->verts_in = P.take<double>(3 * std::max<int64_t>(nv_max, 3));
+    G->tris_in = P.take<int32_t>(3 * std::max<int64_t>(nt_max, 1));
     G->bucket_cnt = P.take<int32_t>(NBUCKET_MAX + 1);
     G->bucket_off = P.take<int32_t>(NBUCKET_MAX + 1);
-    G->bucket_ent = P.take<int32_t>(8 * std::max<int64_t>(nt_max, 1) + 16);
+    G->bucket_ent = P.take<int32_t>(std::max<int64_t>(nt_max, 1));
     G->col_cnt = P.take<int32_t>(ncol + 1);
     G->col_off = P.take<int32_t>(ncol + 1);
     G->col_fill = P.take<int32_t>(std::max<int64_t>(ncol + 1, NBUCKET_MAX + 1));
@@ -418,60 +420,41 @@ ibm_status ibm_bind_workspace(ibm_grid *g, void *device_ptr, size_t bytes, int64
     return IBM_OK;
 }
 
-static ibm_status set_geometry_impl(ibm_grid *g, const double *verts, int64_t nv, const int32_t *tris, int64_t nt,
-                                    void *stream, bool known_topology);
+// why a mesh is refused, by the host's own checks (nullptr: it is accepted)
+static const char *mesh_refused(const double *verts, int64_t nv, const int32_t *tris, int64_t nt, ibm_status *st) {
+    *st = IBM_E_ARG;
+    for (int64_t i = 0; i < 3 * nv; ++i)
+        if (!std::isfinite(verts[i])) return "non-finite vertex coordinate";
+    for (int64_t i = 0; i < 3 * nt; ++i)
+        if (tris[i] < 0 || tris[i] >= nv) return "triangle index out of range";
+    *st = IBM_E_GEOMETRY;
+    return mesh_closed_oriented(tris, nt, nv);
+}
 
 ibm_status ibm_set_geometry(ibm_grid *g, const double *verts, int64_t nv, const int32_t *tris, int64_t nt,
                             void *stream) {
     Range range_("ibm_set_geometry");
-    return set_geometry_impl(g, verts, nv, tris, nt, stream, false);
-}
-
-static ibm_status set_geometry_impl(ibm_grid *g, const double *verts, int64_t nv, const int32_t *tris, int64_t nt,
-                                    void *stream, bool known_topology) {
     if (!g) return fail(nullptr, IBM_E_ARG, "ibm_set_geometry: NULL handle");
     if (g->stage < ST_BOUND) return fail(g, IBM_E_STATE, "ibm_set_geometry before ibm_bind_workspace");
     const double t_in = now_s();
     if (!verts || !tris || nv < 3 || nt < 1) return fail(g, IBM_E_ARG, "ibm_set_geometry: empty mesh");
     if (nv > g->nv_max || nt > g->nt_max) return fail(g, IBM_E_NOMEM, "mesh larger than the bound capacities");
-    bool finite = true;  // no early exit: the loops vectorise
-    for (int64_t i = 0; i < 3 * nv; ++i) finite &= std::isfinite(verts[i]);
-    if (!finite) return fail(g, IBM_E_ARG, "non-finite vertex coordinate");
-    // a move that keeps the triangles (the same indices as the last validated mesh, compared
-    // exactly) skips the index and closedness checks
-    const bool same = known_topology && g->topo_valid && g->topo_nv == nv &&
-                      (int64_t)g->topo_tris.size() == 3 * nt &&
-                      std::memcmp(g->topo_tris.data(), tris, sizeof(int32_t) * 3 * nt) == 0;
-    if (!same) {
-        g->topo_valid = false;
-        int32_t tmin = tris[0], tmax = tris[0];
-        for (int64_t i = 0; i < 3 * nt; ++i) {
-            tmin = std::min(tmin, tris[i]);
-            tmax = std::max(tmax, tris[i]);
-        }
-        if (tmin < 0 || tmax >= nv) return fail(g, IBM_E_ARG, "triangle index out of range");
-        if (const char *why = mesh_closed_oriented(tris, nt, nv)) return fail(g, IBM_E_GEOMETRY, why);
-        g->topo_tris.assign(tris, tris + 3 * nt);
-        g->topo_nv = nv;
-        g->topo_valid = true;
+    hipStream_t s = (hipStream_t)stream;
+    HIP_TRY(hipSetDevice(g->device), "hipSetDevice");
+    // the new mesh is checked beside the one in use, which stays the handle's if this fails
+    HIP_TRY(hipMemcpyAsync(g->verts_in, verts, sizeof(double) * 3 * nv, hipMemcpyHostToDevice, s), "upload verts");
+    HIP_TRY(hipMemcpyAsync(g->tris_in, tris, sizeof(int32_t) * 3 * nt, hipMemcpyHostToDevice, s), "upload tris");
+    MeshScan scan;
+    HIP_TRY(launch_mesh_scan(g, g->verts_in, nv, g->tris_in, nt, &scan, s), "mesh check");
+    if (scan.bad) {
+        ibm_status why_st;
+        if (const char *why = mesh_refused(verts, nv, tris, nt, &why_st)) return fail(g, why_st, why);
     }
+    std::swap(g->verts, g->verts_in);
+    std::swap(g->tris, g->tris_in);
     // bucket grid over the mesh bounding box: buckets at least as large as the largest
     // triangle extent; each triangle is listed in the bucket of its bounding box's low corner
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY}, ext[3] = {0, 0, 0};
-    for (int64_t t = 0; t < nt; ++t) {
-        double tl[3] = {INFINITY, INFINITY, INFINITY}, th[3] = {-INFINITY, -INFINITY, -INFINITY};
-        for (int q = 0; q < 3; ++q)
-            for (int d = 0; d < 3; ++d) {
-                double x = verts[3 * tris[3 * t + q] + d];
-                tl[d] = std::min(tl[d], x);
-                th[d] = std::max(th[d], x);
-            }
-        for (int d = 0; d < 3; ++d) {
-            ext[d] = std::max(ext[d], th[d] - tl[d]);
-            lo[d] = std::min(lo[d], tl[d]);
-            hi[d] = std::max(hi[d], th[d]);
-        }
-    }
+    const double *lo = scan.lo, *hi = scan.hi, *ext = scan.ext;
     double span[3], vol = 1.0;
     for (int d = 0; d < 3; ++d) {
         span[d] = std::max(hi[d] - lo[d], 1e-12);
@@ -496,17 +479,9 @@ static ibm_status set_geometry_impl(ibm_grid *g, const double *verts, int64_t nv
         g->bsize[d] = span[d] / g->nb[d];
         g->bext[d] = ext[d] + 1e-9 * span[d];  // covers the rounding of the extents
     }
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(hipSetDevice(g->device), "hipSetDevice");
-    HIP_TRY(hipMemcpyAsync(g->verts, verts, sizeof(double) * 3 * nv, hipMemcpyHostToDevice, s), "upload verts");
-    HIP_TRY(hipMemcpyAsync(g->tris, tris, sizeof(int32_t) * 3 * nt, hipMemcpyHostToDevice, s), "upload tris");
     g->nv = nv;
     g->nt = nt;
     HIP_TRY(launch_buckets(g, s), "bucket grid");
-    int64_t bucket_overflow = 0;
-    HIP_TRY(hipMemcpyAsync(&bucket_overflow, g->counters + 6, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read");
-    HIP_TRY(hipStreamSynchronize(s), "set_geometry sync");  // host arrays may be freed after return
-    if (bucket_overflow) return fail(g, IBM_E_NOMEM, "triangle bucket grid overflow");
     g->stage = ST_GEOMETRY;
     g->ng = 0;
     g->t_setup = now_s() - t_in;
@@ -1340,7 +1315,7 @@ ibm_status ibm_move_geometry(ibm_grid *g, const double *verts, int64_t nv, const
     HIP_TRY(hipSetDevice(g->device), "hipSetDevice");
     HIP_TRY(hipMemcpyAsync(g->type_prev, g->type, (size_t)g->N, hipMemcpyDeviceToDevice, s), "save types");
     g->nfresh = 0;
-    ibm_status st = set_geometry_impl(g, verts, nv, tris, nt, stream, true);
+    ibm_status st = ibm_set_geometry(g, verts, nv, tris, nt, stream);
     if (st != IBM_OK) return st;
     int64_t counts[3];
     if ((st = ibm_classify(g, stream, counts)) != IBM_OK) return st;

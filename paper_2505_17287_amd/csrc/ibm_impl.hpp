@@ -256,8 +256,8 @@ struct ibm_grid {
     float *w0f[3] = {nullptr, nullptr, nullptr};
     // mesh and geometry scratch
     int64_t nv = 0, nt = 0;
-    double *verts = nullptr;
-    int32_t *tris = nullptr;
+    double *verts = nullptr, *verts_in = nullptr;  // the mesh in use, and the one being checked
+    int32_t *tris = nullptr, *tris_in = nullptr;   // (exchanged when it is accepted)
     int32_t *bucket_off = nullptr, *bucket_cnt = nullptr, *bucket_ent = nullptr;
     int nb[3] = {1, 1, 1};
     double bmin[3] = {0, 0, 0}, bsize[3] = {1, 1, 1};
@@ -280,9 +280,6 @@ struct ibm_grid {
     double *g_betaDg = nullptr;            // per ghost: weight of the intercept value
     double *g_ubi = nullptr;               // 3 per ghost: velocity at the body intercept
     double *g_uscr = nullptr;              // 3 per ghost: held-back ghost values of an in-place pass
-    std::vector<int32_t> topo_tris;        // triangle indices of the last validated mesh
-    int64_t topo_nv = 0;                   // and its vertex count
-    bool topo_valid = false;
     // fresh cells of the last move (capacity ghost_max)
     uint8_t *type_prev = nullptr;          // cell types before the move
     int64_t nfresh = 0;
@@ -362,6 +359,15 @@ ibm_status report_error(ibm_status st, const std::string &msg);
 // kernel launchers (geometry.hip)
 hipError_t launch_metrics(ibm_grid *g, hipStream_t s);
 hipError_t launch_buckets(ibm_grid *g, hipStream_t s);
+// check and extents of an uploaded mesh (device arrays); synchronises the stream
+constexpr int MESH_BAD_VERT = 1, MESH_BAD_INDEX = 2, MESH_BAD_TOPO = 4;
+constexpr int64_t MESH_TAB_PAD = 64;  // slots of the edge table beyond 3 per triangle
+struct MeshScan {
+    double lo[3], hi[3], ext[3];  // over the triangles with valid indices
+    int bad;
+};
+hipError_t launch_mesh_scan(ibm_grid *g, const double *V, int64_t nv, const int32_t *T, int64_t nt, MeshScan *out,
+                            hipStream_t s);
 hipError_t launch_classify(ibm_grid *g, hipStream_t s, int64_t counts[4]);
 hipError_t launch_stencils(ibm_grid *g, hipStream_t s);
 hipError_t launch_ghost_h(ibm_grid *g, hipStream_t s);
