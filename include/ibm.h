@@ -114,6 +114,10 @@ ibm_status ibm_create_grid(int nx, int ny, int nz, const double *xf, const doubl
 size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,
                            ibm_precision prec);
 
+/* Surface area of a triangle mesh (host arrays, host call): what a caller sizes max_ghosts by.
+   -1 for NULL pointers or a triangle index outside [0, nv). */
+double ibm_mesh_area(const double *verts, int64_t nv, const int32_t *tris, int64_t nt);
+
 /* Exact workspace size for an existing handle (its multigrid plan depends on the face
    coordinates).  ibm_workspace_bytes is an upper bound of this for any coordinates. */
 size_t ibm_grid_workspace_bytes(const ibm_grid *g, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,

@@ -95,6 +95,8 @@ def lib():
         L.ibm_grid_workspace_bytes.restype = C.c_size_t
         L.ibm_grid_workspace_bytes.argtypes = [vp, i64, i64, i64, C.c_int]
         L.ibm_bind_workspace.argtypes = [vp, vp, C.c_size_t, i64, i64, i64, C.c_int, vp]
+        L.ibm_mesh_area.restype = C.c_double
+        L.ibm_mesh_area.argtypes = [dp, i64, vp, i64]
         L.ibm_set_geometry.argtypes = [vp, dp, i64, vp, i64, vp]
         L.ibm_classify.argtypes = [vp, vp, vp]
         L.ibm_classify_noalloc.argtypes = [C.c_int, C.c_int, C.c_int, vp, vp, vp, vp, i64, vp, i64, vp, vp, vp]
@@ -192,9 +194,11 @@ def _tptr(t):
 
 def estimate_max_ghosts(xf, yf, zf, verts, tris):
     """Capacity for the ghost list: four cells per finest-cell face of surface, plus slack."""
-    v = np.asarray(verts, dtype=np.float64)
-    t = np.asarray(tris)
-    area = 0.5 * np.linalg.norm(np.cross(v[t[:, 1]] - v[t[:, 0]], v[t[:, 2]] - v[t[:, 0]]), axis=1).sum()
+    v = np.ascontiguousarray(verts, dtype=np.float64)
+    t = np.ascontiguousarray(tris, dtype=np.int32)
+    area = lib().ibm_mesh_area(_dp(v), len(v), C.c_void_p(t.ctypes.data), len(t))
+    if area < 0.0:  # an index out of range: IndexError, or a wrapped index that ibm_set_geometry refuses
+        area = 0.5 * np.linalg.norm(np.cross(v[t[:, 1]] - v[t[:, 0]], v[t[:, 2]] - v[t[:, 0]]), axis=1).sum()
     h = [np.min(np.diff(f)) for f in (xf, yf, zf)]
     if len(zf) == 2:  # one cell thick: count per unit of the z extent inside the cell
         hmin = min(h[0], h[1])

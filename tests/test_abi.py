@@ -130,3 +130,17 @@ def test_classify_noalloc_rejects_sizes_beyond_its_scratch():
     assert L.ibm_classify_noalloc(8, 8, 8, p, p, p, p, 2, p, 1, p, cp, None) == ibm.IBM_E_ARG
     assert L.ibm_classify_noalloc(8, 8, 8, p, p, p, None, 3, p, 1, p, cp, None) == ibm.IBM_E_ARG
     assert L.ibm_classify_noalloc(1, 8, 8, p, p, p, p, 3, p, 1, p, cp, None) == ibm.IBM_E_ARG
+
+
+def test_mesh_area():
+    from paper_2505_17287_amd import inputs as I
+
+    f = I.uniform_faces(-1.0, 1.0, 64)
+    v, t = I.aabb_mesh((-0.5, -0.25, -0.125), (0.5, 0.25, 0.375))
+    n = 64 ** 3
+    # faces 1 x 1/2, 1 x 1/2 and 1/2 x 1/2, twice each: exact in binary
+    assert ibm.estimate_max_ghosts(f, f, f, v, t) == min(n, int(4.0 * 2.5 * 32 ** 2 + 4096))
+    bad = t.copy()
+    bad[3, 1] = len(v)
+    with pytest.raises(IndexError):
+        ibm.estimate_max_ghosts(f, f, f, v, bad)
