@@ -288,6 +288,11 @@ size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int6
             }
         }
     }
+    G->tail.c64 = P.take<double>(8 * TAIL_E);
+    G->tail.c32 = P.take<float>(8 * TAIL_E);
+    G->tail.w = P.take<double>(3 * TAIL_E);
+    G->tail.meta = P.take<uint2>(TAIL_E);
+    G->tail.down = P.take<uint32_t>(TAIL_E);
     // the largest of: reductions over RED_BLOCKS workgroups (up to 4 sums), the coarsening
     // sums, and one Krylov operator pass (2 sums per z-march workgroup, then 2 per ghost block)
     G->partials = P.take<double>(std::max<int64_t>(

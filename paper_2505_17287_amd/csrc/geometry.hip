@@ -1559,6 +1559,8 @@ hipError_t launch_hierarchy(ibm_grid *g, hipStream_t s) {
                            g->type, C, C1.active, F0.plo[0], F0.phi[0], F0.plo[1], F0.phi[1], F0.plo[2], F0.phi[2],
                            g->inject0);
     }
+    const hipError_t e = launch_tail_tables(g, s);
+    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 

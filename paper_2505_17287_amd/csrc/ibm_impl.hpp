@@ -192,6 +192,22 @@ struct LevelHost {
     double vol_active = 0.0;  // device-computed, copied back at hierarchy build
 };
 
+// the levels that one workgroup takes to the bottom of the V-cycle (tail.hip): the first has at
+// most SMALL_LEVEL cells, the others together take at most TAIL_E - SMALL_LEVEL table entries
+constexpr int SMALL_CPT = 4, SMALL_LEVEL = 1024 * SMALL_CPT;
+constexpr int TAIL_MAX = 8, TAIL_E = 2 * SMALL_LEVEL;
+struct TailTables {  // per cell of those levels, rebuilt with the hierarchy
+    double *c64 = nullptr;     // 8 x TAIL_E coefficients
+    float *c32 = nullptr;
+    double *w = nullptr;       // 3 x TAIL_E prolongation weights
+    uint2 *meta = nullptr;     // TAIL_E
+    uint32_t *down = nullptr;  // TAIL_E
+};
+int tail_first(const LevelHost *lev, int nlev);  // the first such level; nlev: none
+hipError_t launch_tail_tables(ibm_grid *g, hipStream_t s);
+template <typename T>
+hipError_t launch_tail(ibm_grid *g, int lt, const Coarse<T> &first, int nparts, const ibm_solve_opts *o, hipStream_t s);
+
 enum Stage { ST_CREATED = 0, ST_BOUND = 1, ST_GEOMETRY = 2, ST_CLASSIFIED = 3, ST_STENCILS = 4 };
 
 struct SolveState {  // in-flight solve of the step API
@@ -294,6 +310,7 @@ struct ibm_grid {
     // multigrid
     int nlev = 0;
     ibm::LevelHost lev[ibm::MAX_LEVELS];
+    ibm::TailTables tail;
     double *partials = nullptr;            // RED_BLOCKS * 4 doubles
     ibm::Scalars *sc = nullptr;            // device scalars
     ibm::Scalars *sc_host = nullptr;       // pinned host mirror

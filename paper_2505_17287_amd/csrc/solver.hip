@@ -623,7 +623,6 @@ __global__ void k_sweepC(Coarse<T> L, int colour) {
 // iterate lives in LDS, so a colour costs one LDS pass and one barrier instead of a launch.
 // remove_mean != 0 (coarsest level): afterwards subtract the volume-weighted mean over the
 // active cells.  The arithmetic of every cell is that of k_sweepC.
-constexpr int SMALL_CPT = 4, SMALL_LEVEL = 1024 * SMALL_CPT;
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps, const double *vol, int remove_mean) {
     __shared__ double sh[NT / 64];
@@ -704,290 +703,6 @@ __global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps, const d
     for (int c = 0; c < SMALL_CPT; ++c) {
         const int id = (int)threadIdx.x + NT * c;
         if (fl[c] & 1u) L.e[id] = (remove_mean && (fl[c] & 2u)) ? es[id] - (T)mean : es[id];
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// The tail of the V-cycle in one workgroup: every level from the first one with at most
-// SMALL_LEVEL cells down to the coarsest.  Pre-smoothing, residual and restriction, the
-// coarsest sweeps with mean removal, prolongation and post-smoothing of these levels run
-// with the iterates in LDS, separated by workgroup barriers; right-hand sides and
-// coefficients stay in global memory (they are small and cache-resident).  Per cell the
-// arithmetic is that of k_sweepC / k_resrestrictC / k_prolongC / k_coarsest.
-// ---------------------------------------------------------------------------------------
-constexpr int TAIL_MAX = 8, TAIL_NT = 1024, TAIL_E = 2 * SMALL_LEVEL;
-
-template <typename T>
-struct TailArgs {
-    int nl;                   // tail levels; index 0 is the first, nl - 1 the coarsest
-    Coarse<T> L[TAIL_MAX];    // level views (e and R in global memory)
-    ProlongTab P[TAIL_MAX];   // P[q]: table of tail level q from level q + 1
-    const int *cs[TAIL_MAX][3];  // cs[q]: children starts of tail level q + 1 in level q
-    int off[TAIL_MAX];        // offset of each level's iterate in LDS
-    const double *vol[TAIL_MAX];
-    double *mu[TAIL_MAX];
-    const double *partials;   // restriction partials of tail level 0
-    int nparts, nu1, nu2, ncoarse;
-};
-
-template <typename T>
-__device__ __forceinline__ void tail_ijk(const Coarse<T> &L, int id, int &I, int &J, int &K) {
-    I = id % L.n[0];
-    J = (id / L.n[0]) % L.n[1];
-    K = id / (L.n[0] * L.n[1]);
-}
-
-// prolongation into a tail level from the next coarser one (both held in LDS)
-template <typename T>
-struct TailUp {
-    const T *ec;           // coarser iterate
-    const uint8_t *cact;   // coarser active flags
-    int cn0, cn1;          // coarser x and y sizes
-    const ProlongTab *P;   // table of this level from the coarser one
-};
-
-// One tail level in one workgroup: optional prolongation from the coarser level (up leg),
-// ns red-black sweeps on the LDS iterate es, optional removal of the volume-weighted active
-// mean (coarsest level), optional residual into rs (down leg).  A thread owns cells
-// tid + TAIL_NT c and keeps their coefficients in registers through all three phases; the
-// sweep multiplies by the reciprocal of the diagonal.  act: the level's active flags (LDS).
-template <typename T>
-__device__ void tail_smooth(const Coarse<T> &L, T *es, const uint8_t *act, int ns, T mu, const double *vol,
-                            int remove_mean, const TailUp<T> *up, T *rs, double *sh, double *mean_s) {
-    const int NC = L.n[0] * L.n[1] * L.n[2];
-    const int sy = L.n[0], sz = L.n[0] * L.n[1];
-    unsigned fl[SMALL_CPT];
-    T txm[SMALL_CPT], txp[SMALL_CPT], tym[SMALL_CPT], typ[SMALL_CPT], tzm[SMALL_CPT], tzp[SMALL_CPT];
-    T rhs[SMALL_CPT], inv[SMALL_CPT];
-#pragma unroll
-    for (int c = 0; c < SMALL_CPT; ++c) {
-        const int id = (int)threadIdx.x + TAIL_NT * c;
-        const bool live = id < NC;
-        const int idc = live ? id : 0;
-        int I, J, K;
-        tail_ijk(L, idc, I, J, K);
-        const bool hx1 = I < L.n[0] - 1, hy1 = J < L.n[1] - 1, hz1 = K < L.n[2] - 1;
-        fl[c] = (live ? 1u : 0u) | ((live && act[idc] != 0) ? 2u : 0u) | ((unsigned)((I + J + K) & 1) << 2) |
-                (I > 0 ? 8u : 0u) | (hx1 ? 16u : 0u) | (J > 0 ? 32u : 0u) | (hy1 ? 64u : 0u) | (K > 0 ? 128u : 0u) |
-                (hz1 ? 256u : 0u);
-        txm[c] = L.Tl[0][idc];
-        txp[c] = hx1 ? L.Tl[0][idc + 1] : T(0);
-        tym[c] = L.Tl[1][idc];
-        typ[c] = hy1 ? L.Tl[1][idc + sy] : T(0);
-        tzm[c] = L.Tl[2][idc];
-        tzp[c] = hz1 ? L.Tl[2][idc + sz] : T(0);
-        const T v = (L.w[0][I] * L.w[1][J]) * L.w[2][K];
-        rhs[c] = L.R[idc] - v * mu;
-        T d = txm[c] + txp[c];
-        d = d + tym[c];
-        d = d + typ[c];
-        d = d + tzm[c];
-        d = d + tzp[c];
-        inv[c] = d > T(0) ? T(1) / d : T(0);
-        if (up && (fl[c] & 2u)) {
-            // trilinear from the 2 x 2 x 2 nearest coarser centres, or the parent's value when
-            // one of them is inactive (the parent is the first contributor on every axis)
-            const ProlongTab &P = *up->P;
-            const int ix[2] = {P.lo[0][I], P.hi[0][I]}, iy[2] = {P.lo[1][J], P.hi[1][J]},
-                      iz[2] = {P.lo[2][K], P.hi[2][K]};
-            const double tx = P.t[0][I], ty = P.t[1][J], tz = P.t[2][K];
-            const double wx[2] = {1.0 - tx, tx}, wy[2] = {1.0 - ty, ty}, wz[2] = {1.0 - tz, tz};
-            const int nx_ = (ix[0] == ix[1]) ? 1 : 2, ny_ = (iy[0] == iy[1]) ? 1 : 2, nz_ = (iz[0] == iz[1]) ? 1 : 2;
-            bool all = true;
-            double sv = 0.0;
-            for (int cz = 0; cz < nz_; ++cz)
-                for (int b = 0; b < ny_; ++b)
-                    for (int a = 0; a < nx_; ++a) {
-                        const int cid = (iz[cz] * up->cn1 + iy[b]) * up->cn0 + ix[a];
-                        if (!up->cact[cid]) all = false;
-                        sv += (wx[a] * wy[b]) * wz[cz] * (double)up->ec[cid];
-                    }
-            if (!all) sv = (double)up->ec[(iz[0] * up->cn1 + iy[0]) * up->cn0 + ix[0]];
-            es[id] = (T)((double)es[id] + sv);  // the thread's own cell: no other thread reads it yet
-        }
-    }
-    if (up) __syncthreads();
-    // a level that the first wave holds alone (cells of a thread are tid + TAIL_NT c, so with
-    // NC <= 64 only lanes of wave 0 own cells) is swept by that wave in registers, one cell
-    // per lane: the neighbours' values arrive by lane permutation (their lanes are the cell
-    // offsets -1, +1, -sy, +sy, -sz, +sz, clamped into the wave; a missing neighbour is masked
-    // by its flag), so a colour costs one permute round trip and no LDS store or barrier
-    const bool one_wave = NC <= 64;
-    if (one_wave) {
-        if (threadIdx.x < 64) {
-            const int id = (int)threadIdx.x;
-            const unsigned f = fl[0];
-            const bool upd = (f & 2u) && inv[0] > T(0);
-            const unsigned mycol = (f >> 2) & 1u;
-            const int lxm = max(id - 1, 0), lxp = min(id + 1, 63), lym = max(id - sy, 0), lyp = min(id + sy, 63),
-                      lzm = max(id - sz, 0), lzp = min(id + sz, 63);
-            T x = (f & 1u) ? es[id] : T(0);
-            for (int sw = 0; sw < ns; ++sw) {
-                for (unsigned col = 0; col < 2; ++col) {
-                    const T xm = __shfl(x, lxm, 64), xp = __shfl(x, lxp, 64), ym = __shfl(x, lym, 64),
-                            yp = __shfl(x, lyp, 64), zm = __shfl(x, lzm, 64), zp = __shfl(x, lzp, 64);
-                    if (upd && mycol == col) {
-                        T num = 0;
-                        num = num + ((f & 8u) ? txm[0] * xm : T(0));
-                        num = num + ((f & 16u) ? txp[0] * xp : T(0));
-                        num = num + ((f & 32u) ? tym[0] * ym : T(0));
-                        num = num + ((f & 64u) ? typ[0] * yp : T(0));
-                        num = num + ((f & 128u) ? tzm[0] * zm : T(0));
-                        num = num + ((f & 256u) ? tzp[0] * zp : T(0));
-                        x = (num - rhs[0]) * inv[0];
-                    }
-                }
-            }
-            if (f & 1u) es[id] = x;
-        }
-        __syncthreads();
-    } else {
-        for (int sw = 0; sw < ns; ++sw) {
-            for (unsigned col = 0; col < 2; ++col) {
-#pragma unroll
-                for (int c = 0; c < SMALL_CPT; ++c) {
-                    const int id = (int)threadIdx.x + TAIL_NT * c;
-                    const unsigned f = fl[c];
-                    if ((f & 2u) && ((f >> 2) & 1u) == col && inv[c] > T(0)) {
-                        T num = 0;
-                        num = num + ((f & 8u) ? txm[c] * es[id - 1] : T(0));
-                        num = num + ((f & 16u) ? txp[c] * es[id + 1] : T(0));
-                        num = num + ((f & 32u) ? tym[c] * es[id - sy] : T(0));
-                        num = num + ((f & 64u) ? typ[c] * es[id + sy] : T(0));
-                        num = num + ((f & 128u) ? tzm[c] * es[id - sz] : T(0));
-                        num = num + ((f & 256u) ? tzp[c] * es[id + sz] : T(0));
-                        es[id] = (num - rhs[c]) * inv[c];
-                    }
-                }
-                __syncthreads();
-            }
-        }
-    }
-    if (remove_mean) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < SMALL_CPT; ++c) {
-            const int id = (int)threadIdx.x + TAIL_NT * c;
-            if (fl[c] & 2u) {
-                int I, J, K;
-                tail_ijk(L, id, I, J, K);
-                acc += (double)((L.w[0][I] * L.w[1][J]) * L.w[2][K]) * (double)es[id];
-            }
-        }
-        const double tot = block_sum<TAIL_NT>(acc, sh, threadIdx.x);
-        if (threadIdx.x == 0) *mean_s = (*vol > 0.0) ? tot / *vol : 0.0;
-        __syncthreads();
-        const T m = (T)*mean_s;
-#pragma unroll
-        for (int c = 0; c < SMALL_CPT; ++c) {
-            const int id = (int)threadIdx.x + TAIL_NT * c;
-            if (fl[c] & 2u) es[id] -= m;
-        }
-        __syncthreads();
-    }
-    if (rs) {
-        // residual (R - V mu) - (A e) of the active cells, 0 elsewhere
-#pragma unroll
-        for (int c = 0; c < SMALL_CPT; ++c) {
-            const int id = (int)threadIdx.x + TAIL_NT * c;
-            const unsigned f = fl[c];
-            if (!(f & 1u)) continue;
-            T r = T(0);
-            if (f & 2u) {
-                T sm = 0;
-                sm = sm + ((f & 8u) ? txm[c] * es[id - 1] : T(0));
-                sm = sm + ((f & 16u) ? txp[c] * es[id + 1] : T(0));
-                sm = sm + ((f & 32u) ? tym[c] * es[id - sy] : T(0));
-                sm = sm + ((f & 64u) ? typ[c] * es[id + sy] : T(0));
-                sm = sm + ((f & 128u) ? tzm[c] * es[id - sz] : T(0));
-                sm = sm + ((f & 256u) ? tzp[c] * es[id + sz] : T(0));
-                T d = txm[c] + txp[c];
-                d = d + tym[c];
-                d = d + typ[c];
-                d = d + tzm[c];
-                d = d + tzp[c];
-                r = rhs[c] - (sm - d * es[id]);
-            }
-            rs[id] = r;
-        }
-        __syncthreads();
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(TAIL_NT) k_tailC(TailArgs<T> A) {
-    __shared__ T es[TAIL_E];           // iterates of all tail levels
-    __shared__ T rs[SMALL_LEVEL];      // residual of the level being restricted
-    __shared__ uint8_t acts[TAIL_E];   // active flags of all tail levels
-    __shared__ double sh[TAIL_NT / 64];
-    __shared__ double mean_s, mu_s[TAIL_MAX];
-    const int tid = threadIdx.x;
-    {   // mu of the first tail level from the restriction partials; activity of every level
-        double a = 0.0;
-        for (int q = tid; q < A.nparts; q += TAIL_NT) a += A.partials[q];
-        for (int q = 0; q < A.nl; ++q) {
-            const int n = A.L[q].n[0] * A.L[q].n[1] * A.L[q].n[2];
-            for (int id = tid; id < n; id += TAIL_NT) acts[A.off[q] + id] = A.L[q].active[id];
-        }
-        const double tot = block_sum<TAIL_NT>(a, sh, tid);
-        if (tid == 0) {
-            const double m = (*A.vol[0] > 0.0) ? tot / *A.vol[0] : 0.0;
-            mu_s[0] = m;
-            *A.mu[0] = m;
-        }
-        const int n0 = A.L[0].n[0] * A.L[0].n[1] * A.L[0].n[2];
-        for (int id = tid; id < n0; id += TAIL_NT) es[A.off[0] + id] = T(0);
-        __syncthreads();
-    }
-    // down: smooth and form the residual, restrict it (inactive cells hold a zero residual)
-    for (int q = 0; q + 1 < A.nl; ++q) {
-        const Coarse<T> &L = A.L[q];
-        tail_smooth<T>(L, es + A.off[q], acts + A.off[q], A.nu1, (T)mu_s[q], A.vol[q], 0, nullptr, rs, sh, &mean_s);
-        const Coarse<T> &C = A.L[q + 1];
-        const int *const *cs = A.cs[q];
-        const int NCC = C.n[0] * C.n[1] * C.n[2];
-        double psum = 0.0;
-        for (int cid = tid; cid < NCC; cid += TAIL_NT) {
-            int I, J, K;
-            tail_ijk(C, cid, I, J, K);
-            T R = 0;
-            for (int k = cs[2][K]; k < cs[2][K + 1]; ++k)
-                for (int j = cs[1][J]; j < cs[1][J + 1]; ++j)
-                    for (int i = cs[0][I]; i < cs[0][I + 1]; ++i) R += rs[(k * L.n[1] + j) * L.n[0] + i];
-            C.R[cid] = R;
-            es[A.off[q + 1] + cid] = T(0);
-            psum += (double)R;
-        }
-        const double tot = block_sum<TAIL_NT>(psum, sh, tid);
-        if (tid == 0) {
-            const double m = (*A.vol[q + 1] > 0.0) ? tot / *A.vol[q + 1] : 0.0;
-            mu_s[q + 1] = m;
-            *A.mu[q + 1] = m;
-        }
-        __syncthreads();
-    }
-    // coarsest
-    {
-        const int q = A.nl - 1;
-        tail_smooth<T>(A.L[q], es + A.off[q], acts + A.off[q], A.ncoarse, (T)mu_s[q], A.vol[q], 1, nullptr, nullptr,
-                       sh, &mean_s);
-    }
-    // up: prolong and smooth
-    for (int q = A.nl - 2; q >= 0; --q) {
-        TailUp<T> up;
-        up.ec = es + A.off[q + 1];
-        up.cact = acts + A.off[q + 1];
-        up.cn0 = A.L[q + 1].n[0];
-        up.cn1 = A.L[q + 1].n[1];
-        up.P = &A.P[q];
-        tail_smooth<T>(A.L[q], es + A.off[q], acts + A.off[q], A.nu2, (T)mu_s[q], A.vol[q], 0, &up, nullptr, sh,
-                       &mean_s);
-    }
-    // the first tail level's correction goes back to global memory for the prolongation above
-    {
-        const Coarse<T> &L = A.L[0];
-        const int NC = L.n[0] * L.n[1] * L.n[2];
-        for (int id = tid; id < NC; id += TAIL_NT) L.e[id] = es[A.off[0] + id];
     }
 }
 
@@ -1522,19 +1237,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
     }
     if (g->nlev > 1) {
         const int Lc = g->nlev - 1;
-        // the tail: every level from the first one with at most SMALL_LEVEL cells down to the
-        // coarsest, run by one workgroup, when those levels fit its LDS together (TAIL_E cells)
-        // and number at most TAIL_MAX; else the tail starts further down
-        int lt = Lc + 1;
-        for (int l = 1; l <= Lc; ++l) {
-            if (g->lev[l].ncell() > SMALL_LEVEL || Lc - l + 1 > TAIL_MAX) continue;
-            int64_t tot = 0;
-            for (int q = l; q <= Lc; ++q) tot += g->lev[q].ncell();
-            if (tot <= TAIL_E) {
-                lt = l;
-                break;
-            }
-        }
+        const int lt = tail_first(g->lev, g->nlev);
         const bool tail = lt <= Lc;
         const int Lb = tail ? lt : Lc;  // levels 1 .. Lb-1 run level by level
         int nparts = 0;                 // restriction partials into level Lb
@@ -1574,27 +1277,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
                                    &g->sc->mu[l + 1]);
         }
         if (tail) {
-            TailArgs<T> A;
-            A.nl = Lc - lt + 1;
-            int off = 0;
-            for (int q = 0; q < A.nl; ++q) {
-                const int l = lt + q;
-                A.L[q] = coarse_view<T>(g, l);
-                if (q + 1 < A.nl) {
-                    A.P[q] = prolong_tab(g, l);
-                    for (int d = 0; d < 3; ++d) A.cs[q][d] = g->lev[l + 1].cs_d[d];
-                }
-                A.off[q] = off;
-                off += (int)g->lev[l].ncell();
-                A.vol[q] = &g->sc->vol[l];
-                A.mu[q] = &g->sc->mu[l];
-            }
-            A.partials = g->partials;
-            A.nparts = nparts;
-            A.nu1 = o->nu1;
-            A.nu2 = o->nu2;
-            A.ncoarse = o->coarsest_sweeps;
-            hipLaunchKernelGGL(k_tailC<T>, dim3(1), dim3(TAIL_NT), 0, s, A);
+            if ((e = launch_tail<T>(g, lt, coarse_view<T>(g, lt), nparts, o, s)) != hipSuccess) return e;
         } else if (g->lev[Lc].ncell() <= SMALL_LEVEL) {
             launch_smallC<T>(coarse_view<T>(g, Lc), g->lev[Lc].ncell(), o->coarsest_sweeps, &g->sc->vol[Lc], 1, s);
         } else {
