@@ -68,6 +68,12 @@ hipError_t launch_sweep(const Fine<T> &F, const T *pin, T *pout, const T *f, con
 hipError_t launch_sweep_widen(const Fine<float> &F, const float *pin, double *pout, const float *f, const float *lam,
                               hipStream_t s);
 
+// the same sweep by bricks (sweepb.hip), which launch_sweep takes for small grids
+constexpr int64_t BRICK_LARGE_CELLS = 1 << 20;  // larger bricks from here
+template <typename T, typename TO>
+hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T *f, const T *lam, hipStream_t s,
+                              hipEvent_t ev0, hipEvent_t ev1);
+
 // fused red-black sweep of a coarse level (sweepc.hip): eout = one RB-GS sweep of L.e, the
 // two buffers distinct; for levels of at least SWC_MIN_CELLS cells (sweepC_fused_ok)
 bool sweepC_fused_ok(const int n[3]);

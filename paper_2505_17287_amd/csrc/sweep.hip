@@ -369,15 +369,28 @@ static hipError_t launch_sweep_tiles(const Fine<T> &F, const T *pin, TO *pout, c
     return hipGetLastError();
 }
 
+// Grids that the bricks of sweepb.hip sweep faster than this z-march.  us per sweep, bricks
+// against z-march: FP64, even rows 64^3 4.6 / 21, 128^3 15.7 / 26, 160^3 27.9 / 30.5, 176^3 33.1 /
+// 32.5, 192^3 44 / 42, 128 x 128 3.5 / 6.3; odd rows (the z-march's unpaired loads) 97 x 83 x 71
+// 8.7 / 17.6, 161 x 159 x 157 27.9 / 36.5, 211^3 56 / 67.  FP32, five BiCGStab steps: 128^3 3.02 /
+// 3.22 ms, 160^3 4.62 / 4.41; odd 161 x 159 x 157 5.08 / 5.18, 189^3 6.27 / 6.27.
+template <typename T>
+static bool by_bricks(int nx, int ny, int nz) {
+    const int64_t even = sizeof(T) == 8 ? 5 << 20 : 3 << 20, odd = sizeof(T) == 8 ? 12 << 20 : 6 << 20;
+    return (int64_t)nx * ny * nz <= ((nx & 1) ? odd : even);  // at most 2^24: the bricks' index arithmetic
+}
+
 template <typename T>
 hipError_t launch_sweep(const Fine<T> &F, const T *pin, T *pout, const T *f, const T *lam, hipStream_t s,
                         hipEvent_t ev0, hipEvent_t ev1) {
+    if (by_bricks<T>(F.nx, F.ny, F.nz)) return launch_sweep_brick<T, T>(F, pin, pout, f, lam, s, ev0, ev1);
     if ((F.nx & 1) == 0) return launch_sweep_tiles<T, T, 32, true>(F, pin, pout, f, lam, s, ev0, ev1);
     return launch_sweep_tiles<T, T, 16, false>(F, pin, pout, f, lam, s, ev0, ev1);
 }
 
 hipError_t launch_sweep_widen(const Fine<float> &F, const float *pin, double *pout, const float *f, const float *lam,
                               hipStream_t s) {
+    if (by_bricks<float>(F.nx, F.ny, F.nz)) return launch_sweep_brick<float, double>(F, pin, pout, f, lam, s, nullptr, nullptr);
     if ((F.nx & 1) == 0) return launch_sweep_tiles<float, double, 32, true>(F, pin, pout, f, lam, s);
     return launch_sweep_tiles<float, double, 16, false>(F, pin, pout, f, lam, s);
 }

@@ -1,0 +1,59 @@
+"""The fine sweep by bricks: bitwise equal to the oracle's two colour passes at the edges of the
+brick shapes (rows of 64 and 128 columns with and without a halo, remainders along every axis,
+odd rows, one plane), and the FP32 and widening forms through the mixed solve."""
+import numpy as np
+import pytest
+
+from oracle import OracleProblem
+from paper_2505_17287_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(2, 2, 1), (2, 3, 2), (5, 4, 3), (63, 9, 1), (64, 8, 1), (65, 17, 1), (128, 7, 1), (62, 5, 4), (64, 4, 4),
+         (66, 9, 5), (120, 6, 7), (121, 5, 9), (127, 10, 3), (129, 4, 6), (66, 130, 124), (128, 90, 92), (127, 91, 92),
+         (150, 92, 78)]
+
+
+def _problem(dims):
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    rng = np.random.default_rng(sum(dims))
+    f = [np.concatenate([[0.0], np.cumsum(rng.uniform(0.8, 1.2, n))]) for n in dims]
+    c = [0.5 * a[-1] for a in f]
+    if dims[2] == 1:
+        v, t = I.prism_mesh(0.2 * min(f[0][-1], f[1][-1]), 16, -1.0, 2.0, center=(c[0], c[1]))
+    else:
+        v, t = I.icosphere(2)
+        v = v * 0.27 * min(a[-1] for a in f) + np.array(c)
+    P = OracleProblem(*f)
+    P.set_mesh(v, t)
+    P.classify()
+    g = ibm.Grid(*f, precision="mixed")
+    g.set_geometry(v, t)
+    g.classify()
+    p, rhs = (rng.uniform(-1.0, 1.0, (dims[2], dims[1], dims[0])) for _ in range(2))
+    return torch, P, g, p, rhs
+
+
+@pytest.mark.parametrize("dims", SIZES, ids=lambda d: "x".join(map(str, d)))
+def test_brick_sweep_is_bitwise_the_two_pass_sweep(dims):
+    torch, P, g, p, rhs = _problem(dims)
+    ref = P.sweep(p, rhs, lam=0.3, nsweeps=2, refresh=False)
+    out = g.debug_sweep(torch.from_numpy(p).cuda(), torch.from_numpy(rhs).cuda(), lam=0.3, n=2)
+    fluid = P.types() == 0
+    assert np.array_equal(out.cpu().numpy()[fluid], ref[fluid])
+    assert np.array_equal(out.cpu().numpy()[~fluid], p[~fluid])  # the others keep their values
+
+
+@pytest.mark.parametrize("dims", [(65, 17, 1), (66, 9, 8), (121, 8, 9), (128, 90, 92), (127, 91, 92)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_mixed_cycle_by_bricks(dims):
+    torch, P, g, p, rhs = _problem(dims)
+    g.build_ghost_stencils()
+    r = torch.from_numpy(rhs).cuda()
+    a, _ = g.poisson_solve(r, precision="fp64", rel_tol=1e-12, max_cycles=60)
+    b, st = g.poisson_solve(r, precision="mixed", rel_tol=1e-12, max_cycles=60)
+    assert st.status == 0
+    assert float((a - b).abs().max() / a.abs().max()) <= 1e-8
