@@ -272,7 +272,7 @@ size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int6
             L.R64 = P.take<double>(NC);
             L.e32 = P.take<float>(NC);
             L.R32 = P.take<float>(NC);
-            if (sweepC_fused_ok(L.n)) {
+            if (NC > SMALL_LEVEL) {
                 L.e64b = P.take<double>(NC);
                 L.e32b = P.take<float>(NC);
             } else {

@@ -74,11 +74,17 @@ template <typename T, typename TO>
 hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T *f, const T *lam, hipStream_t s,
                               hipEvent_t ev0, hipEvent_t ev1);
 
-// fused red-black sweep of a coarse level (sweepc.hip): eout = one RB-GS sweep of L.e, the
-// two buffers distinct; for levels of at least SWC_MIN_CELLS cells (sweepC_fused_ok)
-bool sweepC_fused_ok(const int n[3]);
+// where a coarse level's first sweep gets mu (sweepc.hip); n = 0: mu is there already
+struct MuSource {
+    const double *partials = nullptr;  // n sums of the restriction
+    int n = 0;
+    const double *vol = nullptr;
+    double *mu = nullptr;
+};
+// red-black sweep of a coarse level (sweepc.hip): eout = one RB-GS sweep of L.e, the two buffers
+// distinct; zero: L.e counts as zero and need not be read
 template <typename T>
-hipError_t launch_sweepC_fused(const Coarse<T> &L, T *eout, hipStream_t s);
+hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s);
 
 // fine index -> (lo, hi, weight of hi) per axis; lo is always the parent (the coarse cell
 // holding the fine one)
@@ -184,8 +190,8 @@ struct LevelHost {
     double *c64[3] = {nullptr, nullptr, nullptr};
     double *e64 = nullptr, *R64 = nullptr;
     float *e32 = nullptr, *R32 = nullptr;
-    // second error buffer of the out-of-place coarse sweep (levels that sweepC_fused_ok
-    // accepts); swapped with e after each sweep
+    // second error buffer of the out-of-place coarse sweep (levels of more than SMALL_LEVEL
+    // cells); swapped with e after each sweep
     double *e64b = nullptr;
     float *e32b = nullptr;
     // prolongation tables of THIS level from the next coarser one

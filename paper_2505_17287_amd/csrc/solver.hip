@@ -254,40 +254,8 @@ __device__ __forceinline__ void coarse_stencil(const Coarse<T> &L, const T *__re
 // residual + restriction, fused with block partial sums of the coarse right-hand side
 // =======================================================================================
 
-// level l -> l+1 (l >= 1): R_{l+1}(C) = sum over active children of r, r = (R - V mu) - S e;
-// the children (one or two per axis) are summed x fastest, then y, then z
-template <typename T>
-__global__ void k_resrestrictC(Coarse<T> L, Coarse<T> C, ChildMap M, double *partials) {
-    __shared__ double sh[4];
-    const int64_t NC = (int64_t)C.n[0] * C.n[1] * C.n[2];
-    const int64_t cid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double Rsum = 0.0;
-    if (cid < NC) {
-        const T mu = (T)(*L.mu);
-        int I, J, K;
-        unflatten(cid, C.n[0], C.n[1], I, J, K);
-        const int i0 = M.cs[0][I], i1 = M.cs[0][I + 1], j0 = M.cs[1][J], j1 = M.cs[1][J + 1];
-        const int k0 = M.cs[2][K], k1 = M.cs[2][K + 1];
-        T R = 0;
-        for (int k = k0; k < k1; ++k)
-            for (int j = j0; j < j1; ++j)
-                for (int i = i0; i < i1; ++i) {
-                    const int64_t id = ((int64_t)k * L.n[1] + j) * L.n[0] + i;
-                    T num, diag;
-                    coarse_stencil(L, L.e, i, j, k, id, num, diag);
-                    const T vol = (L.w[0][i] * L.w[1][j]) * L.w[2][k];
-                    const T rc = (L.R[id] - vol * mu) - (num - diag * L.e[id]);
-                    if (L.active[id]) R += rc;
-                }
-        C.R[cid] = R;
-        C.e[cid] = T(0);
-        Rsum = (double)R;
-    }
-    double s = block_sum<256>(Rsum, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[blockIdx.x] = s;
-}
-
-// The same for any child map, row-wise (the tiling of the level-0 restriction k_restrict0_map):
+// level l -> l+1 (l >= 1): R_{l+1}(C) = sum over active children of r, r = (R - V mu) - S e, for
+// any child map, row-wise (the tiling of the level-0 restriction k_restrict0_map):
 // a wave owns one coarse row J (one or two finer rows) of a tile of RM_CX coarse columns, a
 // lane one finer column, and the lane marches up the finer planes with both rows in
 // registers; the x neighbours and the high x face come from the adjacent lanes (lanes 0 and
@@ -295,11 +263,11 @@ __global__ void k_resrestrictC(Coarse<T> L, Coarse<T> C, ChildMap M, double *par
 // high z face the next plane's low face, loaded with that plane.  Per cell the operations
 // are those of coarse_stencil; each lane sums its active cells over the rows and planes of
 // the current coarse plane, and when that plane is complete lane I - I0 adds the sums of the
-// one or two lanes holding the children of coarse column I (the same sum as
-// k_resrestrictC's, in another order).
-// the row-wise pass from levels of at least this many cells (below, a thread per coarse cell)
-constexpr int64_t RC_MAP_MIN_CELLS = 1 << 17;
-constexpr int RC_TILES_PER_CU = 8, RC_KMIN = 4;
+// one or two lanes holding the children of coarse column I.
+// Tiles down to one coarse plane: the smaller levels are bound by the serial finer planes of a
+// tile.  (A thread per coarse cell took 16 us on levels of 2 x 10^4 to 10^5 cells, and at least
+// four planes per tile 12 to 20 us on the larger ones: a wing solve 17.47 ms, 17.06 with this.)
+constexpr int RC_TILES_PER_CU = 8, RC_KMIN = 1;
 
 template <typename T>
 struct RCPlane {
@@ -486,7 +454,7 @@ __global__ void __launch_bounds__(RM_NT)
 // around the block and the high-face transmissibilities once, all before any arithmetic,
 // instead of rebuilding each child's stencil from scalar loads.  Per child the operations
 // are those of coarse_stencil, and the children are summed in the same order (x fastest,
-// then y, then z), so the result is bitwise that of k_resrestrictC.
+// then y, then z).
 template <typename T>
 __global__ void __launch_bounds__(256) k_resrestrictC8(Coarse<T> L, Coarse<T> C, double *partials) {
     using V = typename Pair2<T>::type;
@@ -593,36 +561,13 @@ __global__ void k_finalize_mu(const double *partials, int n, const double *vol, 
 // coarse levels: red-black GS on  sum_F T_F (e_NB - e_C) = R_C - V_C mu
 // =======================================================================================
 
-// one colour of a red-black sweep of a coarse level: a thread per cell of that colour (in
-// each x pair of a row exactly one cell has the colour), every load issued before the
-// activity test
-template <typename T>
-__global__ void k_sweepC(Coarse<T> L, int colour) {
-    const int hx = (L.n[0] + 1) >> 1;
-    const int64_t npair = (int64_t)hx * L.n[1] * L.n[2];
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= npair) return;
-    int P, J, K;
-    unflatten(t, hx, L.n[1], P, J, K);
-    const int I = 2 * P + ((J + K + colour) & 1);
-    if (I >= L.n[0]) return;
-    const int64_t id = ((int64_t)K * L.n[1] + J) * L.n[0] + I;
-    const uint8_t act = L.active[id];
-    T num, diag;
-    coarse_stencil(L, L.e, I, J, K, id, num, diag);
-    const T vol = (L.w[0][I] * L.w[1][J]) * L.w[2][K];
-    const T r = L.R[id];
-    if (act && diag > T(0)) L.e[id] = (num - (r - vol * (T)(*L.mu))) / diag;
-}
-
-
 // coarsest level in one workgroup: e = 0 (set by the restriction), n sweeps, then removal
 // of the volume-weighted mean over the active cells
 // nsweeps red-black sweeps of a level of at most SMALL_LEVEL cells in one workgroup of 1024
 // threads: each thread keeps the coefficients of up to SMALL_CPT cells in registers and the
 // iterate lives in LDS, so a colour costs one LDS pass and one barrier instead of a launch.
 // remove_mean != 0 (coarsest level): afterwards subtract the volume-weighted mean over the
-// active cells.  The arithmetic of every cell is that of k_sweepC.
+// active cells.  The arithmetic of every cell is that of launch_sweepC.
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps, const double *vol, int remove_mean) {
     __shared__ double sh[NT / 64];
@@ -1194,28 +1139,19 @@ static hipError_t timed_sweep(ibm_grid *g, const Fine<T> &F, const T *pin, T *po
     return hipSuccess;
 }
 
-// nsweeps red-black sweeps of coarse level l (more cells than the tail takes): the fused
-// out-of-place pass when the level has a second error buffer (the buffers are swapped after
-// each sweep, so every later view of the level sees the current one), else two one-colour
-// passes in place
+// nsweeps red-black sweeps of coarse level l (more than SMALL_LEVEL cells), out of place between
+// its two error buffers, which are swapped after each (every later view of the level sees the
+// current one).  The first sweep forms mu when ms has its partials; zero: the correction is 0.
 template <typename T>
-static hipError_t smooth_level(ibm_grid *g, int l, int nsweeps, hipStream_t s) {
+static hipError_t smooth_level(ibm_grid *g, int l, int nsweeps, const MuSource &ms, bool zero, hipStream_t s) {
     LevelHost &H = g->lev[l];
-    if (level_e2<T>(H) != nullptr) {
-        for (int q = 0; q < nsweeps; ++q) {
-            const hipError_t e = launch_sweepC_fused<T>(coarse_view<T>(g, l), level_e2<T>(H), s);
-            if (e != hipSuccess) return e;
-            std::swap(level_e<T>(H), level_e2<T>(H));
-        }
-        return hipSuccess;
-    }
-    const Coarse<T> L = coarse_view<T>(g, l);
-    const int nbh = nblk((int64_t)((H.n[0] + 1) / 2) * H.n[1] * H.n[2]);
     for (int q = 0; q < nsweeps; ++q) {
-        hipLaunchKernelGGL(k_sweepC<T>, dim3(nbh), dim3(256), 0, s, L, 0);
-        hipLaunchKernelGGL(k_sweepC<T>, dim3(nbh), dim3(256), 0, s, L, 1);
+        const hipError_t e = launch_sweepC<T>(coarse_view<T>(g, l), level_e2<T>(H), q == 0 ? ms : MuSource{},
+                                              zero && q == 0, s);
+        if (e != hipSuccess) return e;
+        std::swap(level_e<T>(H), level_e2<T>(H));
     }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 template <typename T>
@@ -1246,15 +1182,26 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
             if ((e = launch_restrict0<T>(F, bufs[*cur], rhs, lam, C1, child_map(g->lev[1]), g->partials, &nparts,
                                          s)) != hipSuccess)
                 return e;
-            if (!(tail && lt == 1))
-                hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nparts, &g->sc->vol[1],
-                                   &g->sc->mu[1]);
         }
+        // mu of level l from the partials of the restriction into it: by its first sweep where one
+        // follows, by the tail for its own levels, else by a launch
+        auto swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
+        auto finalize_mu = [&](int l) {
+            if (!swept(l) && !(tail && l == lt))
+                hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nparts, &g->sc->vol[l],
+                                   &g->sc->mu[l]);
+        };
+        finalize_mu(1);
         for (int l = 1; l < Lb; ++l) {
             if (g->lev[l].ncell() <= SMALL_LEVEL) {
                 if (o->nu1 > 0) launch_smallC<T>(coarse_view<T>(g, l), g->lev[l].ncell(), o->nu1, &g->sc->vol[l], 0, s);
-            } else if ((e = smooth_level<T>(g, l, o->nu1, s)) != hipSuccess) {
-                return e;
+            } else {
+                MuSource ms;
+                ms.partials = g->partials;
+                ms.n = nparts;
+                ms.vol = &g->sc->vol[l];
+                ms.mu = &g->sc->mu[l];
+                if ((e = smooth_level<T>(g, l, o->nu1, ms, true, s)) != hipSuccess) return e;
             }
             Coarse<T> L = coarse_view<T>(g, l);  // after the sweeps: the current error buffer
             Coarse<T> C = coarse_view<T>(g, l + 1);
@@ -1262,19 +1209,15 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
             int nbc = nblk(g->lev[l + 1].ncell());
             if (M.halved[0] && M.halved[1] && M.halved[2]) {
                 hipLaunchKernelGGL(k_resrestrictC8<T>, dim3(nbc), dim3(256), 0, s, L, C, g->partials);
-            } else if (g->lev[l].ncell() >= RC_MAP_MIN_CELLS) {
+            } else {
                 RowTiles t;
                 if ((e = row_tiles(C.n, RC_TILES_PER_CU, RC_KMIN, zmarch_partials_max(g->nx, g->ny, g->nz), &t,
                                    &nbc)) != hipSuccess)
                     return e;
                 hipLaunchKernelGGL(k_resrestrictC_map<T>, dim3(nbc), dim3(RM_NT), 0, s, L, C, M, t, g->partials);
-            } else {
-                hipLaunchKernelGGL(k_resrestrictC<T>, dim3(nbc), dim3(256), 0, s, L, C, M, g->partials);
             }
             nparts = nbc;
-            if (!(tail && l + 1 == lt))
-                hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nbc, &g->sc->vol[l + 1],
-                                   &g->sc->mu[l + 1]);
+            finalize_mu(l + 1);
         }
         if (tail) {
             if ((e = launch_tail<T>(g, lt, coarse_view<T>(g, lt), nparts, o, s)) != hipSuccess) return e;
@@ -1300,7 +1243,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
                 hipLaunchKernelGGL(k_prolongC<T>, dim3(nb), dim3(256), 0, s, L, coarse_view<T>(g, l + 1), PT);
             if (g->lev[l].ncell() <= SMALL_LEVEL) {
                 if (o->nu2 > 0) launch_smallC<T>(L, g->lev[l].ncell(), o->nu2, &g->sc->vol[l], 0, s);
-            } else if ((e = smooth_level<T>(g, l, o->nu2, s)) != hipSuccess) {
+            } else if ((e = smooth_level<T>(g, l, o->nu2, MuSource{}, false, s)) != hipSuccess) {
                 return e;
             }
         }

@@ -24,11 +24,28 @@ namespace ibm {
 // queue.  A face is open only when the fine cells on both of its sides are active, so a
 // cell with an open face is active and an inactive cell has none: the test sum_f T_f > 0
 // already excludes inactive cells, and the activity mask is not read.  Wall faces hold 0.
-// Per cell the operations and their order are those of the one-colour kernel (k_sweepC),
-// so both give the same bits.
 // Algorithmic traffic per cell: read e, R and three transmissibilities, write e
 // (48 B in FP64, 24 B in FP32).
 // =======================================================================================
+
+// The compatibility shift of a level's right-hand side, mu = sum of the restriction's partials /
+// active volume, formed by the level's first sweep itself (n > 0; every workgroup sums the
+// partials, in a fixed order, and the first tile's stores mu for the kernels that follow) instead of by
+// a launch of its own, which took 5 us on each level of each cycle.
+__device__ __forceinline__ void mu_partial(const MuSource &ms, double *sh) {
+    if (threadIdx.x >= 256) return;
+    double s = 0.0;
+    for (int q = (int)threadIdx.x; q < ms.n; q += 256) s += ms.partials[q];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+}
+// after a barrier
+__device__ __forceinline__ double mu_total(const MuSource &ms, const double *sh, bool store) {
+    const double tot = ((sh[0] + sh[1]) + sh[2]) + sh[3], vol = *ms.vol;
+    const double mu = vol > 0.0 ? tot / vol : 0.0;
+    if (store && threadIdx.x == 0) *ms.mu = mu;
+    return mu;
+}
 
 // one plane of a thread's two columns: old values, right-hand side, low-face
 // transmissibilities in x, y and z
@@ -41,17 +58,18 @@ struct CPlane {
 constexpr int SWC_KC_MAX = 512;  // longest z chunk of one workgroup
 constexpr int SWC_NC = 64;       // columns of a tile including the 2-column halo
 constexpr int SWC_KC_MIN = 8;    // shortest z chunk (each chunk re-reads four planes)
-// Levels below this size keep the two one-colour passes: there the z-march is bound by the
-// latency of its plane steps, not by bandwidth (at 64^3 the fused pass took 10.4 us against
-// 2 x 4.8 us; at 128^3 22 us against 2 x 19.5 us).
-constexpr int64_t SWC_MIN_CELLS = 3 << 17;
+// Levels below this size are swept by bricks (below): there the z-march is bound by the latency
+// of its plane steps, not by bandwidth.  With the bricks up to 2^20 cells a wing's FP64 solve
+// (levels of 5 x 10^5 and 8 x 10^5) takes 17.0 ms instead of 16.7, a 256^3 mixed one (76^3) 11.22
+// instead of 11.42.
+template <typename T>
+constexpr int64_t SWC_MIN_CELLS = sizeof(T) == 8 ? 3 << 17 : 1 << 20;
 
 // Relaxation value of one cell: the six neighbour products summed from zero in the order
 // -x, +x, -y, +y, -z, +z, the diagonal summed in the same order.  A missing neighbour meets
 // a zero transmissibility (a wall face, or a high face masked where the level ends), so its
 // product is an exact zero; the sum starts at +0 and never becomes -0, so adding that zero
-// changes nothing, and the result has the bits of the one-colour kernel, which skips the
-// term.
+// changes nothing.
 template <typename T>
 __device__ __forceinline__ T rbc_update(T txm, T txp, T tym, T typ, T tzm, T tzp, T xm, T xp, T ym, T yp, T zm, T zp,
                                         T r, T vol, T mu, T &diag) {
@@ -82,7 +100,7 @@ __device__ __forceinline__ T rbc_update(T txm, T txp, T tym, T typ, T tzm, T tzp
 // plane), so they enter no result.
 template <typename T, int BY, int QD, bool VEC>
 __global__ void __launch_bounds__(32 * BY)
-    k_rbgsC_fused(Coarse<T> L, T *__restrict__ eout, int ntx, int nty, int kc, int ntiles) {
+    k_rbgsC_fused(Coarse<T> L, T *__restrict__ eout, MuSource ms, int ntx, int nty, int kc, int ntiles) {
     static_assert(BY % 4 == 0, "two same-parity rows of 32 threads per wave");
     static_assert(QD == 4 || QD == 6, "planes held per thread");
     using V = typename Pair2<T>::type;
@@ -98,6 +116,7 @@ __global__ void __launch_bounds__(32 * BY)
     const int logical = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (logical >= ntiles) return;
     int tile = logical;
+    [[maybe_unused]] const int tile0 = tile;
     const int txi = tile % ntx;
     tile /= ntx;
     const int tyi = tile % nty;
@@ -148,7 +167,12 @@ __global__ void __launch_bounds__(32 * BY)
     const bool x1in = VEC || ia + 1 < nx;
     const T vxy0 = in0 ? L.w[0][ia] * L.w[1][jc] : T(0);
     const T vxy1 = in1 ? L.w[0][ia + 1] * L.w[1][jc] : T(0);
-    const T mu = (T)(*L.mu);
+    __shared__ double smu[4];
+    if (ms.n > 0) {
+        mu_partial(ms, smu);
+        __syncthreads();
+    }
+    const T mu = ms.n > 0 ? (T)mu_total(ms, smu, tile0 == 0) : (T)(*L.mu);
     // LDS rows and columns of the neighbours, clamped into the tile (lanes whose result is
     // discarded read valid entries)
     const int rym = max(ty - 1, 0), ryp = min(ty + 1, BY - 1);
@@ -338,13 +362,182 @@ struct SwcRows<float> {
     static constexpr int BY = 32, QD = 4;
 };
 
-bool sweepC_fused_ok(const int n[3]) {
-    return n[0] >= 2 && (int64_t)n[0] * n[1] * n[2] >= SWC_MIN_CELLS;
+// The sweep of a smaller level by bricks: the scheme of the fine level's bricks (sweepb.hip) with
+// the coarse operator.  Half a wave takes a row of 64 columns, a lane two adjacent columns; each
+// of the NT row takers updates NI rows of the brick's BY x BZ and NH of the ring around them, and
+// loads right-hand sides and transmissibilities of its rows along with the old values, all in
+// flight together.  zero: the level's correction is still zero, so no old values are read.
+// Two launches of one colour each took 2 x 4.7 us on levels of 10^4 to 10^5 cells; one of these
+// takes 5.9 to 6.3 us there (FP64) and 12.4 us at 72^3.  Cell by cell the operations are those of rbc_update, and a cell
+// without an open face keeps its value.
+template <typename T, int BY, int BZ, int NW>
+__global__ void __launch_bounds__(64 * NW, 4)
+    k_rbgsC_brick(Coarse<T> L, T *__restrict__ eout, MuSource ms, int zero, int ntx, int nty, int bx, int xoff,
+                  int ntiles) {
+    constexpr int LW = 32, NT = 2 * NW;
+    constexpr int HY = BY + 4, HZ = BZ + 4, ROWS = HY * HZ, NL = (ROWS + NT - 1) / NT;
+    constexpr int SIDES = 2 * (BZ + 2), RING = SIDES + 2 * BY;
+    constexpr int NI = BY * BZ / NT, NH = (RING + NT - 1) / NT, NU = NI + NH;
+    static_assert(NI * NT == BY * BZ, "interior rows divide among the takers");
+    typedef T U2 __attribute__((ext_vector_type(2)));
+    typedef U2 U __attribute__((aligned(sizeof(T))));
+    constexpr int P = LW + 1;
+    __shared__ T s[2][ROWS][P];  // even and odd columns, with guards: see sweepb.hip
+    __shared__ double smu[4];
+    const int per = gridDim.x >> 3;
+    const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (tile >= ntiles) return;
+    const int nx = L.n[0], ny = L.n[1], nz = L.n[2], tid = (int)threadIdx.x;
+    const int l = tid & (LW - 1), me = tid / LW;
+    const int x0 = tile % ntx * bx - xoff, y0 = tile / ntx % nty * BY - 2, z0 = tile / (ntx * nty) * BZ - 2;
+    const int i = x0 + 2 * l;
+    const bool in0 = i >= 0 && i < nx, in1 = i >= 0 && i + 1 < nx, in2 = i >= 0 && i + 2 < nx;
+    // unconditional loads at clamped places; what lies outside meets zero transmissibilities
+    const uint32_t ic = (uint32_t)min(max(i, 0), nx - 2), ip = (uint32_t)min(max(i + 2, 0), nx - 1);
+    const bool shf = i == nx - 1;
+    auto cell = [&](int y, int z) -> uint32_t {  // a level below SWC_MIN_CELLS: 24 bits
+        const uint32_t j = (uint32_t)min(max(y0 + y, 0), ny - 1), k = (uint32_t)min(max(z0 + z, 0), nz - 1);
+        return __umul24(__umul24(k, (uint32_t)ny) + j, (uint32_t)nx);
+    };
+    auto pair = [&](const T *a, uint32_t c) -> U {
+        U v = *reinterpret_cast<const U *>(a + c);
+        if (shf) v.x = v.y;
+        return v;
+    };
+    U v[NL];
+    {
+        int y = me % HY, z = me / HY;
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            v[q] = U{T(0), T(0)};
+            if (!zero) v[q] = pair(L.e, cell(y, z) + ic);
+            y += NT % HY;
+            z += NT / HY;
+            if (y >= HY) {
+                y -= HY;
+                ++z;
+            }
+        }
+    }
+    // the rows this taker updates.  Interior rows need both cells of the pair, ring rows the red one.
+    int yu[NU], zu[NU];
+    bool row[NU];
+    U r[NI], tx[NI], ty[NI], tyh[NI], tz[NI], tzh[NI];
+    T txh[NI], g[NH][7];
+#pragma unroll
+    for (int q = 0; q < NU; ++q) {
+        bool any = true;
+        if (q < NI) {
+            const int e = q * NT + me;
+            yu[q] = e % BY + 2;
+            zu[q] = e / BY + 2;
+        } else {
+            const int e = (q - NI) * NT + me, u = e - SIDES;
+            any = e < RING;
+            yu[q] = !any ? 1 : e < SIDES ? ((e & 1) ? BY + 2 : 1) : u % BY + 2;
+            zu[q] = !any ? 1 : e < SIDES ? (e >> 1) + 1 : u / BY ? BZ + 2 : 1;
+        }
+        const int j = y0 + yu[q], k = z0 + zu[q];
+        row[q] = any && j >= 0 && j < ny && k >= 0 && k < nz;
+        const uint32_t c0 = cell(yu[q], zu[q]), cy = cell(yu[q] + 1, zu[q]), cz = cell(yu[q], zu[q] + 1);
+        const bool hy = j + 1 < ny, hz = k + 1 < nz;
+        if (q < NI) {
+            r[q] = pair(L.R, c0 + ic);
+            tx[q] = pair(L.Tl[0], c0 + ic);
+            txh[q] = L.Tl[0][c0 + ip];
+            ty[q] = pair(L.Tl[1], c0 + ic);
+            tyh[q] = pair(L.Tl[1], cy + ic);
+            tz[q] = pair(L.Tl[2], c0 + ic);
+            tzh[q] = pair(L.Tl[2], cz + ic);
+            if (!in1) tx[q].y = T(0);  // the first cell's high face is the wall
+            if (!in2) txh[q] = T(0);
+            if (!hy) tyh[q] = U{T(0), T(0)};
+            if (!hz) tzh[q] = U{T(0), T(0)};
+        } else {
+            const int x = i + ((j + k) & 1);
+            const uint32_t xc = (uint32_t)min(max(x, 0), nx - 1), xp = (uint32_t)min(max(x + 1, 0), nx - 1);
+            T(&h)[7] = g[q - NI];
+            h[0] = L.Tl[0][c0 + xc];
+            h[1] = L.Tl[0][c0 + xp];
+            h[2] = L.Tl[1][c0 + xc];
+            h[3] = L.Tl[1][cy + xc];
+            h[4] = L.Tl[2][c0 + xc];
+            h[5] = L.Tl[2][cz + xc];
+            h[6] = L.R[c0 + xc];
+            if (x + 1 >= nx) h[1] = T(0);
+            if (!hy) h[3] = T(0);
+            if (!hz) h[5] = T(0);
+        }
+    }
+    const T wx[2] = {in0 ? L.w[0][i] : T(0), in1 ? L.w[0][i + 1] : T(0)};
+    if (ms.n > 0) mu_partial(ms, smu);
+    for (int q = tid; q < ROWS; q += 64 * NW) s[1][q][0] = s[0][q][LW] = T(0);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+        const int rr = q * NT + me;
+        if (rr < ROWS) {
+            s[0][rr][l] = v[q].x;
+            s[1][rr][l + 1] = v[q].y;
+        }
+    }
+    __syncthreads();
+    const T mu = ms.n > 0 ? (T)mu_total(ms, smu, tile == 0) : (T)(*L.mu);
+    // the cell of parity b of the pair in the taker's row q; live: it has an open face
+    auto update = [&](int q, int b, T &own, bool &live) -> T {
+        const T *p = &s[0][zu[q] * HY + yu[q]][l];
+        const T *c = p + (b ? ROWS * P + 1 : 0), *o = p + (b ? 0 : ROWS * P + 1);
+        own = o[0];
+        const T side = o[b ? 1 : -1];
+        const int j = min(max(y0 + yu[q], 0), ny - 1), k = min(max(z0 + zu[q], 0), nz - 1);
+        const T vol = ((b ? wx[1] : wx[0]) * L.w[1][j]) * L.w[2][k];
+        T d, n;
+        if (q < NI) {
+            n = rbc_update<T>(b ? tx[q].y : tx[q].x, b ? txh[q] : tx[q].y, b ? ty[q].y : ty[q].x,
+                              b ? tyh[q].y : tyh[q].x, b ? tz[q].y : tz[q].x, b ? tzh[q].y : tzh[q].x,
+                              b ? own : side, b ? side : own, c[-P], c[P], c[-P * HY], c[P * HY],
+                              b ? r[q].y : r[q].x, vol, mu, d);
+        } else {
+            const T(&h)[7] = g[q - NI];
+            n = rbc_update<T>(h[0], h[1], h[2], h[3], h[4], h[5], b ? own : side, b ? side : own, c[-P], c[P],
+                              c[-P * HY], c[P * HY], h[6], vol, mu, d);
+        }
+        live = row[q] && (b ? in1 : in0) && d > T(0);
+        return n;
+    };
+    T own;
+    bool live;
+#pragma unroll
+    for (int q = 0; q < NU; ++q) {
+        const int b = (y0 + yu[q] + z0 + zu[q]) & 1;  // x0 is even
+        const T n = update(q, b, own, live);
+        if (live) s[b][zu[q] * HY + yu[q]][l + b] = n;
+    }
+    __syncthreads();
+    const bool mine = 2 * l >= xoff && 2 * l < xoff + bx && in0;
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+        const int b = (y0 + yu[q] + z0 + zu[q] + 1) & 1;
+        const T n = update(q, b, own, live);
+        const T x = live ? n : s[b][zu[q] * HY + yu[q]][l + b];
+        T *o = eout + cell(yu[q], zu[q]) + i;
+        const U pr = U{b ? own : x, b ? x : own};
+        if (mine && row[q] && in1) *reinterpret_cast<U *>(o) = pr;
+        else if (mine && row[q]) *o = pr.x;
+    }
 }
 
 template <typename T>
-hipError_t launch_sweepC_fused(const Coarse<T> &L, T *eout, hipStream_t s) {
-    if (!sweepC_fused_ok(L.n)) return hipErrorInvalidValue;
+hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s) {
+    if (L.n[0] < 2) return hipErrorInvalidValue;
+    if ((int64_t)L.n[0] * L.n[1] * L.n[2] < SWC_MIN_CELLS<T>) {
+        constexpr int BY = 4, BZ = 4, NW = 8, COLS = 64;
+        const int ntx = L.n[0] <= COLS ? 1 : (L.n[0] + COLS - 5) / (COLS - 4);  // one tile needs no halo
+        const int xoff = ntx == 1 ? 0 : 2, bx = ntx == 1 ? COLS : (((L.n[0] + ntx - 1) / ntx + 1) & ~1);
+        const int nty = (L.n[1] + BY - 1) / BY, ntiles = ntx * nty * ((L.n[2] + BZ - 1) / BZ);
+        hipLaunchKernelGGL((k_rbgsC_brick<T, BY, BZ, NW>), dim3((ntiles + 7) / 8 * 8), dim3(64 * NW), 0, s, L, eout, ms,
+                           zero ? 1 : 0, ntx, nty, bx, xoff, ntiles);
+        return hipGetLastError();
+    }
     constexpr int BY = SwcRows<T>::BY, QD = SwcRows<T>::QD;
     constexpr int TXC = SWC_NC - 4, TY = BY - 4;
     const int ntx = (L.n[0] + TXC - 1) / TXC, nty = (L.n[1] + TY - 1) / TY;
@@ -361,15 +554,15 @@ hipError_t launch_sweepC_fused(const Coarse<T> &L, T *eout, hipStream_t s) {
     const int ntiles = (int)(per_slab * nchunk);
     const int grid = ((ntiles + 7) / 8) * 8;
     if ((L.n[0] & 1) == 0)
-        hipLaunchKernelGGL((k_rbgsC_fused<T, BY, QD, true>), dim3(grid), dim3(32 * BY), 0, s, L, eout, ntx, nty, kc,
+        hipLaunchKernelGGL((k_rbgsC_fused<T, BY, QD, true>), dim3(grid), dim3(32 * BY), 0, s, L, eout, ms, ntx, nty, kc,
                            ntiles);
     else
-        hipLaunchKernelGGL((k_rbgsC_fused<T, BY, QD, false>), dim3(grid), dim3(32 * BY), 0, s, L, eout, ntx, nty, kc,
+        hipLaunchKernelGGL((k_rbgsC_fused<T, BY, QD, false>), dim3(grid), dim3(32 * BY), 0, s, L, eout, ms, ntx, nty, kc,
                            ntiles);
     return hipGetLastError();
 }
 
-template hipError_t launch_sweepC_fused<double>(const Coarse<double> &, double *, hipStream_t);
-template hipError_t launch_sweepC_fused<float>(const Coarse<float> &, float *, hipStream_t);
+template hipError_t launch_sweepC<double>(const Coarse<double> &, double *, const MuSource &, bool, hipStream_t);
+template hipError_t launch_sweepC<float>(const Coarse<float> &, float *, const MuSource &, bool, hipStream_t);
 
 }  // namespace ibm

@@ -14,8 +14,8 @@
 //   lane busy (cells dealt out linearly left half of them masked).
 // 128^3 with four bodies (levels of 10^3 and below): 47 -> 29 us; a 128^2 grid (levels 64^2 and
 // below): 93 -> 58 us; 384^3: 81 -> 54 us.
-// Per cell the arithmetic is that of k_sweepC (times the reciprocal of the diagonal),
-// k_resrestrictC and k_prolongC.
+// Per cell the arithmetic is that of the level-by-level sweeps (times the reciprocal of the
+// diagonal), restrictions and prolongations.
 #include <hip/hip_runtime.h>
 
 #include "device_util.hpp"

@@ -57,3 +57,37 @@ def test_mixed_cycle_by_bricks(dims):
     b, st = g.poisson_solve(r, precision="mixed", rel_tol=1e-12, max_cycles=60)
     assert st.status == 0
     assert float((a - b).abs().max() / a.abs().max()) <= 1e-8
+
+
+@pytest.mark.parametrize("nu", [(2, 2), (1, 0), (0, 3)])
+@pytest.mark.parametrize("dims", [(130, 34, 34), (128, 64, 64), (122, 70, 66), (260, 36, 36), (40, 60, 60), (256, 250, 1)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_coarse_bricks(dims, nu):
+    """Level 1 (half of dims along every axis) at the edges of the coarse bricks, mu formed by the
+    first sweep or, without pre-smoothing, by its own launch: two BiCGStab steps as the oracle's."""
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    f = [I.uniform_faces(0.0, n / 32.0, n) if n > 1 else np.array([-1.0 / 64, 1.0 / 64]) for n in dims]
+    c = [0.46 * a[-1] for a in f]
+    if dims[2] == 1:
+        v, t = I.prism_mesh(1.1, 64, -1.0, 1.0, center=(c[0], c[1]))
+    else:
+        v, t = I.icosphere(3)
+        v = v * 0.3 * min(a[-1] for a in f) + np.array(c)
+    P = OracleProblem(*f)
+    P.set_mesh(v, t)
+    P.classify()
+    P.build_stencils()
+    rhs = np.random.default_rng(7).uniform(-1.0, 1.0, (dims[2], dims[1], dims[0]))
+    kw = dict(fixed_cycles=2, method="bicgstab", nu1=nu[0], nu2=nu[1])
+    ref, _ = P.solve(rhs, **kw)
+    active = P.types() != 2
+    for precision, tol in (("fp64", 1e-9), ("mixed", 1e-4)):  # mixed: two steps of an FP32 preconditioner
+        g = ibm.Grid(*f, precision=precision)
+        g.setup(v, t)
+        p, _ = g.poisson_solve(torch.from_numpy(rhs).cuda(), precision=precision, **kw)
+        err = np.max(np.abs(p.cpu().numpy() - ref)[active]) / np.max(np.abs(ref[active]))
+        print(dims, nu, precision, g.levels()[1:3], "err", err, flush=True)
+        assert err <= tol
