@@ -3,13 +3,13 @@
 // scheduled relaxed Jacobi, with the no-slip (Dirichlet) ghost rows of Section 2.2.
 //
 // Cell-centred velocity components live in three arrays of the level-0 layout [nz][ny][nx].
-// The two cell passes (right-hand side, relaxed Jacobi sweep) are z-marches over 64 x 4
-// column tiles: a thread owns a column, keeps the centre values of the planes below and
-// above in registers, and issues every load of the next plane before computing the current
-// one; x and y neighbours come from the lanes' common cache lines.
+// The two cell passes (right-hand side, relaxed Jacobi sweep) march in z over tiles of columns
+// (mom_march below).
+#include <algorithm>
+#include <type_traits>
+
 #include "device_util.hpp"
 #include "ibm_impl.hpp"
-#include "zmarch.hpp"
 
 namespace ibm {
 
@@ -127,263 +127,382 @@ __global__ void k_ghost_scatter(int64_t ng, const int32_t *__restrict__ gcell, c
     for (int c = 0; c < 3; ++c) dst.c[c][cell] = scr[3 * g + c];
 }
 
-// one plane of a column for the right-hand side pass: the four lateral neighbours and the
-// centre of the plane above, per component, the previous convective term and the type
-struct RhsPlane {
-    double xm[3], xp[3], ym[3], yp[3], up[3], hold[3];
-    double azm, azp, zpl, zph, zml, zmh, wz;
-    uint8_t ty;
+// March of the two cell passes.  A workgroup of NW waves owns a tile of columns and a chunk of
+// planes; RPW rows of 64 / RPW lanes per wave, two adjacent columns per lane (16-byte accesses),
+// the first and the last row of the tile being halo rows that only supply values.  A thread keeps
+// the pairs of three planes of the three components in registers and loads one plane ahead; the
+// current plane goes through LDS for the x and y neighbours (even and odd columns apart, so that
+// a wave's reads are contiguous; one barrier a plane, double-buffered), so nothing is loaded
+// twice but the halo.  Both passes are bound by HBM (73 and 97 bytes per cell).  With one column per
+// thread and every neighbour loaded (26 and 39 loads a plane, 150 and 208 registers) they took 314 and
+// 540 us at 256^3; this way about 248 and 405 us.
+struct MTiles {
+    int ntx, nty, bx, kc, ntiles, grid;
 };
+
+template <int RPW, int NW>
+struct March {
+    static constexpr int LW = 64 / RPW, ROWS = NW * RPW, BY = ROWS - 2, P = LW + 1;
+    typedef double U2 __attribute__((ext_vector_type(2)));
+    typedef U2 U __attribute__((aligned(8)));  // a pair at element alignment (odd rows)
+    typedef uint16_t Byte2 __attribute__((aligned(1)));
+    struct Shared {
+        double s[2][3][2][ROWS][P];  // buffer, component, even / odd columns (guards: odd 0, even LW)
+    };
+    int nx, ny, nz, l, r, i, j, k0, k1;
+    bool live, in0, in1, mine, shf, edge;
+    uint32_t ic, xe;      // first column of the loaded pair; the column beside the tile (edge lanes)
+    int64_t plane, row;
+
+    __device__ __forceinline__ March(const MTiles &t, int nx_, int ny_, int nz_) : nx(nx_), ny(ny_), nz(nz_) {
+        const int per = gridDim.x >> 3;  // XCD-aware order (see zmarch.hpp)
+        const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+        live = tile < t.ntiles;
+        const int wave = (int)threadIdx.x >> 6;
+        l = (int)threadIdx.x & (LW - 1);
+        r = wave * RPW + (RPW == 1 ? 0 : ((int)threadIdx.x & 63) / LW);
+        i = tile % t.ntx * t.bx + 2 * l;
+        j = tile / t.ntx % t.nty * BY + r - 1;
+        k0 = tile / (t.ntx * t.nty) * t.kc;
+        k1 = min(nz, k0 + t.kc);
+        const bool rowin = j >= 0 && j < ny && r >= 1 && r <= BY && 2 * l < t.bx;
+        in0 = rowin && i < nx;
+        in1 = rowin && i + 1 < nx;
+        mine = in0;
+        shf = i == nx - 1;
+        ic = (uint32_t)min(i, nx - 2);
+        edge = l == 0 || l == LW - 1;
+        xe = (uint32_t)(l == 0 ? max(i - 1, 0) : min(i + 2, nx - 1));
+        plane = (int64_t)nx * ny;
+        row = (int64_t)min(max(j, 0), ny - 1) * nx;
+    }
+    __device__ __forceinline__ int64_t base(int k) const { return (int64_t)min(max(k, 0), nz - 1) * plane + row; }
+    __device__ __forceinline__ U pair(const double *a, int64_t b) const {
+        return *reinterpret_cast<const U *>(a + b + ic);
+    }
+    __device__ __forceinline__ U fix(U v) const {  // an odd row's last column is the second of the loaded pair
+        if (shf) v.x = v.y;
+        return v;
+    }
+    __device__ __forceinline__ void store(double *a, int64_t b, double v0, double v1) const {
+        typedef double W2 __attribute__((ext_vector_type(2)));
+        typedef W2 W __attribute__((aligned(8)));
+        if (in1) __builtin_nontemporal_store(W{v0, v1}, reinterpret_cast<W *>(a + b + i));
+        else __builtin_nontemporal_store(v0, a + b + i);
+    }
+};
+
+// Runs body(k, below, centre, above, f, type, nb) over the chunk; nb(c, b, q): component c of the
+// neighbour of cell b (0, 1) at -x, +x, -y, +y (q).  F: a second field, read at the cell itself
+// (not loaded when its components are null).
+template <int RPW, int NW, typename Body>
+__device__ __forceinline__ void mom_march(const March<RPW, NW> &m, typename March<RPW, NW>::Shared &sh, CV3 X, CV3 F,
+                                          const uint8_t *type, Body body) {
+    using U = typename March<RPW, NW>::U;
+    constexpr int LW = March<RPW, NW>::LW;
+    struct Own {  // what only its own step needs, loaded one plane ahead
+        U f[3];
+        double e[3];
+        uint32_t t;
+    };
+    auto own = [&](int k) {
+        Own d;
+        const int64_t b = m.base(k);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            d.f[c] = U{0.0, 0.0};
+            if (F.c[0] && m.mine) d.f[c] = m.pair(F.c[c], b);
+            d.e[c] = m.edge ? X.c[c][b + m.xe] : 0.0;
+        }
+        d.t = *reinterpret_cast<const typename March<RPW, NW>::Byte2 *>(type + b + m.ic);
+        return d;
+    };
+    U below[3], centre[3], next[3];
+    {
+        const int64_t b0 = m.base(m.k0 - 1), b1 = m.base(m.k0), b2 = m.base(m.k0 + 1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            below[c] = m.fix(m.pair(X.c[c], b0));
+            centre[c] = m.fix(m.pair(X.c[c], b1));
+            next[c] = m.pair(X.c[c], b2);
+        }
+    }
+    Own o = own(m.k0);
+    int buf = 0;
+    for (int k = m.k0; k < m.k1; ++k, buf ^= 1) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            sh.s[buf][c][0][m.r][m.l] = centre[c].x;
+            sh.s[buf][c][1][m.r][m.l + 1] = centre[c].y;
+            if (m.l == 0) sh.s[buf][c][1][m.r][0] = o.e[c];
+            if (m.l == LW - 1) sh.s[buf][c][0][m.r][LW] = o.e[c];
+        }
+        U ahead[3];
+        const int64_t b2 = m.base(k + 2);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ahead[c] = m.pair(X.c[c], b2);
+        const Own on = own(k + 1);
+        __syncthreads();
+        U above[3], f[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            above[c] = m.fix(next[c]);
+            f[c] = m.fix(o.f[c]);
+        }
+        if (m.mine) {
+            auto nb = [&](int c, int b, int q) -> double {
+                const double(&s)[2][March<RPW, NW>::ROWS][March<RPW, NW>::P] = sh.s[buf][c];
+                if (q == 0) return b ? centre[c].x : s[1][m.r][m.l];
+                if (q == 1) return b ? s[0][m.r][m.l + 1] : centre[c].y;
+                return s[b][m.r + (q == 2 ? -1 : 1)][m.l + b];
+            };
+            body(k, below, centre, above, f, m.shf ? o.t >> 8 : o.t, nb);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            below[c] = centre[c];
+            centre[c] = above[c];
+            next[c] = ahead[c];
+        }
+        o = on;
+    }
+}
 
 // Right-hand side of the Crank-Nicolson system on fluid rows and the convective term:
 //   H = -(1/V) sum_faces (+/-) A_f Un_f (u_i)_f      (face values: linear interpolation)
 //   b = u + dt (3/2 H - 1/2 H_old) + a L u,   a = nu dt / 2   (first step: H_old = H)
-// H overwrites H_old in place (each thread reads and writes only its own cells).  Non-fluid
+// H overwrites H_old in place (each thread reads and writes only its own cells; a plane of H_old
+// is read before the plane of H below it is written, and no cell is read twice).  Non-fluid
 // cells get H = b = 0.  partials[block] = sum of b^2 over the block's fluid cells.
-__global__ void __launch_bounds__(ZM_NT)
-    k_mom_rhs(MomView M, CV3 U, V3 H, V3 B, double dt, double a, int first, ZTiles t, double *partials) {
-    __shared__ double sh[ZM_NT / 64];
-    const ZPos z = zpos(t, M.nz);
-    if (!z.live) {
+constexpr int MOM_KC_MAX = 256;
+template <int RPW, int NW>
+__global__ void __launch_bounds__(64 * NW)
+    k_mom_rhs(MomView M, CV3 U, V3 H, V3 B, double dt, double a, int first, MTiles t, double *partials) {
+    __shared__ typename March<RPW, NW>::Shared sh;
+    __shared__ double red[NW], zw[7][MOM_KC_MAX];  // per plane: four face weights, width, two coefficients
+    __shared__ double xw[7][2][March<RPW, NW>::LW];  // the same per column, even and odd ones
+    const March<RPW, NW> m(t, M.nx, M.ny, M.nz);
+    if (!m.live) {
         if (threadIdx.x == 0) partials[blockIdx.x] = 0.0;
         return;
     }
-    const int nx = M.nx, ny = M.ny, nz = M.nz;
-    const bool in = z.i < nx && z.j < ny;
-    const int i = min(z.i, nx - 1), j = min(z.j, ny - 1);
-    const int64_t plane = (int64_t)nx * ny, row = (int64_t)j * nx + i;
-    const bool hx0 = i > 0, hx1 = i < nx - 1, hy0 = j > 0, hy1 = j < ny - 1;
-    const int64_t dxm = hx0 ? -1 : 0, dxp = hx1 ? 1 : 0, dym = hy0 ? -(int64_t)nx : 0, dyp = hy1 ? (int64_t)nx : 0;
-    // interpolation weights (low cell, high cell) of the four lateral faces
-    double xpl = 0, xph = 0, xml = 0, xmh = 0, ypl = 0, yph = 0, yml = 0, ymh = 0;
-    if (hx1) {
-        const double h = M.xc[i + 1] - M.xc[i];
-        xpl = (M.xc[i + 1] - M.xf[i + 1]) / h;
-        xph = (M.xf[i + 1] - M.xc[i]) / h;
+    for (int q = (int)threadIdx.x; q < m.k1 - m.k0; q += 64 * NW) {
+        const int k = m.k0 + q;
+        double w[4] = {0.0, 0.0, 0.0, 0.0};
+        if (k < m.nz - 1) {
+            const double h = M.zc[k + 1] - M.zc[k];
+            w[0] = (M.zc[k + 1] - M.zf[k + 1]) / h;
+            w[1] = (M.zf[k + 1] - M.zc[k]) / h;
+        }
+        if (k > 0) {
+            const double h = M.zc[k] - M.zc[k - 1];
+            w[2] = (M.zc[k] - M.zf[k]) / h;
+            w[3] = (M.zf[k] - M.zc[k - 1]) / h;
+        }
+        for (int v = 0; v < 4; ++v) zw[v][q] = w[v];
+        zw[4][q] = M.wz[k];
+        zw[5][q] = k > 0 ? M.azm[k] : 0.0;
+        zw[6][q] = k < m.nz - 1 ? M.azp[k] : 0.0;
     }
-    if (hx0) {
-        const double h = M.xc[i] - M.xc[i - 1];
-        xml = (M.xc[i] - M.xf[i]) / h;
-        xmh = (M.xf[i] - M.xc[i - 1]) / h;
+    // interpolation weights (low cell, high cell) and flux coefficients; 0 on the walls
+    if (m.r == 0) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int i = min(m.i + b, m.nx - 1);
+            double w[4] = {0.0, 0.0, 0.0, 0.0};
+            if (i < m.nx - 1) {
+                const double h = M.xc[i + 1] - M.xc[i];
+                w[0] = (M.xc[i + 1] - M.xf[i + 1]) / h;
+                w[1] = (M.xf[i + 1] - M.xc[i]) / h;
+            }
+            if (i > 0) {
+                const double h = M.xc[i] - M.xc[i - 1];
+                w[2] = (M.xc[i] - M.xf[i]) / h;
+                w[3] = (M.xf[i] - M.xc[i - 1]) / h;
+            }
+            for (int v = 0; v < 4; ++v) xw[v][b][m.l] = w[v];
+            xw[4][b][m.l] = M.wx[i];
+            xw[5][b][m.l] = i > 0 ? M.axm[i] : 0.0;
+            xw[6][b][m.l] = i < m.nx - 1 ? M.axp[i] : 0.0;
+        }
     }
-    if (hy1) {
+    const int j = min(max(m.j, 0), m.ny - 1);
+    double ypl = 0, yph = 0, yml = 0, ymh = 0, cym = 0, cyp = 0;
+    if (j < m.ny - 1) {
         const double h = M.yc[j + 1] - M.yc[j];
         ypl = (M.yc[j + 1] - M.yf[j + 1]) / h;
         yph = (M.yf[j + 1] - M.yc[j]) / h;
+        cyp = M.ayp[j];
     }
-    if (hy0) {
+    if (j > 0) {
         const double h = M.yc[j] - M.yc[j - 1];
         yml = (M.yc[j] - M.yf[j]) / h;
         ymh = (M.yf[j] - M.yc[j - 1]) / h;
+        cym = M.aym[j];
     }
-    const double wx = M.wx[i], wy = M.wy[j];
-    const double cxm = M.axm[i], cxp = M.axp[i], cym = M.aym[j], cyp = M.ayp[j];
-    auto ld = [&](int k) -> RhsPlane {
-        RhsPlane d;
-        const int kk = min(k, nz - 1);
-        const int64_t base = (int64_t)kk * plane + row;
-        const int64_t up = (kk < nz - 1) ? base + plane : base;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            d.xm[q] = U.c[q][base + dxm];
-            d.xp[q] = U.c[q][base + dxp];
-            d.ym[q] = U.c[q][base + dym];
-            d.yp[q] = U.c[q][base + dyp];
-            d.up[q] = U.c[q][up];
-            d.hold[q] = H.c[q][base];
-        }
-        d.ty = M.type[base];
-        d.azm = M.azm[kk];
-        d.azp = M.azp[kk];
-        d.wz = M.wz[kk];
-        d.zpl = d.zph = d.zml = d.zmh = 0.0;
-        if (kk < nz - 1) {
-            const double h = M.zc[kk + 1] - M.zc[kk];
-            d.zpl = (M.zc[kk + 1] - M.zf[kk + 1]) / h;
-            d.zph = (M.zf[kk + 1] - M.zc[kk]) / h;
-        }
-        if (kk > 0) {
-            const double h = M.zc[kk] - M.zc[kk - 1];
-            d.zml = (M.zc[kk] - M.zf[kk]) / h;
-            d.zmh = (M.zf[kk] - M.zc[kk - 1]) / h;
-        }
-        return d;
-    };
-    double cm[3], cc[3];  // centres of the planes k - 1 and k
-    {
-        const int64_t b0 = (int64_t)z.k0 * plane + row;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            cc[q] = U.c[q][b0];
-            cm[q] = z.k0 > 0 ? U.c[q][b0 - plane] : 0.0;
-        }
-    }
+    const double wy = M.wy[j];
+    CV3 hold;
+    for (int c = 0; c < 3; ++c) hold.c[c] = first ? nullptr : H.c[c];
+    __syncthreads();
     double acc = 0.0;
-    auto compute = [&](const RhsPlane &D, int k) {
-        const int64_t id = (int64_t)k * plane + row;
-        if (in && k < z.k1) {
-            if (D.ty != T_FLUID) {
+    using P = typename March<RPW, NW>::U;
+    mom_march<RPW, NW>(m, sh, U, hold, M.type,
+                       [&](int k, const P(&below)[3], const P(&centre)[3], const P(&above)[3], const P(&hf)[3],
+                           uint32_t ty, auto nb) {
+        const int q = k - m.k0;
+        const double zpl = zw[0][q], zph = zw[1][q], zml = zw[2][q], zmh = zw[3][q], wz = zw[4][q], czm = zw[5][q],
+                     czp = zw[6][q];
+        double hv[3][2], bv[3][2];
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    H.c[q][id] = 0.0;
-                    B.c[q][id] = 0.0;
-                }
-            } else {
-                const bool hz0 = k > 0, hz1 = k < nz - 1;
-                const double ax = D.wz * wy, ay = D.wz * wx, az = wy * wx;
-                const double vol = (D.wz * wy) * wx;
-                const double uxp = hx1 ? xpl * cc[0] + xph * D.xp[0] : 0.0;
-                const double uxm = hx0 ? xml * D.xm[0] + xmh * cc[0] : 0.0;
-                const double vyp = hy1 ? ypl * cc[1] + yph * D.yp[1] : 0.0;
-                const double vym = hy0 ? yml * D.ym[1] + ymh * cc[1] : 0.0;
-                const double wzp = hz1 ? D.zpl * cc[2] + D.zph * D.up[2] : 0.0;
-                const double wzm = hz0 ? D.zml * cm[2] + D.zmh * cc[2] : 0.0;
+        for (int b = 0; b < 2; ++b) {
+            const bool fluid = ((ty >> (8 * b)) & 0xff) == T_FLUID && (b ? m.in1 : true);
+            const double xpl = xw[0][b][m.l], xph = xw[1][b][m.l], xml = xw[2][b][m.l], xmh = xw[3][b][m.l],
+                         wx = xw[4][b][m.l], cxm = xw[5][b][m.l], cxp = xw[6][b][m.l];
+            const double ax = wz * wy, ay = wz * wx, az = wy * wx, vol = (wz * wy) * wx;
+            auto at = [&](const P(&v)[3], int c) { return b ? v[c].y : v[c].x; };
+            const double uxp = xpl * at(centre, 0) + xph * nb(0, b, 1);
+            const double uxm = xml * nb(0, b, 0) + xmh * at(centre, 0);
+            const double vyp = ypl * at(centre, 1) + yph * nb(1, b, 3);
+            const double vym = yml * nb(1, b, 2) + ymh * at(centre, 1);
+            const double wzp = zpl * at(centre, 2) + zph * at(above, 2);
+            const double wzm = zml * at(below, 2) + zmh * at(centre, 2);
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const double fc = cc[q];
-                    const double fxp = D.xp[q], fxm = D.xm[q], fyp = D.yp[q], fym = D.ym[q];
-                    const double fzp = D.up[q], fzm = cm[q];
-                    double h = 0.0;
-                    if (hx1) h -= (uxp * (xpl * fc + xph * fxp)) * ax;
-                    if (hx0) h += (uxm * (xml * fxm + xmh * fc)) * ax;
-                    if (hy1) h -= (vyp * (ypl * fc + yph * fyp)) * ay;
-                    if (hy0) h += (vym * (yml * fym + ymh * fc)) * ay;
-                    if (hz1) h -= (wzp * (D.zpl * fc + D.zph * fzp)) * az;
-                    if (hz0) h += (wzm * (D.zml * fzm + D.zmh * fc)) * az;
-                    h /= vol;
-                    double lap = 0.0;
-                    if (hx1) lap += cxp * (fxp - fc);
-                    if (hx0) lap -= cxm * (fc - fxm);
-                    if (hy1) lap += cyp * (fyp - fc);
-                    if (hy0) lap -= cym * (fc - fym);
-                    if (hz1) lap += D.azp * (fzp - fc);
-                    if (hz0) lap -= D.azm * (fc - fzm);
-                    const double hp = first ? h : D.hold[q];
-                    const double b = fc + dt * (1.5 * h - 0.5 * hp) + a * lap;
-                    __builtin_nontemporal_store(h, H.c[q] + id);  // streaming, as in the sweep
-                    __builtin_nontemporal_store(b, B.c[q] + id);
-                    acc += b * b;
-                }
+            for (int c = 0; c < 3; ++c) {
+                const double fc = at(centre, c), fxm = nb(c, b, 0), fxp = nb(c, b, 1), fym = nb(c, b, 2),
+                             fyp = nb(c, b, 3), fzm = at(below, c), fzp = at(above, c);
+                // a wall's weights and coefficients are 0: its terms vanish
+                double h = 0.0;
+                h -= (uxp * (xpl * fc + xph * fxp)) * ax;
+                h += (uxm * (xml * fxm + xmh * fc)) * ax;
+                h -= (vyp * (ypl * fc + yph * fyp)) * ay;
+                h += (vym * (yml * fym + ymh * fc)) * ay;
+                h -= (wzp * (zpl * fc + zph * fzp)) * az;
+                h += (wzm * (zml * fzm + zmh * fc)) * az;
+                h /= vol;
+                double lap = 0.0;
+                lap += cxp * (fxp - fc);
+                lap -= cxm * (fc - fxm);
+                lap += cyp * (fyp - fc);
+                lap -= cym * (fc - fym);
+                lap += czp * (fzp - fc);
+                lap -= czm * (fc - fzm);
+                const double hp = first ? h : at(hf, c);
+                const double rhs = fc + dt * (1.5 * h - 0.5 * hp) + a * lap;
+                hv[c][b] = fluid ? h : 0.0;
+                bv[c][b] = fluid ? rhs : 0.0;
+                acc += bv[c][b] * bv[c][b];
             }
+            __builtin_amdgcn_sched_barrier(0);  // one cell's values at a time in registers
         }
+        const int64_t o = m.base(k);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            cm[q] = cc[q];
-            cc[q] = D.up[q];
+        for (int c = 0; c < 3; ++c) {
+            m.store(H.c[c], o, hv[c][0], hv[c][1]);
+            m.store(B.c[c], o, bv[c][0], bv[c][1]);
         }
-    };
-    RhsPlane qa = ld(z.k0), qb;
-    for (int k = z.k0; k < z.k1; k += 2) {
-        qb = ld(k + 1);
-        compute(qa, k);
-        qa = ld(k + 2);
-        compute(qb, k + 1);
-    }
-    const double tot = block_sum<ZM_NT>(acc, sh, threadIdx.x);
+    });
+    const double tot = block_sum<64 * NW>(acc, red, threadIdx.x);
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
-
-struct SrjPlane {
-    double xm[3], xp[3], ym[3], yp[3], up[3], b[3];
-    double azm, azp;
-    uint8_t ty;
-};
 
 // One relaxed Jacobi sweep of the fluid rows of (I - a L) u = b:
 //   y = (1 - omega) x + omega (b + a sum_f a_f x_nb) / (1 + a sum_f a_f)
 // ghost cells are copied (their rows follow in their own pass), dead cells cleared.
 // partials[block] = sum of the squared fluid-row residuals b - (I - a L) x at the input.
-__global__ void __launch_bounds__(ZM_NT)
-    k_srj_sweep(MomView M, CV3 X, V3 Y, CV3 B, double a, double omega, ZTiles t, double *partials) {
-    __shared__ double sh[ZM_NT / 64];
-    const ZPos z = zpos(t, M.nz);
-    if (!z.live) {
+template <int RPW, int NW>
+__global__ void __launch_bounds__(64 * NW, 3)
+    k_srj_sweep(MomView M, CV3 X, V3 Y, CV3 B, double a, double omega, MTiles t, double *partials) {
+    __shared__ typename March<RPW, NW>::Shared sh;
+    __shared__ double red[NW], zw[2][MOM_KC_MAX];
+    const March<RPW, NW> m(t, M.nx, M.ny, M.nz);
+    if (!m.live) {
         if (threadIdx.x == 0) partials[blockIdx.x] = 0.0;
         return;
     }
-    const int nx = M.nx, ny = M.ny, nz = M.nz;
-    const bool in = z.i < nx && z.j < ny;
-    const int i = min(z.i, nx - 1), j = min(z.j, ny - 1);
-    const int64_t plane = (int64_t)nx * ny, row = (int64_t)j * nx + i;
-    const bool hx0 = i > 0, hx1 = i < nx - 1, hy0 = j > 0, hy1 = j < ny - 1;
-    const int64_t dxm = hx0 ? -1 : 0, dxp = hx1 ? 1 : 0, dym = hy0 ? -(int64_t)nx : 0, dyp = hy1 ? (int64_t)nx : 0;
-    const double cxp = hx1 ? M.axp[i] : 0.0, cxm = hx0 ? M.axm[i] : 0.0;
-    const double cyp = hy1 ? M.ayp[j] : 0.0, cym = hy0 ? M.aym[j] : 0.0;
-    auto ld = [&](int k) -> SrjPlane {
-        SrjPlane d;
-        const int kk = min(k, nz - 1);
-        const int64_t base = (int64_t)kk * plane + row;
-        const int64_t up = (kk < nz - 1) ? base + plane : base;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            d.xm[q] = X.c[q][base + dxm];
-            d.xp[q] = X.c[q][base + dxp];
-            d.ym[q] = X.c[q][base + dym];
-            d.yp[q] = X.c[q][base + dyp];
-            d.up[q] = X.c[q][up];
-            d.b[q] = B.c[q][base];
-        }
-        d.ty = M.type[base];
-        d.azm = M.azm[kk];
-        d.azp = M.azp[kk];
-        return d;
-    };
-    double cm[3], cc[3];
-    {
-        const int64_t b0 = (int64_t)z.k0 * plane + row;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            cc[q] = X.c[q][b0];
-            cm[q] = z.k0 > 0 ? X.c[q][b0 - plane] : 0.0;
-        }
+    for (int q = (int)threadIdx.x; q < m.k1 - m.k0; q += 64 * NW) {
+        const int k = m.k0 + q;
+        zw[0][q] = k > 0 ? M.azm[k] : 0.0;
+        zw[1][q] = k < m.nz - 1 ? M.azp[k] : 0.0;
     }
+    double cxm[2], cxp[2];  // 0 on the walls
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int i = min(m.i + b, m.nx - 1);
+        cxm[b] = i > 0 ? M.axm[i] : 0.0;
+        cxp[b] = i < m.nx - 1 ? M.axp[i] : 0.0;
+    }
+    const int j = min(max(m.j, 0), m.ny - 1);
+    const double cym = j > 0 ? M.aym[j] : 0.0, cyp = j < m.ny - 1 ? M.ayp[j] : 0.0;
+    __syncthreads();
     double acc = 0.0;
-    auto compute = [&](const SrjPlane &D, int k) {
-        const int64_t id = (int64_t)k * plane + row;
-        if (in && k < z.k1) {
-            if (D.ty != T_FLUID) {
-                const bool dead = D.ty == T_DEAD;
+    using P = typename March<RPW, NW>::U;
+    mom_march<RPW, NW>(m, sh, X, B, M.type,
+                       [&](int k, const P(&below)[3], const P(&centre)[3], const P(&above)[3], const P(&rhs)[3],
+                           uint32_t ty, auto nb) {
+        const double czm = zw[0][k - m.k0], czp = zw[1][k - m.k0];
+        const int64_t o = m.base(k);
+        const uint32_t tc[2] = {ty & 0xff, (ty >> 8) & 0xff};
+        const bool fluid[2] = {tc[0] == T_FLUID, tc[1] == T_FLUID && m.in1};
+        double den[2];
 #pragma unroll
-                for (int q = 0; q < 3; ++q) Y.c[q][id] = dead ? 0.0 : cc[q];
-            } else {
-                const bool hz0 = k > 0, hz1 = k < nz - 1;
-                const double czp = hz1 ? D.azp : 0.0, czm = hz0 ? D.azm : 0.0;
-                const double d = ((czm + czp) + (cym + cyp)) + (cxm + cxp);
-                const double den = 1.0 + a * d;
+        for (int b = 0; b < 2; ++b) {
+            const double d = ((czm + czp) + (cym + cyp)) + (cxm[b] + cxp[b]);
+            den[b] = 1.0 + a * d;
+        }
 #pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    double s = 0.0;
-                    if (hx1) s += cxp * D.xp[q];
-                    if (hx0) s += cxm * D.xm[q];
-                    if (hy1) s += cyp * D.yp[q];
-                    if (hy0) s += cym * D.ym[q];
-                    if (hz1) s += czp * D.up[q];
-                    if (hz0) s += czm * cm[q];
-                    const double xc = cc[q];
-                    const double num = D.b[q] + a * s;
-                    const double r = num - den * xc;
-                    // full-field result, not re-read by this pass: non-temporal (measured faster)
-                    __builtin_nontemporal_store((1.0 - omega) * xc + omega * (num / den), Y.c[q] + id);
-                    acc += r * r;
-                }
+        for (int c = 0; c < 3; ++c) {
+            double y[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                auto at = [&](const P(&v)[3]) { return b ? v[c].y : v[c].x; };
+                double s = 0.0;
+                s += cxp[b] * nb(c, b, 1);
+                s += cxm[b] * nb(c, b, 0);
+                s += cyp * nb(c, b, 3);
+                s += cym * nb(c, b, 2);
+                s += czp * at(above);
+                s += czm * at(below);
+                const double xc = at(centre), num = at(rhs) + a * s, r = num - den[b] * xc;
+                y[b] = fluid[b] ? (1.0 - omega) * xc + omega * (num / den[b]) : tc[b] == T_DEAD ? 0.0 : xc;
+                acc += fluid[b] ? r * r : 0.0;
             }
+            m.store(Y.c[c], o, y[0], y[1]);
+            __builtin_amdgcn_sched_barrier(0);  // one component's values at a time in registers
         }
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            cm[q] = cc[q];
-            cc[q] = D.up[q];
-        }
-    };
-    SrjPlane qa = ld(z.k0), qb;
-    for (int k = z.k0; k < z.k1; k += 2) {
-        qb = ld(k + 1);
-        compute(qa, k);
-        qa = ld(k + 2);
-        compute(qb, k + 1);
-    }
-    const double tot = block_sum<ZM_NT>(acc, sh, threadIdx.x);
+    });
+    const double tot = block_sum<64 * NW>(acc, red, threadIdx.x);
     if (threadIdx.x == 0) partials[blockIdx.x] = tot;
 }
+
+// Workgroups: the sweep four waves with three workgroups per compute unit (156 registers; eight
+// waves at 128 registers spill: 460 us at 256^3), the right-hand side eight waves, one workgroup
+// (251 registers; two of four waves 455, any bound on the registers 1800 us and more).
+// Tiles of cols columns and by rows, `per_cu` workgroups per compute unit at once; a chunk of kc
+// planes costs about kc + 3 plane steps, and the chunk count minimises rounds x (kc + 3).
+MTiles mom_tiles(int nx, int ny, int nz, int cols, int by, int per_cu) {
+    MTiles t;
+    t.ntx = (nx + cols - 1) / cols;
+    t.bx = ((nx + t.ntx - 1) / t.ntx + 1) & ~1;
+    t.nty = (ny + by - 1) / by;
+    const int64_t per_slab = (int64_t)t.ntx * t.nty, slots = (int64_t)per_cu * device_cu_count();
+    int64_t best = -1;
+    t.kc = std::min(nz, MOM_KC_MAX);
+    for (int c = 1; c <= nz; ++c) {
+        const int kc = (nz + c - 1) / c;
+        if (kc > MOM_KC_MAX) continue;
+        const int64_t cost = (per_slab * c + slots - 1) / slots * (kc + 3);
+        if (best < 0 || cost < best) {
+            best = cost;
+            t.kc = kc;
+        }
+    }
+    t.ntiles = (int)(per_slab * ((nz + t.kc - 1) / t.kc));
+    t.grid = (t.ntiles + 7) / 8 * 8;
+    return t;
+}
+
+// rows of 128 columns, or of 64 where those waste fewer lanes
+bool mom_wide(int nx) { return (nx + 127) / 128 * 128 <= (nx + 63) / 64 * 64; }
 
 __global__ void k_mom_sum(const double *partials, int n, double *out) {
     __shared__ double sh[4];
@@ -502,9 +621,14 @@ hipError_t momentum_enqueue_prep(ibm_grid *g, double *const uvw[3], double *cons
     const CV3 U = cv3(uvw[0], uvw[1], uvw[2]);
     hipError_t e = refresh(g, U, v3(uvw[0], uvw[1], uvw[2]), s, g->g_uscr);
     if (e != hipSuccess) return e;
-    const ZTiles t = ztiles(g->nx, g->ny, g->nz);
-    hipLaunchKernelGGL(k_mom_rhs, dim3(t.grid), dim3(ZM_NT), 0, s, mom_view(g), U, v3(hc[0], hc[1], hc[2]),
-                       v3(work[0], work[1], work[2]), dt, a, first, t, g->partials);
+    auto launch = [&](auto rpw) {
+        constexpr int RPW = decltype(rpw)::value, NW = 8;
+        const MTiles t = mom_tiles(g->nx, g->ny, g->nz, 128 / RPW, NW * RPW - 2, 1);
+        hipLaunchKernelGGL((k_mom_rhs<RPW, NW>), dim3(t.grid), dim3(64 * NW), 0, s, mom_view(g), U,
+                           v3(hc[0], hc[1], hc[2]), v3(work[0], work[1], work[2]), dt, a, first, t, g->partials);
+        return t;
+    };
+    const MTiles t = mom_wide(g->nx) ? launch(std::integral_constant<int, 1>()) : launch(std::integral_constant<int, 2>());
     hipLaunchKernelGGL(k_mom_sum, dim3(1), dim3(256), 0, s, g->partials, t.grid, &g->sc->mom_b2);
     return hipGetLastError();
 }
@@ -515,9 +639,14 @@ hipError_t momentum_enqueue_sweep(ibm_grid *g, double *const X[3], double *const
                                   double a, double omega, bool sum, hipStream_t s) {
     const CV3 x = cv3(X[0], X[1], X[2]);
     const V3 y = v3(Y[0], Y[1], Y[2]);
-    const ZTiles t = ztiles(g->nx, g->ny, g->nz);
-    hipLaunchKernelGGL(k_srj_sweep, dim3(t.grid), dim3(ZM_NT), 0, s, mom_view(g), x, y, cv3(work[0], work[1], work[2]),
-                       a, omega, t, g->partials);
+    auto launch = [&](auto rpw) {
+        constexpr int RPW = decltype(rpw)::value, NW = 4;
+        const MTiles t = mom_tiles(g->nx, g->ny, g->nz, 128 / RPW, NW * RPW - 2, 3);
+        hipLaunchKernelGGL((k_srj_sweep<RPW, NW>), dim3(t.grid), dim3(64 * NW), 0, s, mom_view(g), x, y,
+                           cv3(work[0], work[1], work[2]), a, omega, t, g->partials);
+        return t;
+    };
+    const MTiles t = mom_wide(g->nx) ? launch(std::integral_constant<int, 1>()) : launch(std::integral_constant<int, 2>());
     if (sum) hipLaunchKernelGGL(k_mom_sum, dim3(1), dim3(256), 0, s, g->partials, t.grid, &g->sc->mom_r2);
     return refresh(g, x, y, s);
 }
