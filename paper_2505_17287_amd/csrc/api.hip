@@ -294,10 +294,10 @@ size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int6
     G->tail.meta = P.take<uint2>(TAIL_E);
     G->tail.down = P.take<uint32_t>(TAIL_E);
     // the largest of: reductions over RED_BLOCKS workgroups (up to 4 sums), the coarsening
-    // sums, and one Krylov operator pass (2 sums per z-march workgroup, then 2 per ghost block)
+    // sums, and one Krylov operator pass (2 sums per z-march workgroup, 3 per ghost-row block)
     G->partials = P.take<double>(std::max<int64_t>(
         std::max<int64_t>(4 * RED_BLOCKS, N / 256 + 1024),
-        2 * zmarch_partials_max(nx, ny, nz) + 2 * (std::max<int64_t>(gmax, 1) / 256 + 2)));
+        2 * zmarch_partials_max(nx, ny, nz) + 3 * GHOST_ROW_BLOCKS));
     G->sc = P.take<Scalars>(1);
     return P.off + 256;
 }

@@ -49,6 +49,35 @@ __device__ __forceinline__ double block_sum(double v, double *sh, int tid) {
     __syncthreads();
     return r;
 }
+// The same for NS sums at once, one pair of barriers for all of them (a reduction kernel whose
+// block handles a few cells per thread is mostly these); v[q] becomes the sum in thread q.
+template <int NT, int NS>
+__device__ __forceinline__ void block_sums(double (&v)[NS], double (*sh)[NS], int tid) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q) v[q] = wave_sum(v[q]);
+    if ((tid & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) sh[tid >> 6][q] = v[q];
+    }
+    __syncthreads();
+    if (tid < NS) {
+        double r = 0.0;
+        for (int w = 0; w < NT / 64; ++w) r += sh[w][tid];
+#pragma unroll
+        for (int q = 0; q < NS; ++q)
+            if (tid == q) v[q] = r;
+    }
+    __syncthreads();
+}
+// NS sums of a block stored at partials[NS block + q]
+template <int NT, int NS>
+__device__ __forceinline__ void block_sums_store(double (&v)[NS], double *partials) {
+    __shared__ double sh[NT / 64][NS];
+    block_sums<NT, NS>(v, sh, threadIdx.x);
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+        if ((int)threadIdx.x == q) partials[(int64_t)NS * blockIdx.x + q] = v[q];
+}
 template <int NT>
 __device__ __forceinline__ double block_max(double v, double *sh, int tid) {
     v = wave_max(v);
@@ -61,6 +90,9 @@ __device__ __forceinline__ double block_max(double v, double *sh, int tid) {
     __syncthreads();
     return r;
 }
+
+// two adjacent doubles moved as one access, aligned as one double
+typedef double DPair __attribute__((ext_vector_type(2), aligned(8)));
 
 // two adjacent elements moved as one access (8- or 16-byte aligned pairs)
 template <typename T>

@@ -62,26 +62,29 @@ __device__ __forceinline__ void zm_block_sum_store(double v, double *partials) {
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-// NS sums per workgroup, stored at partials[NS * block + q]
-template <int NT, int NS>
-__device__ __forceinline__ void zm_block_sums_store(const double (&v)[NS], double *partials) {
-    __shared__ double sh[NT / 64];
-#pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        const double s = block_sum<NT>(v[q], sh, threadIdx.x);
-        if (threadIdx.x == 0) partials[NS * blockIdx.x + q] = s;
-    }
-}
-
-// Sums of the Krylov operator passes.  DOTS 0: w = S y, sum V w.  DOTS 1 and 2: w = S y - mu
+// Sums of the Krylov operator passes.  DOTS 1 and 2: w = S y - mu
 // (the image with its volume-weighted fluid mean, known beforehand, removed), sum o w and
 // sum w w (o is the vector the image is dotted with: the shadow residual or s; w w gives
 // omega, and the near-breakdown test of alpha).  DOTS 3: the residual w = o - S y (o the
 // right-hand side), sum V w.
 template <int DOTS>
 struct ApplySums {
-    static constexpr int NS = (DOTS == 1 || DOTS == 2) ? 2 : 1;
+    static constexpr int NS = DOTS == 3 ? 1 : 2;
 };
+
+// mu, by every workgroup for itself from the ghost-row blocks' sums (at most GHOST_ROW_BLOCKS,
+// in L2): a launch of one workgroup in between cost 5.4 us at 128^3, this 2.  Each workgroup
+// adds them in the same order, so all have the same mu.
+template <int NT>
+__device__ __forceinline__ double mean_of(const MeanParts &m) {
+    __shared__ double sh[NT / 64], mean;
+    double a = 0.0;
+    for (int q = threadIdx.x; q < m.n; q += NT) a += m.part[q];
+    a = block_sum<NT>(a, sh, threadIdx.x);
+    if (threadIdx.x == 0) mean = a / *m.vol;
+    __syncthreads();
+    return mean;
+}
 
 // ---- residual + restriction --------------------------------------------------------------
 // R_1(C) = sum over fluid children c of V_c r_c with r = (f - lambda) - S p; e_1 = 0;
@@ -634,17 +637,16 @@ __global__ void __launch_bounds__(ZM_NT)
 // The FP64 level-0 results of the prolongation and operator passes are written with
 // non-temporal stores (store_stream): the writing pass does not read them again, and keeping
 // these full fields from displacing cached data measured faster over a whole projection.
-// w = S y on fluid rows, 0 elsewhere, with the sums of ApplySums<DOTS> over the block (the
-// fluid rows' contributions; w is 0 elsewhere).  The loads of plane k+1 are issued before
+// w = S y on fluid rows, 0 on dead cells, with the sums of ApplySums<DOTS> over the fluid rows of
+// the block; ghost cells hold their rows already (k_ghost_rows) and are not written.  The loads of plane k+1 are issued before
 // plane k is computed.  Off the fluid rows o is not read into a sum at all (selected out, not
 // multiplied by the zero image): the shadow residual is never written on dead cells, so its
 // values there are whatever the workspace held, possibly NaN or Inf.
 template <int DOTS>
 __global__ void __launch_bounds__(ZM_NT)
     k_apply_fluid_zm(Fine<double> F, const double *__restrict__ y, double *__restrict__ w,
-                     const double *__restrict__ o, const double *__restrict__ mup, ZTiles t, double *partials) {
+                     const double *__restrict__ o, MeanParts mp, ZTiles t, double *partials) {
     constexpr int NS = ApplySums<DOTS>::NS;
-    const double mu = (DOTS == 1 || DOTS == 2) ? *mup : 0.0;
     const ZPos z = zpos(t, F.nz);
     if (!z.live) {
         if (threadIdx.x == 0)
@@ -672,7 +674,7 @@ __global__ void __launch_bounds__(ZM_NT)
         d.azm = F.azm[kk];
         d.azp = F.azp[kk];
         d.wz = F.wz[kk];
-        d.fv = DOTS ? o[base] : 0.0;
+        d.fv = o[base];
         return d;
     };
     double ym1 = (z.k0 > 0) ? y[(int64_t)(z.k0 - 1) * plane + rowoff] : 0.0;
@@ -687,19 +689,18 @@ __global__ void __launch_bounds__(ZM_NT)
         zm_stencil<double>(axm, axp, aym, ayp, (D).azm, (D).azp, hx0, hx1, hy0, hy1, k_ > 0, k_ < nz - 1, (D).xm,  \
                            (D).xp, (D).ym, (D).yp, ym1, (D).pp, num, diag);                                        \
         const bool fl = in && (D).ty == T_FLUID;                                                                   \
-        const double a = fl ? (DOTS == 3 ? (D).fv - (num - diag * yc)                                              \
-                                         : (DOTS ? (num - diag * yc) - mu : num - diag * yc))                      \
-                            : 0.0;                                                                                 \
+        const double a = fl ? (DOTS == 3 ? (D).fv - (num - diag * yc) : (num - diag * yc) - mu) : 0.0;            \
         if (in && k_ < z.k1) {                                                                                     \
-            __builtin_nontemporal_store(a, w + (int64_t)k_ * plane + rowoff);                                      \
-            if (DOTS == 0 || DOTS == 3) acc[0] += (vxy * (D).wz) * a;                                              \
-            if (DOTS == 1 || DOTS == 2) acc[0] += fl ? (D).fv * a : 0.0;                                           \
-            if (DOTS == 1 || DOTS == 2) acc[1 % NS] += a * a;                                                      \
+            if ((D).ty != T_GHOST) __builtin_nontemporal_store(a, w + (int64_t)k_ * plane + rowoff);               \
+            if (DOTS == 3) acc[0] += (vxy * (D).wz) * a;                                                           \
+            if (DOTS != 3) acc[0] += fl ? (D).fv * a : 0.0;                                                        \
+            if (DOTS != 3) acc[1 % NS] += a * a;                                                                   \
         }                                                                                                          \
         ym1 = yc;                                                                                                  \
         yc = (D).pp;                                                                                               \
     }
     RPlane<double> qa = ld(z.k0), qb;
+    const double mu = DOTS == 3 ? 0.0 : mean_of<ZM_NT>(mp);
     for (int k = z.k0; k < z.k1; k += 2) {
         qb = ld(k + 1);
         IBM_APPLY_PLANE(qa, k);
@@ -707,7 +708,7 @@ __global__ void __launch_bounds__(ZM_NT)
         IBM_APPLY_PLANE(qb, k + 1);
     }
 #undef IBM_APPLY_PLANE
-    zm_block_sums_store<ZM_NT, NS>(acc, partials);
+    block_sums_store<ZM_NT, NS>(acc, partials);
 }
 
 // ---- relaxed Jacobi sweep (the scheduled-Jacobi preconditioner) -------------------------
@@ -973,11 +974,10 @@ __global__ void __launch_bounds__(ZP_NT)
 template <int DOTS>
 __global__ void __launch_bounds__(ZP_NT)
     k_apply_fluid_zm2(Fine<double> F, const double *__restrict__ y, double *__restrict__ w,
-                      const double *__restrict__ o, const double *__restrict__ mup, ZTiles t, double *partials) {
+                      const double *__restrict__ o, MeanParts mp, ZTiles t, double *partials) {
     using V = double2;
     typedef double NV __attribute__((ext_vector_type(2)));  // native pair for the streaming store
     constexpr int NS = ApplySums<DOTS>::NS;
-    const double mu = (DOTS == 1 || DOTS == 2) ? *mup : 0.0;
     const ZPos2 z = zpos2(t, F.nz);
     if (!z.live) {
         if (threadIdx.x == 0)
@@ -1006,7 +1006,7 @@ __global__ void __launch_bounds__(ZP_NT)
         d.azm = F.azm[kk];
         d.azp = F.azp[kk];
         d.wz = F.wz[kk];
-        d.fv = DOTS ? *reinterpret_cast<const V *>(o + base) : V{0.0, 0.0};
+        d.fv = *reinterpret_cast<const V *>(o + base);
         return d;
     };
     V ym1 = (z.k0 > 0) ? *reinterpret_cast<const V *>(y + (int64_t)(z.k0 - 1) * plane + rowoff) : V{0.0, 0.0};
@@ -1024,26 +1024,24 @@ __global__ void __launch_bounds__(ZP_NT)
         zm_stencil<double>(axm1, axp1, aym, ayp, (D).azm, (D).azp, true, hx1, hy0, hy1, z0_, z1_, yc.x, (D).xp,   \
                            (D).ym.y, (D).yp.y, ym1.y, (D).pp.y, n1, d1);                                           \
         const bool f0_ = in && ((D).tt & 0xff) == T_FLUID, f1_ = in && ((D).tt >> 8) == T_FLUID;                  \
-        const double a0 = f0_                                                                                      \
-                              ? (DOTS == 3 ? (D).fv.x - (n0 - d0 * yc.x)                                           \
-                                           : (DOTS ? (n0 - d0 * yc.x) - mu : n0 - d0 * yc.x))                      \
-                              : 0.0;                                                                               \
-        const double a1 = f1_                                                                                      \
-                              ? (DOTS == 3 ? (D).fv.y - (n1 - d1 * yc.y)                                           \
-                                           : (DOTS ? (n1 - d1 * yc.y) - mu : n1 - d1 * yc.y))                      \
-                              : 0.0;                                                                               \
+        const double a0 = f0_ ? (DOTS == 3 ? (D).fv.x - (n0 - d0 * yc.x) : (n0 - d0 * yc.x) - mu) : 0.0;          \
+        const double a1 = f1_ ? (DOTS == 3 ? (D).fv.y - (n1 - d1 * yc.y) : (n1 - d1 * yc.y) - mu) : 0.0;          \
         if (in && k_ < z.k1) {                                                                                     \
-            const NV o_ = {a0, a1};                                                                                \
-            __builtin_nontemporal_store(o_, reinterpret_cast<NV *>(w + (int64_t)k_ * plane + rowoff));             \
-            if (DOTS == 0 || DOTS == 3) {                                                                          \
+            double *w_ = w + (int64_t)k_ * plane + rowoff;                                                         \
+            const bool g0_ = ((D).tt & 0xff) == T_GHOST, g1_ = ((D).tt >> 8) == T_GHOST;                          \
+            if (!g0_ && !g1_) {                                                                                    \
+                const NV o_ = {a0, a1};                                                                            \
+                __builtin_nontemporal_store(o_, reinterpret_cast<NV *>(w_));                                       \
+            } else {                                                                                               \
+                if (!g0_) w_[0] = a0;                                                                              \
+                if (!g1_) w_[1] = a1;                                                                              \
+            }                                                                                                      \
+            if (DOTS == 3) {                                                                                       \
                 acc[0] += (vxy0 * (D).wz) * a0;                                                                    \
                 acc[0] += (vxy1 * (D).wz) * a1;                                                                    \
-            }                                                                                                      \
-            if (DOTS == 1 || DOTS == 2) {                                                                          \
+            } else {                                                                                               \
                 acc[0] += f0_ ? (D).fv.x * a0 : 0.0;                                                               \
                 acc[0] += f1_ ? (D).fv.y * a1 : 0.0;                                                               \
-            }                                                                                                      \
-            if (DOTS == 1 || DOTS == 2) {                                                                          \
                 acc[1 % NS] += a0 * a0;                                                                            \
                 acc[1 % NS] += a1 * a1;                                                                            \
             }                                                                                                      \
@@ -1052,6 +1050,7 @@ __global__ void __launch_bounds__(ZP_NT)
         yc = (D).pp;                                                                                               \
     }
     RPlane2<double> qa = ld(z.k0), qb;
+    const double mu = DOTS == 3 ? 0.0 : mean_of<ZP_NT>(mp);
     for (int k = z.k0; k < z.k1; k += 2) {
         qb = ld(k + 1);
         IBM_APPLY_PLANE2(qa, k);
@@ -1059,7 +1058,7 @@ __global__ void __launch_bounds__(ZP_NT)
         IBM_APPLY_PLANE2(qb, k + 1);
     }
 #undef IBM_APPLY_PLANE2
-    zm_block_sums_store<ZP_NT, NS>(acc, partials);
+    block_sums_store<ZP_NT, NS>(acc, partials);
 }
 
 }  // namespace
@@ -1105,7 +1104,7 @@ hipError_t launch_prolong0(const Fine<T> &F, const T *pcur, T *pnext, const Coar
 
 template <int DOTS>
 static hipError_t apply_fluid_dots(const Fine<double> &F, const double *y, double *w, const double *o,
-                                   const double *mu, double *partials, int *nparts, hipStream_t s) {
+                                   const MeanParts &mu, double *partials, int *nparts, hipStream_t s) {
     if ((F.nx & 1) == 0 && F.nx >= 2) {
         const ZTiles t = ztiles2(F.nx, F.ny, F.nz);
         hipLaunchKernelGGL(k_apply_fluid_zm2<DOTS>, dim3(t.grid), dim3(ZP_NT), 0, s, F, y, w, o, mu, t, partials);
@@ -1118,12 +1117,11 @@ static hipError_t apply_fluid_dots(const Fine<double> &F, const double *y, doubl
     return hipGetLastError();
 }
 
-hipError_t launch_apply_fluid(const Fine<double> &F, const double *y, double *w, const double *o, const double *mu,
+hipError_t launch_apply_fluid(const Fine<double> &F, const double *y, double *w, const double *o, const MeanParts &mu,
                               int dots, double *partials, int *nparts, hipStream_t s) {
     if (dots == 1) return apply_fluid_dots<1>(F, y, w, o, mu, partials, nparts, s);
     if (dots == 2) return apply_fluid_dots<2>(F, y, w, o, mu, partials, nparts, s);
-    if (dots == 3) return apply_fluid_dots<3>(F, y, w, o, mu, partials, nparts, s);
-    return apply_fluid_dots<0>(F, y, w, o, mu, partials, nparts, s);
+    return apply_fluid_dots<3>(F, y, w, o, mu, partials, nparts, s);
 }
 
 hipError_t launch_jacobi0(const Fine<double> &F, const double *y, const double *f, double *out, double omega,

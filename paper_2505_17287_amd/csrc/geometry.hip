@@ -1516,9 +1516,9 @@ __global__ void k_prolong_tab(int nf, int nc, const int *__restrict__ cs, const 
 
 hipError_t launch_hierarchy(ibm_grid *g, hipStream_t s) {
     // level-0 fluid volume
-    hipLaunchKernelGGL(k_fluid_volume, dim3(RED_BLOCKS), dim3(256), 0, s, g->type, g->nx, g->ny, g->nz, g->w0[0],
+    hipLaunchKernelGGL(k_fluid_volume, dim3(red_blocks(g->N)), dim3(256), 0, s, g->type, g->nx, g->ny, g->nz, g->w0[0],
                        g->w0[1], g->w0[2], g->partials);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, &g->sc->vol[0]);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, g->partials, red_blocks(g->N), &g->sc->vol[0]);
     for (int l = 1; l < g->nlev; ++l) {
         LevelHost &Fh = g->lev[l - 1], &Ch = g->lev[l];
         LevelDims F, C;

@@ -27,7 +27,16 @@ namespace ibm {
 constexpr uint8_t T_FLUID = 0, T_GHOST = 1, T_DEAD = 2;
 constexpr int GF_DEGENERATE = 1, GF_CLAMPED = 2, GF_NFALLBACK = 4, GF_SELF = 8;
 constexpr int MAX_LEVELS = 24;
-constexpr int RED_BLOCKS = 4096;  // fixed block count of the deterministic reductions (enough waves to fill every SIMD)
+// Block count of the deterministic reductions: a function of the item count alone, at most
+// RED_BLOCKS (enough waves to fill every SIMD); a 128^2 grid with 4096 blocks, most of them
+// empty, took 9.2 us for the step's last update and 5.7 us to add up the partials.
+constexpr int RED_BLOCKS = 4096;
+inline int red_blocks(int64_t items, int per_block = 256) {
+    const int64_t n = (items + per_block - 1) / per_block;
+    return (int)(n < 1 ? 1 : n < RED_BLOCKS ? n : RED_BLOCKS);
+}
+// block limit of the ghost-row pass, whose partials every block of the operator pass adds up
+constexpr int GHOST_ROW_BLOCKS = 1024;
 constexpr int NBUCKET_MAX = 1 << 21;
 
 // ---------------------------------------------------------------------------------------
@@ -110,11 +119,16 @@ hipError_t launch_restrict0(const Fine<T> &F, const T *p, const T *f, const T *l
 template <typename T>
 hipError_t launch_prolong0(const Fine<T> &F, const T *pcur, T *pnext, const Coarse<T> &C, const ProlongTab &P,
                            hipStream_t s);
-// Krylov operator on fluid rows.  dots 0: w = S y, one sum per workgroup (sum V w).  dots 1
-// and 2: w = S y - *mu (device scalar: the image's volume-weighted fluid mean), sums of o w and
-// (dots 2) of w w per workgroup, stored with a stride of 1 or 2.  dots 3: the residual
+// Krylov operator on fluid rows; w is 0 on dead cells and not written on ghost cells.  dots 1
+// and 2: w = S y - mu, sums of o w and of w w per workgroup (stride 2).  dots 3: the residual
 // w = o - S y (o the right-hand side; mu unused), sum V w per workgroup.
-hipError_t launch_apply_fluid(const Fine<double> &F, const double *y, double *w, const double *o, const double *mu,
+// mu, the image's volume-weighted fluid mean: the sum of n partials over the fluid volume
+struct MeanParts {
+    const double *part;
+    int n;
+    const double *vol;
+};
+hipError_t launch_apply_fluid(const Fine<double> &F, const double *y, double *w, const double *o, const MeanParts &mu,
                               int dots, double *partials, int *nparts, hipStream_t s);
 hipError_t launch_jacobi0(const Fine<double> &F, const double *y, const double *f, double *out, double omega,
                           hipStream_t s);
@@ -157,7 +171,7 @@ struct Scalars {
     int pad1;
     // Krylov (BiCGStab) scalars
     double rho, rho_old, alpha, omega, beta;
-    double mu_v;        // volume-weighted fluid mean removed from an operator image
+    double mu_v;        // volume-weighted fluid mean removed from a residual
     double zero;        // constant 0 (shift of the preconditioner's right-hand side)
     float zero32, pad2;
     double rh2;         // squared norm of the shadow residual (set when it is (re)started)

@@ -27,6 +27,28 @@ namespace ibm {
 // Weights are FP64; the right-hand sides gh may be absent (homogeneous error equation).
 // =======================================================================================
 
+// mean of p over a cell's fluid 26-neighbours (0 without any)
+template <typename T>
+__device__ inline double fluid_mean26(int64_t cell, int nx, int ny, int nz, const uint8_t *__restrict__ type,
+                                      const T *p) {
+    int i, j, k;
+    unflatten(cell, nx, ny, i, j, k);
+    double sm = 0.0;
+    int n = 0;
+    for (int dk = -1; dk <= 1; ++dk)
+        for (int dj = -1; dj <= 1; ++dj)
+            for (int di = -1; di <= 1; ++di) {
+                const int ii = i + di, jj = j + dj, kk = k + dk;
+                if (ii < 0 || jj < 0 || kk < 0 || ii >= nx || jj >= ny || kk >= nz) continue;
+                const int64_t q = ((int64_t)kk * ny + jj) * nx + ii;
+                if (type[q] == T_FLUID) {
+                    sm += (double)p[q];
+                    ++n;
+                }
+            }
+    return n ? sm / n : 0.0;
+}
+
 // Eight lanes per ghost: lane m of a group takes stencil member m (the index and weight
 // loads of a wave are contiguous and the eight gathers are in flight together), and the
 // group sums its terms with three shuffle steps.  Degenerate ghosts (mean of the fluid
@@ -57,22 +79,7 @@ __global__ void __launch_bounds__(REFRESH_NT)
     if (!live || m != 0) return;
     double v;
     if (flags & GF_DEGENERATE) {
-        int i, j, k;
-        unflatten(cell, nx, ny, i, j, k);
-        double sm = 0.0;
-        int n = 0;
-        for (int dk = -1; dk <= 1; ++dk)
-            for (int dj = -1; dj <= 1; ++dj)
-                for (int di = -1; di <= 1; ++di) {
-                    int ii = i + di, jj = j + dj, kk = k + dk;
-                    if (ii < 0 || jj < 0 || kk < 0 || ii >= nx || jj >= ny || kk >= nz) continue;
-                    int64_t qq = ((int64_t)kk * ny + jj) * nx + ii;
-                    if (type[qq] == T_FLUID) {
-                        sm += (double)dst[qq];
-                        ++n;
-                    }
-                }
-        v = n ? sm / n : 0.0;
+        v = fluid_mean26(cell, nx, ny, nz, type, dst);
     } else {
         v = gh ? term + hg : term;
     }
@@ -959,7 +966,6 @@ template <bool WRITE_R32>
 __global__ void __launch_bounds__(NORM_NT) k_norm0(Fine<double> F, const double *__restrict__ p,
                                                    const double *__restrict__ f, const double *__restrict__ lamp,
                                                    float *r32, double *partials) {
-    __shared__ double sh[NORM_NT / 64];
     const int64_t N = (int64_t)F.nx * F.ny * F.nz;
     const double lam = *lamp;
     double sv = 0.0, s2 = 0.0, s1 = 0.0;
@@ -979,27 +985,41 @@ __global__ void __launch_bounds__(NORM_NT) k_norm0(Fine<double> F, const double 
         s1 += a;
         if (WRITE_R32) r32[id] = (float)a;
     }
-    double t;
-    t = block_sum<NORM_NT>(sv, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x] = t;
-    t = block_sum<NORM_NT>(s2, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x + 1] = t;
-    t = block_sum<NORM_NT>(s1, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x + 2] = t;
+    double sums[3] = {sv, s2, s1};
+    block_sums_store<NORM_NT, 3>(sums, partials);
 }
 
-__global__ void k_norm_finalize(const double *partials, int nb, Scalars *sc, double nfluid, int set_ref) {
-    __shared__ double sh[4];
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) {
-        a += partials[3 * q];
-        b += partials[3 * q + 1];
-        c += partials[3 * q + 2];
+// The kernels that add up partials: one workgroup of FIN_NT threads, bound by the round trips of
+// its loads, so every thread has only a few (256 threads and one sum at a time: 5.4 us).
+constexpr int FIN_NT = 1024;
+
+// sums of the NS-tuples a[0 .. nb); v[q] is the sum in thread 0
+template <int NS>
+__device__ __forceinline__ void sum_partials(const double *a, int nb, double (&v)[NS]) {
+    for (int q = threadIdx.x; q < nb; q += FIN_NT) {
+#pragma unroll
+        for (int c = 0; c < NS; ++c) v[c] += a[NS * q + c];
     }
-    a = block_sum<256>(a, sh, threadIdx.x);
-    b = block_sum<256>(b, sh, threadIdx.x);
-    c = block_sum<256>(c, sh, threadIdx.x);
+}
+template <int NS>
+__device__ __forceinline__ void finish_sums(double (&v)[NS]) {
+    __shared__ double sh[FIN_NT / 64][NS], tot[NS];
+    block_sums<FIN_NT, NS>(v, sh, threadIdx.x);
+#pragma unroll
+    for (int c = 0; c < NS; ++c)
+        if ((int)threadIdx.x == c) tot[c] = v[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NS; ++c) v[c] = tot[c];
+}
+
+__global__ void __launch_bounds__(FIN_NT) k_norm_finalize(const double *partials, int nb, Scalars *sc, double nfluid,
+                                                          int set_ref) {
+    double v[3] = {0.0, 0.0, 0.0};
+    sum_partials<3>(partials, nb, v);
+    finish_sums<3>(v);
     if (threadIdx.x == 0) {
+        const double a = v[0], b = v[1], c = v[2];
         const double delta = a / sc->vol[0];
         double q2 = b - 2.0 * delta * c + delta * delta * nfluid;
         if (q2 < 0.0) q2 = 0.0;
@@ -1036,14 +1056,13 @@ __global__ void __launch_bounds__(NORM_NT) k_fsum(Fine<double> F, const double *
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-__global__ void k_fsum_finalize(const double *partials, int nb, Scalars *sc, int pass) {
-    __shared__ double sh[4];
-    double a = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) a += partials[q];
-    a = block_sum<256>(a, sh, threadIdx.x);
+__global__ void __launch_bounds__(FIN_NT) k_fsum_finalize(const double *partials, int nb, Scalars *sc, int pass) {
+    double v[1] = {0.0};
+    sum_partials<1>(partials, nb, v);
+    finish_sums<1>(v);
     if (threadIdx.x == 0) {
-        if (pass == 0) sc->vmean = a / sc->vol[0];
-        else sc->ref = sqrt(a);
+        if (pass == 0) sc->vmean = v[0] / sc->vol[0];
+        else sc->ref = sqrt(v[0]);
     }
 }
 
@@ -1310,28 +1329,28 @@ hipError_t vcycle_mixed(ibm_grid *g, double **bufs, int *cur, const double *f, h
 
 hipError_t norm_pass(ibm_grid *g, const double *p, const double *f, hipStream_t s, bool write_r32, bool first) {
     if (write_r32)
-        hipLaunchKernelGGL(k_norm0<true>, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), p, f, &g->sc->lambda, g->r32,
+        hipLaunchKernelGGL(k_norm0<true>, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), p, f, &g->sc->lambda, g->r32,
                            g->partials);
     else
-        hipLaunchKernelGGL(k_norm0<false>, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), p, f, &g->sc->lambda,
+        hipLaunchKernelGGL(k_norm0<false>, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), p, f, &g->sc->lambda,
                            (float *)nullptr, g->partials);
-    hipLaunchKernelGGL(k_norm_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, g->sc, (double)g->nfluid,
+    hipLaunchKernelGGL(k_norm_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, red_blocks(g->N), g->sc, (double)g->nfluid,
                        0);
     (void)first;
     return hipGetLastError();
 }
 
 hipError_t ref_norm_pass(ibm_grid *g, const double *f, hipStream_t s) {
-    hipLaunchKernelGGL(k_fsum, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), f, &g->sc->vmean, g->partials, 0);
-    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, g->sc, 0);
-    hipLaunchKernelGGL(k_fsum, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), f, &g->sc->vmean, g->partials, 1);
-    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, g->sc, 1);
+    hipLaunchKernelGGL(k_fsum, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), f, &g->sc->vmean, g->partials, 0);
+    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, red_blocks(g->N), g->sc, 0);
+    hipLaunchKernelGGL(k_fsum, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), f, &g->sc->vmean, g->partials, 1);
+    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, red_blocks(g->N), g->sc, 1);
     return hipGetLastError();
 }
 
 hipError_t gauge_pass(ibm_grid *g, const double *pcur, double *pdst, hipStream_t s) {
-    hipLaunchKernelGGL(k_psum, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), pcur, g->partials);
-    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, g->sc, 0);
+    hipLaunchKernelGGL(k_psum, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), pcur, g->partials);
+    hipLaunchKernelGGL(k_fsum_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, red_blocks(g->N), g->sc, 0);
     hipLaunchKernelGGL(k_shift, dim3(nblk(g->N)), dim3(256), 0, s, g->type, g->N, pcur, pdst, g->sc);
     return hipGetLastError();
 }
@@ -1503,11 +1522,11 @@ __global__ void __launch_bounds__(NORM_NT) k_divmax(Fine<double> F, const double
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
-__global__ void __launch_bounds__(256) k_max_finalize(const double *partials, int nb, double *out) {
-    __shared__ double sh[4];
+__global__ void __launch_bounds__(FIN_NT) k_max_finalize(const double *partials, int nb, double *out) {
+    __shared__ double sh[FIN_NT / 64];
     double m = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) m = fmax(m, partials[q]);
-    m = block_max<256>(m, sh, threadIdx.x);
+    for (int q = threadIdx.x; q < nb; q += FIN_NT) m = fmax(m, partials[q]);
+    m = block_max<FIN_NT>(m, sh, threadIdx.x);
     if (threadIdx.x == 0) *out = m;
 }
 
@@ -1522,22 +1541,7 @@ __global__ void __launch_bounds__(256) k_ghost_res(GhostView G, const double *__
         const int64_t cell = G.cell[g];
         double target;
         if (G.flags[g] & GF_DEGENERATE) {
-            int i, j, k;
-            unflatten(cell, nx, ny, i, j, k);
-            double sm = 0.0;
-            int n = 0;
-            for (int dk = -1; dk <= 1; ++dk)
-                for (int dj = -1; dj <= 1; ++dj)
-                    for (int di = -1; di <= 1; ++di) {
-                        const int ii = i + di, jj = j + dj, kk = k + dk;
-                        if (ii < 0 || jj < 0 || kk < 0 || ii >= nx || jj >= ny || kk >= nz) continue;
-                        const int64_t q = ((int64_t)kk * ny + jj) * nx + ii;
-                        if (type[q] == T_FLUID) {
-                            sm += p[q];
-                            ++n;
-                        }
-                    }
-            target = n ? sm / n : 0.0;
+            target = fluid_mean26(cell, nx, ny, nz, type, p);
         } else {
             double sm = 0.0;
             for (int m = 0; m < 8; ++m) {
@@ -1554,19 +1558,19 @@ __global__ void __launch_bounds__(256) k_ghost_res(GhostView G, const double *__
 
 hipError_t ghost_residual_pass(ibm_grid *g, const double *p, hipStream_t s) {
     if (g->ng == 0) {
-        hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(256), 0, s, g->partials, 0, &g->sc->ghost_res);
+        hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, 0, &g->sc->ghost_res);
         return hipGetLastError();
     }
     const unsigned nb = (unsigned)((g->ng + 255) / 256);
     hipLaunchKernelGGL(k_ghost_res, dim3(nb), dim3(256), 0, s, ghost_view(g), p, g->nx, g->ny, g->nz, g->type,
                        g->partials);
-    hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(256), 0, s, g->partials, (int)nb, &g->sc->ghost_res);
+    hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, (int)nb, &g->sc->ghost_res);
     return hipGetLastError();
 }
 
 hipError_t divmax_pass(ibm_grid *g, const double *u, const double *v, const double *w, hipStream_t s) {
-    hipLaunchKernelGGL(k_divmax, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, fine64(g), u, v, w, g->partials);
-    hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, &g->sc->div_max);
+    hipLaunchKernelGGL(k_divmax, dim3(red_blocks(g->N)), dim3(NORM_NT), 0, s, fine64(g), u, v, w, g->partials);
+    hipLaunchKernelGGL(k_max_finalize, dim3(1), dim3(FIN_NT), 0, s, g->partials, red_blocks(g->N), &g->sc->div_max);
     return hipGetLastError();
 }
 
@@ -1600,91 +1604,85 @@ __global__ void k_ghost_scale(int64_t ng, const int32_t *__restrict__ gcell, int
     scale[g] = d;
 }
 
-// ghost rows of A y (mode 0) or of b - A y (mode 1: out = s_g h_g - A y).  With gpart, the
-// block sums of o_g out_g and out_g^2 over the ghost rows go to gpart[2 block + (0, 1)].
-__global__ void k_apply_ghost(GhostView G, const double *__restrict__ y, double *out, const double *__restrict__ scale,
-                              int nx, int ny, int nz, const uint8_t *__restrict__ type, int mode,
-                              const double *__restrict__ o, double *gpart) {
-    __shared__ double sh[4];
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double d0 = 0.0, d1 = 0.0;
-    if (g < G.ng) {
-        const int64_t cell = G.cell[g];
-        double target;
-        if (G.flags[g] & GF_DEGENERATE) {
-            int i, j, k;
-            unflatten(cell, nx, ny, i, j, k);
-            double s = 0.0;
-            int n = 0;
-            for (int dk = -1; dk <= 1; ++dk)
-                for (int dj = -1; dj <= 1; ++dj)
-                    for (int di = -1; di <= 1; ++di) {
-                        const int ii = i + di, jj = j + dj, kk = k + dk;
-                        if (ii < 0 || jj < 0 || kk < 0 || ii >= nx || jj >= ny || kk >= nz) continue;
-                        const int64_t q = ((int64_t)kk * ny + jj) * nx + ii;
-                        if (type[q] == T_FLUID) {
-                            s += y[q];
-                            ++n;
-                        }
-                    }
-            target = n ? s / n : 0.0;
-        } else {
-            const int32_t *st = G.st + 8 * g;
-            const double *beta = G.beta + 8 * g;
-            double s = 0.0;
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-                if (st[m] >= 0) s = s + beta[m] * y[st[m]];
-            target = s;
+// Ghost rows, before the operator pass (which leaves ghost cells alone): out = s_g (y_g - sum
+// beta y) (RESIDUAL: s_g h_g minus that).  Without RESIDUAL also, per block,
+// flux: the block's share of the volume-weighted fluid sum of the operator image.  Summed over
+//   the fluid rows, V_c (S y)_c = sum_f T_f (y_nb - y_c) cancels on every face between two fluid
+//   cells (T_f = V a_f is the same from both sides) and no flux crosses the box walls, so only the
+//   faces between a fluid cell c and a ghost cell g remain: sum of V_c a_(c->g) (y_g - y_c).
+// gpart[2 block + (0, 1)]: sums of o_g out_g and out_g^2.
+// Eight lanes per ghost, one stencil member and one face each, so that a ghost's gathers are in
+// flight together: the pass is bound by two round trips.  Flux and rows apart, one thread per
+// ghost, the flux added up in a launch between them: 19 us at 128^3, now 4.5 and 2 in the operator.
+constexpr int GHOST_ROW_NT = 256, GHOST_ROW_G = GHOST_ROW_NT / 8;
+template <bool RESIDUAL>
+__global__ void __launch_bounds__(GHOST_ROW_NT)
+    k_ghost_rows(GhostView G, Fine<double> F, const double *__restrict__ y, double *out,
+                 const double *__restrict__ scale, const double *__restrict__ o, double *flux, double *gpart) {
+    const int m = (int)threadIdx.x & 7, nx = F.nx, ny = F.ny, nz = F.nz;
+    double acc = 0.0, d0 = 0.0, d1 = 0.0;
+    for (int64_t g0 = (int64_t)blockIdx.x * GHOST_ROW_G; g0 < G.ng; g0 += (int64_t)gridDim.x * GHOST_ROW_G) {
+        const int64_t g = g0 + (threadIdx.x >> 3);
+        const bool live = g < G.ng;
+        const int64_t gc = live ? g : 0;
+        const int32_t q = G.st[8 * gc + m];
+        const double beta = G.beta[8 * gc + m], sc = scale[gc];
+        const double h = RESIDUAL ? G.h[gc] : 0.0;
+        const int32_t flags = G.flags[gc];
+        const int64_t cell = G.cell[gc];
+        const double yg = y[cell], og = RESIDUAL ? 0.0 : o[cell];
+        double term = live && q >= 0 ? beta * y[max(q, 0)] : 0.0;
+        if (!RESIDUAL && live && m < 6) {
+            // lanes 0 .. 5: the fluid cell below, above along x, y, z
+            const int d = m >> 1, up = m & 1;
+            int I[3];
+            unflatten(cell, nx, ny, I[0], I[1], I[2]);
+            const int at = (d == 0 ? I[0] : d == 1 ? I[1] : I[2]) + (up ? 1 : -1);
+            if (at >= 0 && at < (d == 0 ? nx : d == 1 ? ny : nz)) {
+                const int64_t step = d == 0 ? 1 : d == 1 ? (int64_t)nx : (int64_t)nx * ny;
+                const int64_t c = cell + (up ? step : -step);
+                const double *a = up ? (d == 0 ? F.axm : d == 1 ? F.aym : F.azm)
+                                     : (d == 0 ? F.axp : d == 1 ? F.ayp : F.azp);
+                if (F.type[c] == T_FLUID)
+                    acc += ((F.wx[d == 0 ? at : I[0]] * F.wy[d == 1 ? at : I[1]]) * F.wz[d == 2 ? at : I[2]]) * a[at] *
+                           (yg - y[c]);
+            }
         }
-        const double a = scale[g] * (y[cell] - target);
-        const double v = mode ? scale[g] * G.h[g] - a : a;
+        term += __shfl_xor(term, 1, 64);
+        term += __shfl_xor(term, 2, 64);
+        term += __shfl_xor(term, 4, 64);
+        if (!live || m != 0) continue;
+        if (flags & GF_DEGENERATE) term = fluid_mean26(cell, nx, ny, nz, F.type, y);
+        const double a = sc * (yg - term);
+        const double v = RESIDUAL ? sc * h - a : a;
         out[cell] = v;
-        if (gpart) {
-            d0 = o[cell] * v;
-            d1 = v * v;
-        }
+        d0 += og * v;
+        d1 += v * v;
     }
-    if (gpart) {  // uniform: every thread of the block takes part in the sums
-        const double s0 = block_sum<256>(d0, sh, threadIdx.x);
-        const double s1 = block_sum<256>(d1, sh, threadIdx.x);
-        if (threadIdx.x == 0) {
-            gpart[2 * blockIdx.x] = s0;
-            gpart[2 * blockIdx.x + 1] = s1;
-        }
-    }
+    if (RESIDUAL) return;
+    double sums[3] = {acc, d0, d1};
+    __shared__ double sh[GHOST_ROW_NT / 64][3];
+    block_sums<GHOST_ROW_NT, 3>(sums, sh, threadIdx.x);
+    if (threadIdx.x == 0) flux[blockIdx.x] = sums[0];
+    if (threadIdx.x == 1) gpart[2 * blockIdx.x] = sums[1];
+    if (threadIdx.x == 2) gpart[2 * blockIdx.x + 1] = sums[2];
 }
 
-// The volume-weighted fluid sum of an operator image, before the image is formed.  Summed
-// over the fluid rows, V_c (S y)_c = sum_f T_f (y_nb - y_c) cancels on every face between two
-// fluid cells (T_f = V a_f is the same from both sides) and no flux crosses the box walls, so
-// only the faces between a fluid cell and a ghost cell remain: per block, the sum over ghosts
-// g and their fluid face neighbours c of V_c a_(c->g) (y_g - y_c).
-__global__ void k_ghost_flux(GhostView G, Fine<double> F, const double *__restrict__ y, double *partials) {
-    __shared__ double sh[4];
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
-    if (g < G.ng) {
-        const int64_t cell = G.cell[g];
-        int i, j, k;
-        unflatten(cell, F.nx, F.ny, i, j, k);
-        const int64_t sy = F.nx, sz = (int64_t)F.nx * F.ny;
-        const double yg = y[cell];
-        if (i > 0 && F.type[cell - 1] == T_FLUID)
-            acc += ((F.wx[i - 1] * F.wy[j]) * F.wz[k]) * F.axp[i - 1] * (yg - y[cell - 1]);
-        if (i < F.nx - 1 && F.type[cell + 1] == T_FLUID)
-            acc += ((F.wx[i + 1] * F.wy[j]) * F.wz[k]) * F.axm[i + 1] * (yg - y[cell + 1]);
-        if (j > 0 && F.type[cell - sy] == T_FLUID)
-            acc += ((F.wx[i] * F.wy[j - 1]) * F.wz[k]) * F.ayp[j - 1] * (yg - y[cell - sy]);
-        if (j < F.ny - 1 && F.type[cell + sy] == T_FLUID)
-            acc += ((F.wx[i] * F.wy[j + 1]) * F.wz[k]) * F.aym[j + 1] * (yg - y[cell + sy]);
-        if (k > 0 && F.type[cell - sz] == T_FLUID)
-            acc += ((F.wx[i] * F.wy[j]) * F.wz[k - 1]) * F.azp[k - 1] * (yg - y[cell - sz]);
-        if (k < F.nz - 1 && F.type[cell + sz] == T_FLUID)
-            acc += ((F.wx[i] * F.wy[j]) * F.wz[k + 1]) * F.azm[k + 1] * (yg - y[cell + sz]);
+// The cells in x pairs of the flat order (16-byte accesses, aligned as one element), a contiguous
+// range per block; an odd last cell by itself.  The eight streams of k_xr_update at 384^3: 729 us;
+// ranges strided over the whole launch 767, single cells 733, x and r in passes of their own 764.
+template <typename P, typename L>
+__device__ __forceinline__ void for_pairs(const uint8_t *__restrict__ type, int64_t N, P pair, L last) {
+    const int64_t step = 2 * (int64_t)blockDim.x, per = (N + step * gridDim.x - 1) / (step * gridDim.x) * step;
+    const int64_t end = min(N, per * ((int64_t)blockIdx.x + 1));
+    for (int64_t id = per * blockIdx.x + 2 * (int64_t)threadIdx.x; id < end; id += step) {
+        if (id + 1 < N) {
+            const uint16_t tt = *(const uint16_t *)(type + id);  // type is 256-byte aligned
+            pair(id, tt & 0xff, tt >> 8);
+        } else {
+            last(id, type[id]);
+        }
     }
-    const double t = block_sum<256>(acc, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
 // start of the Krylov recurrences on the residual v: projection of its fluid part
@@ -1692,25 +1690,31 @@ __global__ void k_ghost_flux(GhostView G, Fine<double> F, const double *__restri
 // (fluid).  (The operator images of a step are projected where they are formed.)
 __global__ void __launch_bounds__(NORM_NT) k_project(const uint8_t *__restrict__ type, int64_t N, double *v, double *rh,
                                                      const Scalars *sc, int mode, double *partials) {
-    __shared__ double sh[NORM_NT / 64];
-    const double mu = sc->mu_v;
-    double a = 0.0, b = 0.0;
-    for (int64_t id = (int64_t)blockIdx.x * NORM_NT + threadIdx.x; id < N; id += (int64_t)gridDim.x * NORM_NT) {
-        const uint8_t t = type[id];
-        if (t == T_DEAD) continue;
-        double x = v[id];
-        if (t == T_FLUID && mode != 3) {
-            x -= mu;
-            v[id] = x;
+    const double mu = mode == 3 ? 0.0 : sc->mu_v;
+    double s[2] = {0.0, 0.0};
+    for_pairs(type, N, [&](int64_t id, int t0, int t1) {
+        const DPair x = *(const DPair *)(v + id);
+        const DPair r = {t0 == T_FLUID ? x.x - mu : x.x, t1 == T_FLUID ? x.y - mu : x.y};
+        if (t0 != T_DEAD && t1 != T_DEAD) {
+            if (mode != 3) *(DPair *)(v + id) = r;
+            *(DPair *)(rh + id) = r;
+        } else {
+            if (t0 != T_DEAD) v[id] = rh[id] = r.x;
+            if (t1 != T_DEAD) v[id + 1] = rh[id + 1] = r.y;
         }
-        rh[id] = x;
-        a += x * x;
-        if (t == T_FLUID) b += x * x;
-    }
-    double s = block_sum<NORM_NT>(a, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[2 * blockIdx.x] = s;
-    s = block_sum<NORM_NT>(b, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[2 * blockIdx.x + 1] = s;
+        const double q0 = t0 == T_DEAD ? 0.0 : r.x * r.x, q1 = t1 == T_DEAD ? 0.0 : r.y * r.y;
+        s[0] += q0;
+        s[0] += q1;
+        s[1] += t0 == T_FLUID ? q0 : 0.0;
+        s[1] += t1 == T_FLUID ? q1 : 0.0;
+    }, [&](int64_t id, int t) {
+        if (t == T_DEAD) return;
+        const double r = t == T_FLUID ? v[id] - mu : v[id];
+        v[id] = rh[id] = r;
+        s[0] += r * r;
+        s[1] += t == T_FLUID ? r * r : 0.0;
+    });
+    block_sums_store<NORM_NT, 2>(s, partials);
 }
 
 // Near-breakdown of BiCGStab: an inner product whose modulus is at most brk_tol (the option
@@ -1719,19 +1723,16 @@ __global__ void __launch_bounds__(NORM_NT) k_project(const uint8_t *__restrict__
 // quotient (alpha = 0; beta = 0) and sets sc->brk; the host restarts the shadow residual from
 // the residual.
 
-// stride 3 (K_RHO): sums of rh.r, r.r on fluid rows and r.r on every active row
-__global__ void k_krylov_finalize(const double *partials, int nb, int stride, Scalars *sc, int op, double brk_tol) {
-    __shared__ double sh[4];
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) {
-        a += partials[stride * q];
-        if (stride > 1) b += partials[stride * q + 1];
-        if (stride > 2) c += partials[stride * q + 2];
-    }
-    a = block_sum<256>(a, sh, threadIdx.x);
-    b = block_sum<256>(b, sh, threadIdx.x);
-    c = block_sum<256>(c, sh, threadIdx.x);
+// NS sums per block: 1 (K_MU), 2 (K_INIT, K_RESTART) or 3 (K_RHO: rh.r, r.r on fluid rows and r.r
+// on every active row)
+template <int NS>
+__global__ void __launch_bounds__(FIN_NT) k_krylov_finalize(const double *partials, int nb, Scalars *sc, int op,
+                                                            double brk_tol) {
+    double s[NS] = {};
+    sum_partials<NS>(partials, nb, s);
+    finish_sums<NS>(s);
     if (threadIdx.x != 0) return;
+    const double a = s[0], b = s[1 % NS], c = s[2 % NS];
     switch (op) {
         case K_MU: sc->mu_v = a / sc->vol[0]; break;
         case K_ALPHA:
@@ -1761,23 +1762,16 @@ __global__ void k_krylov_finalize(const double *partials, int nb, int stride, Sc
     }
 }
 
-// alpha = rho / rh.v or omega = t.s / t.t from the operator pass's sums (stride ns over nb
-// workgroups: o w, then w w) and the ghost rows' (stride 2 over ngb blocks)
-__global__ void k_krylov_finalize_dots(const double *part, int nb, int ns, const double *gpart, int ngb, Scalars *sc,
-                                       int op, double brk_tol) {
-    __shared__ double sh[4];
-    double a = 0.0, b = 0.0;
-    for (int q = threadIdx.x; q < nb; q += 256) {
-        a += part[ns * q];
-        if (ns > 1) b += part[ns * q + 1];
-    }
-    for (int q = threadIdx.x; q < ngb; q += 256) {
-        a += gpart[2 * q];
-        b += gpart[2 * q + 1];
-    }
-    a = block_sum<256>(a, sh, threadIdx.x);
-    b = block_sum<256>(b, sh, threadIdx.x);
+// alpha = rho / rh.v or omega = t.s / t.t from the operator pass's sums (o w, then w w, of nb
+// workgroups) and the ghost rows' (of ngb blocks)
+__global__ void __launch_bounds__(FIN_NT) k_krylov_finalize_dots(const double *part, int nb, const double *gpart,
+                                                                 int ngb, Scalars *sc, int op, double brk_tol) {
+    double s[2] = {0.0, 0.0};
+    sum_partials<2>(part, nb, s);
+    sum_partials<2>(gpart, ngb, s);
+    finish_sums<2>(s);
     if (threadIdx.x != 0) return;
+    const double a = s[0], b = s[1];
     if (op == K_ALPHA) {
         // a = rh.v, b = v.v
         if (fabs(a) > brk_tol * sqrt(sc->rh2 * b)) {
@@ -1791,15 +1785,42 @@ __global__ void k_krylov_finalize_dots(const double *part, int nb, int ns, const
     }
 }
 
+// Start of a preconditioner application, by the blocks of the update kernels that take the ghost
+// cells: the ghost right-hand sides gh = x_g / s_g of the vector x the kernel forms, and
+// e_g = gh (the first ghost refresh of a zero field; 0 at degenerate ghosts, which take the mean
+// of their (zero) fluid neighbours).  A pass of its own took 3.6 us, twice a step, for a few
+// thousand ghosts.
+template <typename T>
+struct GhostStart {
+    int64_t ng;
+    const int32_t *cell, *flags;
+    const double *scale;
+    double *gh;
+    T *e;
+    int blocks;  // the first blocks of the launch, one thread per ghost
+    __device__ __forceinline__ void put(int64_t g, int64_t id, double x, float *r32) const {
+        const double h = x / scale[g];
+        gh[g] = h;
+        e[id] = (flags[g] & GF_DEGENERATE) ? T(0) : (T)h;
+        if (r32) r32[id] = 0.0f;
+    }
+};
+
 // pd = r + beta (pd - omega v) on fluid + ghost cells
 // r32 (mixed precision, else null): the FP32 right-hand side of the preconditioner, the
 // fluid part of the result rounded to FP32 and zero elsewhere
 // first: the first step of a solve, p = r (beta is 0 and p, v hold nothing yet: not read)
-__global__ void k_p_update(const uint8_t *__restrict__ type, int64_t N, const double *__restrict__ r,
-                           const double *__restrict__ v, double *pd, const Scalars *sc, float *r32, int first) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= N) return;
-    const uint8_t ty = type[id];
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_p_update(const uint8_t *__restrict__ type, int64_t N, const double *__restrict__ r, const double *__restrict__ v,
+               double *pd, const Scalars *sc, float *r32, int first, GhostStart<T> S) {
+    const bool ghosts = (int)blockIdx.x < S.blocks;
+    int64_t id = (int64_t)(ghosts ? (int)blockIdx.x : (int)blockIdx.x - S.blocks) * 256 + threadIdx.x;
+    if (id >= (ghosts ? S.ng : N)) return;
+    const int64_t g = id;
+    if (ghosts) id = S.cell[g];
+    const uint8_t ty = ghosts ? T_GHOST : type[id];
+    if (!ghosts && ty == T_GHOST) return;
     if (ty == T_DEAD) {
         pd[id] = 0.0;
         if (r32) r32[id] = 0.0f;
@@ -1808,20 +1829,28 @@ __global__ void k_p_update(const uint8_t *__restrict__ type, int64_t N, const do
     double pv = r[id];
     if (!first) pv = pv + sc->beta * (pd[id] - sc->omega * v[id]);
     __builtin_nontemporal_store(pv, pd + id);
-    if (r32) r32[id] = (ty == T_FLUID) ? (float)pv : 0.0f;
+    if (ghosts) S.put(g, id, pv, r32);
+    else if (r32) r32[id] = (float)pv;
 }
 
 // The BiCGStab vector updates write their full-field results with non-temporal stores (see
 // the operator pass).
 // s = r - alpha v
-__global__ void k_s_update(const uint8_t *__restrict__ type, int64_t N, const double *__restrict__ r,
-                           const double *__restrict__ v, double *s, const Scalars *sc, float *r32) {
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= N) return;
-    const uint8_t ty = type[id];
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_s_update(const uint8_t *__restrict__ type, int64_t N, const double *__restrict__ r, const double *__restrict__ v,
+               double *s, const Scalars *sc, float *r32, GhostStart<T> S) {
+    const bool ghosts = (int)blockIdx.x < S.blocks;
+    int64_t id = (int64_t)(ghosts ? (int)blockIdx.x : (int)blockIdx.x - S.blocks) * 256 + threadIdx.x;
+    if (id >= (ghosts ? S.ng : N)) return;
+    const int64_t g = id;
+    if (ghosts) id = S.cell[g];
+    const uint8_t ty = ghosts ? T_GHOST : type[id];
+    if (!ghosts && ty == T_GHOST) return;
     const double sv = (ty == T_DEAD) ? 0.0 : r[id] - sc->alpha * v[id];
     __builtin_nontemporal_store(sv, s + id);
-    if (r32) r32[id] = (ty == T_FLUID) ? (float)sv : 0.0f;
+    if (ghosts) S.put(g, id, sv, r32);
+    else if (r32) r32[id] = (ty == T_FLUID) ? (float)sv : 0.0f;
 }
 
 // x += alpha y + omega z ; r = s - omega t ; partials of rh.r (all), r.r (fluid) and r.r (all)
@@ -1830,31 +1859,45 @@ __global__ void __launch_bounds__(NORM_NT) k_xr_update(const uint8_t *__restrict
                                                        const double *__restrict__ s, const double *__restrict__ t,
                                                        double *r, const double *__restrict__ rh, const Scalars *sc,
                                                        double *partials) {
-    __shared__ double sh[NORM_NT / 64];
     const double alpha = sc->alpha, omega = sc->omega;
-    double a = 0.0, b = 0.0, c = 0.0;
-    for (int64_t id = (int64_t)blockIdx.x * NORM_NT + threadIdx.x; id < N; id += (int64_t)gridDim.x * NORM_NT) {
-        const uint8_t ty = type[id];
-        if (ty == T_DEAD) continue;
-        __builtin_nontemporal_store(x[id] + alpha * y[id] + omega * z[id], x + id);
+    double sums[3] = {0.0, 0.0, 0.0};
+    auto add = [&](int ty, double rhv, double rv) {
+        // selected, not multiplied: the shadow residual is never written on dead cells
+        sums[0] += ty == T_DEAD ? 0.0 : rhv * rv;
+        sums[1] += ty == T_FLUID ? rv * rv : 0.0;
+        sums[2] += ty == T_DEAD ? 0.0 : rv * rv;
+    };
+    for_pairs(type, N, [&](int64_t id, int t0, int t1) {
+        const DPair xv = *(const DPair *)(x + id), yv = *(const DPair *)(y + id), zv = *(const DPair *)(z + id),
+                    sv = *(const DPair *)(s + id), tv = *(const DPair *)(t + id), hv = *(const DPair *)(rh + id);
+        const DPair xn = {xv.x + alpha * yv.x + omega * zv.x, xv.y + alpha * yv.y + omega * zv.y};
+        const DPair rn = {sv.x - omega * tv.x, sv.y - omega * tv.y};
+        if (t0 != T_DEAD && t1 != T_DEAD) {
+            __builtin_nontemporal_store(xn, (DPair *)(x + id));
+            __builtin_nontemporal_store(rn, (DPair *)(r + id));
+        } else if (t0 != T_DEAD) {
+            x[id] = xn.x;
+            r[id] = rn.x;
+        } else if (t1 != T_DEAD) {
+            x[id + 1] = xn.y;
+            r[id + 1] = rn.y;
+        }
+        add(t0, hv.x, rn.x);
+        add(t1, hv.y, rn.y);
+    }, [&](int64_t id, int ty) {
+        if (ty == T_DEAD) return;
+        x[id] = x[id] + alpha * y[id] + omega * z[id];
         const double rv = s[id] - omega * t[id];
-        __builtin_nontemporal_store(rv, r + id);
-        a += rh[id] * rv;
-        c += rv * rv;
-        if (ty == T_FLUID) b += rv * rv;
-    }
-    double q = block_sum<NORM_NT>(a, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x] = q;
-    q = block_sum<NORM_NT>(b, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x + 1] = q;
-    q = block_sum<NORM_NT>(c, sh, threadIdx.x);
-    if (threadIdx.x == 0) partials[3 * blockIdx.x + 2] = q;
+        r[id] = rv;
+        add(ty, rh[id], rv);
+    });
+    block_sums_store<NORM_NT, 3>(sums, partials);
 }
 
-// preconditioner start: ghost right-hand sides gh = r_g / s_g and e_g = gh (the first ghost
-// refresh of a zero field), every other cell 0.  k_precond_zero clears both buffers when no
-// pre-smoothing sweep comes first; otherwise the start iterate (zero except at the ghost
-// cells) is only read by the first sweep, which writes every cell of its output.
+// The start iterate of a preconditioner application is zero except at the ghost cells, which the
+// update kernel before it writes (GhostStart).  k_precond_zero clears both buffers when no
+// pre-smoothing sweep comes first; otherwise the start iterate is only read by the first sweep,
+// which writes every cell of its output.
 template <typename T>
 __global__ void k_precond_zero(int64_t N, T *ea, T *eb) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1862,112 +1905,99 @@ __global__ void k_precond_zero(int64_t N, T *ea, T *eb) {
     ea[id] = T(0);
     if (eb) eb[id] = T(0);
 }
-template <typename T>
-__global__ void k_precond_ghosts(int64_t ng, const int32_t *__restrict__ gcell, const int32_t *__restrict__ flags,
-                                 const double *__restrict__ scale, const double *__restrict__ r, double *gh, T *ea) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= ng) return;
-    const int64_t cell = gcell[g];
-    const double h = r[cell] / scale[g];
-    gh[g] = h;
-    // a degenerate ghost takes the mean of its (zero) fluid neighbours
-    ea[cell] = (flags[g] & GF_DEGENERATE) ? T(0) : (T)h;
-}
 __global__ void k_widen(const uint8_t *__restrict__ type, int64_t N, const float *__restrict__ e, double *y) {
     const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= N) return;
     y[id] = (type[id] == T_DEAD) ? 0.0 : (double)e[id];
 }
 
+// The start iterate of the next preconditioner application (y in ya or yb), cleared if that is
+// one of its working buffers; its ghost values are the update kernel's to write (GhostStart).
+template <typename T>
+static T *precond_start(ibm_grid *g, double *ya, double *yb, const ibm_solve_opts *o, hipStream_t s) {
+    const unsigned nbN = (unsigned)nblk(g->N);
+    if constexpr (sizeof(T) == 4) {
+        if (o->nu1 > 0) return g->pz32;
+        hipLaunchKernelGGL(k_precond_zero<float>, dim3(nbN), dim3(256), 0, s, g->N, g->e32a, g->e32b);
+        return g->e32a;
+    } else {
+        const bool srj = o->method == IBM_BICGSTAB_SRJ;
+        if (srj ? !g->srj_omega.empty() : o->nu1 > 0) return g->pz;
+        hipLaunchKernelGGL(k_precond_zero<double>, dim3(nbN), dim3(256), 0, s, g->N, ya, srj ? (double *)nullptr : yb);
+        return ya;
+    }
+}
+
+template <typename T>
+static GhostStart<T> ghost_start(ibm_grid *g, T *e) {
+    return GhostStart<T>{g->ng, g->g_cell, g->g_flags, g->g_scale, g->g_rhs, e, g->ng > 0 ? (int)nblk(g->ng) : 0};
+}
+
 // y = M r: one V-cycle from zero on the error equation with right-hand side r (fluid) and
-// ghost right-hand sides r_g / s_g.  FP64: the result lands in one of (ya, yb), returned.
+// ghost right-hand sides r_g / s_g (g->g_rhs, and the start iterate e0 at the ghost cells, both
+// written by the kernel that formed r).  FP64: the result lands in one of (ya, yb), returned.
 // Mixed: the cycle runs in FP32 on the workspace's FP32 buffers and is widened into ya.
 // IBM_BICGSTAB_SRJ: instead of the V-cycle, the scheduled relaxed Jacobi sweeps of the
 // grid's schedule, each followed by the ghost refresh (FP64).
-static hipError_t precondition(ibm_grid *g, const double *r, double *ya, double *yb, double **out,
+template <typename T>
+static hipError_t precondition(ibm_grid *g, const double *r, const T *e0, double *ya, double *yb, double **out,
                                const ibm_solve_opts *o, hipStream_t s) {
     hipError_t e;
-    const unsigned nbN = (unsigned)nblk(g->N), nbG = (unsigned)nblk(g->ng > 0 ? g->ng : 1);
-    // With pre-smoothing the cycle starts from the start iterate (zero except at the ghost
-    // cells, written here), which the first sweep only reads: no field is cleared per call.
-    if (o->precision == IBM_MIXED) {
-        const bool st = o->nu1 > 0;
+    // With pre-smoothing the cycle starts from the start iterate, which the first sweep only
+    // reads: no field is cleared per call.
+    const T *start = o->nu1 > 0 ? e0 : nullptr;
+    if constexpr (sizeof(T) == 4) {
         // g->r32 already holds the FP32 fluid part of r: the update kernel that formed r
         // (k_p_update, k_s_update) wrote it beside r
-        float *e0 = st ? g->pz32 : g->e32a;
-        if (!st) hipLaunchKernelGGL(k_precond_zero<float>, dim3(nbN), dim3(256), 0, s, g->N, g->e32a, g->e32b);
-        if (g->ng > 0)
-            hipLaunchKernelGGL(k_precond_ghosts<float>, dim3(nbG), dim3(256), 0, s, g->ng, g->g_cell, g->g_flags,
-                               g->g_scale, r, g->g_rhs, e0);
         float *eb[2] = {g->e32a, g->e32b};
         int ecur = 0;
         // with post-smoothing, the last sweep writes the FP64 result itself
         double *wide = o->nu2 > 0 ? ya : nullptr;
-        if ((e = vcycle_impl<float>(g, eb, &ecur, g->r32, &g->sc->zero32, g->g_rhs, o, s, st ? e0 : nullptr,
-                                    wide)) != hipSuccess)
+        if ((e = vcycle_impl<float>(g, eb, &ecur, g->r32, &g->sc->zero32, g->g_rhs, o, s, start, wide)) != hipSuccess)
             return e;
-        if (!wide) hipLaunchKernelGGL(k_widen, dim3(nbN), dim3(256), 0, s, g->type, g->N, eb[ecur], ya);
+        if (!wide)
+            hipLaunchKernelGGL(k_widen, dim3((unsigned)nblk(g->N)), dim3(256), 0, s, g->type, g->N, eb[ecur], ya);
         *out = ya;
     } else if (o->method == IBM_BICGSTAB_SRJ) {
         // scheduled relaxed Jacobi: every sweep writes all cells of the other buffer; the first
-        // one reads the start iterate
-        if (g->ng > 0)
-            hipLaunchKernelGGL(k_precond_ghosts<double>, dim3(nbG), dim3(256), 0, s, g->ng, g->g_cell, g->g_flags,
-                               g->g_scale, r, g->g_rhs, g->pz);
+        // one reads the start iterate (no sweep: the start iterate, in ya, is the result)
         double *bufs[2] = {ya, yb};
         int cur = 0;
-        bool first = true;
+        const double *pin = e0;
         const Fine<double> F = fine64(g);
         for (double w : g->srj_omega) {
-            const double *pin = first ? g->pz : bufs[cur];
             if ((e = launch_jacobi0(F, pin, r, bufs[1 - cur], w, s)) != hipSuccess) return e;
             if ((e = launch_refresh<double>(g, pin, bufs[1 - cur], g->g_rhs, s)) != hipSuccess) return e;
             cur = 1 - cur;
-            first = false;
-        }
-        if (first) {  // no sweep: the start iterate itself
-            hipLaunchKernelGGL(k_precond_zero<double>, dim3(nbN), dim3(256), 0, s, g->N, ya, (double *)nullptr);
-            if (g->ng > 0)
-                hipLaunchKernelGGL(k_precond_ghosts<double>, dim3(nbG), dim3(256), 0, s, g->ng, g->g_cell,
-                                   g->g_flags, g->g_scale, r, g->g_rhs, ya);
+            pin = bufs[cur];
         }
         *out = bufs[cur];
     } else {
-        const bool st = o->nu1 > 0;
-        double *e0 = st ? g->pz : ya;
-        if (!st) hipLaunchKernelGGL(k_precond_zero<double>, dim3(nbN), dim3(256), 0, s, g->N, ya, yb);
-        if (g->ng > 0)
-            hipLaunchKernelGGL(k_precond_ghosts<double>, dim3(nbG), dim3(256), 0, s, g->ng, g->g_cell, g->g_flags,
-                               g->g_scale, r, g->g_rhs, e0);
         double *bufs[2] = {ya, yb};
         int cur = 0;
-        if ((e = vcycle_impl<double>(g, bufs, &cur, r, &g->sc->zero, g->g_rhs, o, s, st ? e0 : nullptr)) !=
-            hipSuccess)
-            return e;
+        if ((e = vcycle_impl<double>(g, bufs, &cur, r, &g->sc->zero, g->g_rhs, o, s, start)) != hipSuccess) return e;
         *out = bufs[cur];
     }
     return hipGetLastError();
 }
 
 // w = P A y (the fluid part with its volume-weighted mean removed) and the inner products of
-// `mode` (0: rh.w for alpha; 1: t.s and t.t for omega), then alpha or omega.  The mean comes
-// first, from the fluid-ghost faces alone (k_ghost_flux), so the operator pass writes the
-// projected image and forms its inner products in the same sweep.
+// `mode` (0: rh.w for alpha; 1: t.s and t.t for omega), then alpha or omega.  The ghost rows come
+// first, and with them the mean (from the fluid-ghost faces alone), so the operator pass writes
+// the projected image and forms its inner products in the same sweep.
 static hipError_t apply_projected(ibm_grid *g, const double *y, double *w, const double *other, int mode, int op,
                                   double brk_tol, hipStream_t s) {
-    const int ngb = g->ng > 0 ? nblk(g->ng) : 0;
-    double *gpart = g->partials + 2 * zmarch_partials_max(g->nx, g->ny, g->nz);
+    const int ngb = g->ng > 0 ? std::min(GHOST_ROW_BLOCKS, (int)((g->ng + GHOST_ROW_G - 1) / GHOST_ROW_G)) : 0;
+    double *gpart = g->partials + 2 * zmarch_partials_max(g->nx, g->ny, g->nz), *flux = gpart + 2 * GHOST_ROW_BLOCKS;
     if (g->ng > 0)
-        hipLaunchKernelGGL(k_ghost_flux, dim3(ngb), dim3(256), 0, s, ghost_view(g), fine64(g), y, g->partials);
-    hipLaunchKernelGGL(k_krylov_finalize, dim3(1), dim3(256), 0, s, g->partials, ngb, 1, g->sc, (int)K_MU, 0.0);
+        hipLaunchKernelGGL(k_ghost_rows<false>, dim3(ngb), dim3(GHOST_ROW_NT), 0, s, ghost_view(g), fine64(g), y, w,
+                           g->g_scale, other, flux, gpart);
     int nparts = 0;
-    hipError_t e = launch_apply_fluid(fine64(g), y, w, other, &g->sc->mu_v, mode + 1, g->partials, &nparts, s);
+    hipError_t e = launch_apply_fluid(fine64(g), y, w, other, MeanParts{flux, ngb, &g->sc->vol[0]}, mode + 1,
+                                      g->partials, &nparts, s);
     if (e != hipSuccess) return e;
-    if (g->ng > 0)
-        hipLaunchKernelGGL(k_apply_ghost, dim3(ngb), dim3(256), 0, s, ghost_view(g), y, w, g->g_scale, g->nx, g->ny,
-                           g->nz, g->type, 0, other, gpart);
-    hipLaunchKernelGGL(k_krylov_finalize_dots, dim3(1), dim3(256), 0, s, g->partials, nparts, 2, gpart, ngb, g->sc,
-                       op, brk_tol);
+    hipLaunchKernelGGL(k_krylov_finalize_dots, dim3(1), dim3(FIN_NT), 0, s, g->partials, nparts, gpart, ngb, g->sc, op,
+                       brk_tol);
     return hipGetLastError();
 }
 
@@ -1981,47 +2011,58 @@ hipError_t krylov_setup(ibm_grid *g, hipStream_t s) {
 // r = P (b - A x), rh = r, rho = rh.r, norm of the fluid part; lambda = removed mean
 hipError_t krylov_residual(ibm_grid *g, const double *f, const double *x, hipStream_t s) {
     double *r = g->kv[0], *rh = g->kv[1];
+    if (g->ng > 0)
+        hipLaunchKernelGGL(k_ghost_rows<true>, dim3((unsigned)((g->ng + GHOST_ROW_G - 1) / GHOST_ROW_G)),
+                           dim3(GHOST_ROW_NT), 0, s, ghost_view(g), fine64(g), x, r, g->g_scale, (const double *)nullptr,
+                           (double *)nullptr, (double *)nullptr);
     // fluid rows: the z-marching operator pass in its residual form, with sum V r per workgroup
     int nparts = 0;
-    hipError_t e = launch_apply_fluid(fine64(g), x, r, f, nullptr, 3, g->partials, &nparts, s);
+    hipError_t e = launch_apply_fluid(fine64(g), x, r, f, MeanParts{nullptr, 0, nullptr}, 3, g->partials, &nparts, s);
     if (e != hipSuccess) return e;
-    if (g->ng > 0)
-        hipLaunchKernelGGL(k_apply_ghost, dim3(nblk(g->ng)), dim3(256), 0, s, ghost_view(g), x, r, g->g_scale, g->nx,
-                           g->ny, g->nz, g->type, 1, (const double *)nullptr, (double *)nullptr);
-    hipLaunchKernelGGL(k_krylov_finalize, dim3(1), dim3(256), 0, s, g->partials, nparts, 1, g->sc, (int)K_MU, 0.0);
-    hipLaunchKernelGGL(k_project, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, g->type, g->N, r, rh, g->sc, 2, g->partials);
-    hipLaunchKernelGGL(k_krylov_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, 2, g->sc, (int)K_INIT,
-                       0.0);
+    hipLaunchKernelGGL(k_krylov_finalize<1>, dim3(1), dim3(FIN_NT), 0, s, g->partials, nparts, g->sc, (int)K_MU, 0.0);
+    const int nb = red_blocks(g->N, 2 * NORM_NT);
+    hipLaunchKernelGGL(k_project, dim3(nb), dim3(NORM_NT), 0, s, g->type, g->N, r, rh, g->sc, 2, g->partials);
+    hipLaunchKernelGGL(k_krylov_finalize<2>, dim3(1), dim3(FIN_NT), 0, s, g->partials, nb, g->sc, (int)K_INIT, 0.0);
     return hipGetLastError();
 }
 
-// one BiCGStab step on x (kv: r, rh, pd, v, s, t, ya, yb, za, zb)
-hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s) {
+// one BiCGStab step on x (kv: r, rh, pd, v, s, t, ya, yb, za, zb); T: the preconditioner's type
+template <typename T>
+static hipError_t krylov_step_t(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s) {
     double *r = g->kv[0], *rh = g->kv[1], *pd = g->kv[2], *v = g->kv[3], *sv = g->kv[4], *t = g->kv[5];
     double *ya = g->kv[6], *yb = g->kv[7], *za = g->kv[8], *zb = g->kv[9];
-    const unsigned nbN = (unsigned)nblk(g->N);
     hipError_t e;
-    float *r32 = o->precision == IBM_MIXED ? g->r32 : nullptr;  // FP32 right-hand side of the mixed cycle
-    hipLaunchKernelGGL(k_p_update, dim3(nbN), dim3(256), 0, s, g->type, g->N, r, v, pd, g->sc, r32, first ? 1 : 0);
+    float *r32 = sizeof(T) == 4 ? g->r32 : nullptr;  // FP32 right-hand side of the mixed cycle
     double *y = nullptr, *z = nullptr;
-    if ((e = precondition(g, pd, ya, yb, &y, o, s)) != hipSuccess) return e;
+    T *e0 = precond_start<T>(g, ya, yb, o, s);
+    GhostStart<T> S = ghost_start<T>(g, e0);
+    const unsigned nb = (unsigned)(nblk(g->N) + S.blocks);
+    hipLaunchKernelGGL(k_p_update<T>, dim3(nb), dim3(256), 0, s, g->type, g->N, r, v, pd, g->sc, r32, first ? 1 : 0, S);
+    if ((e = precondition<T>(g, pd, e0, ya, yb, &y, o, s)) != hipSuccess) return e;
     if ((e = apply_projected(g, y, v, rh, 0, K_ALPHA, o->breakdown_tol, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_s_update, dim3(nbN), dim3(256), 0, s, g->type, g->N, r, v, sv, g->sc, r32);
-    if ((e = precondition(g, sv, za, zb, &z, o, s)) != hipSuccess) return e;
+    e0 = precond_start<T>(g, za, zb, o, s);
+    S = ghost_start<T>(g, e0);
+    hipLaunchKernelGGL(k_s_update<T>, dim3(nb), dim3(256), 0, s, g->type, g->N, r, v, sv, g->sc, r32, S);
+    if ((e = precondition<T>(g, sv, e0, za, zb, &z, o, s)) != hipSuccess) return e;
     if ((e = apply_projected(g, z, t, sv, 1, K_OMEGA, o->breakdown_tol, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_xr_update, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, g->type, g->N, x, y, z, sv, t, r, rh, g->sc,
+    const int nxr = red_blocks(g->N, 2 * NORM_NT);
+    hipLaunchKernelGGL(k_xr_update, dim3(nxr), dim3(NORM_NT), 0, s, g->type, g->N, x, y, z, sv, t, r, rh, g->sc,
                        g->partials);
-    hipLaunchKernelGGL(k_krylov_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, 3, g->sc, (int)K_RHO,
+    hipLaunchKernelGGL(k_krylov_finalize<3>, dim3(1), dim3(FIN_NT), 0, s, g->partials, nxr, g->sc, (int)K_RHO,
                        o->breakdown_tol);
     return hipGetLastError();
 }
 
+hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s) {
+    return o->precision == IBM_MIXED ? krylov_step_t<float>(g, x, o, first, s) : krylov_step_t<double>(g, x, o, first, s);
+}
+
 // restart the shadow residual after a breakdown: rh = r, rho = r.r, beta = 0
 hipError_t krylov_restart(ibm_grid *g, hipStream_t s) {
-    hipLaunchKernelGGL(k_project, dim3(RED_BLOCKS), dim3(NORM_NT), 0, s, g->type, g->N, g->kv[0], g->kv[1], g->sc, 3,
+    const int nb = red_blocks(g->N, 2 * NORM_NT);
+    hipLaunchKernelGGL(k_project, dim3(nb), dim3(NORM_NT), 0, s, g->type, g->N, g->kv[0], g->kv[1], g->sc, 3,
                        g->partials);
-    hipLaunchKernelGGL(k_krylov_finalize, dim3(1), dim3(256), 0, s, g->partials, RED_BLOCKS, 2, g->sc,
-                       (int)K_RESTART, 0.0);
+    hipLaunchKernelGGL(k_krylov_finalize<2>, dim3(1), dim3(FIN_NT), 0, s, g->partials, nb, g->sc, (int)K_RESTART, 0.0);
     return hipGetLastError();
 }
 
