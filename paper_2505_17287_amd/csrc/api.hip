@@ -15,6 +15,7 @@
 
 #include <rocprofiler-sdk-roctx/roctx.h>
 
+#include "device_util.hpp"
 #include "ibm_impl.hpp"
 #include "mesh_check.hpp"
 
@@ -152,6 +153,29 @@ void plan_levels(int nx, int ny, int nz, const double *xf, const double *yf, con
                 C.w[d][i] = C.f[d][i + 1] - C.f[d][i];
             }
         }
+        // tiles of the restriction: the coarse columns and planes whose first child lies in a window
+        // of finer ones
+        C.tx.clear();
+        for (int I = 0; I < C.n[0]; ++I)
+            while ((int)C.tx.size() * RM_FX <= C.cs[0][I]) C.tx.push_back({I, C.cs[0][I]});
+        C.tx.push_back({C.n[0], F.n[0]});
+        const int64_t slab = (int64_t)(C.tx.size() - 1) * ((C.n[1] + RM_W - 1) / RM_W);
+        const int64_t resident = (int64_t)RM_RESIDENT * device_cu_count();
+        int fz = 2;
+        int64_t best = INT64_MAX;
+        for (int z = 2; z <= RM_ZMAX; ++z) {
+            const int64_t rounds = (slab * ((F.n[2] + z - 1) / z) + resident - 1) / resident;
+            if (rounds * (z + RM_ZCOST) < best) {
+                best = rounds * (z + RM_ZCOST);
+                fz = z;
+            }
+        }
+        C.tz.clear();
+        for (int K = 0; K < C.n[2]; ++K) {
+            while ((int)C.tz.size() * fz <= C.cs[2][K]) C.tz.push_back({K, C.cs[2][K], 0});
+            C.tz.back().ends |= uint64_t(1) << (C.cs[2][K + 1] - 1 - C.tz.back().k0);
+        }
+        C.tz.push_back({C.n[2], F.n[2], 0});
         // side rule of the prolongation table (k_prolong_tab) on uniformly halved axes: fine i
         // takes I = i/2 and the coarse neighbour on the side of its centre
         bool sides = true;
@@ -175,6 +199,10 @@ ChildMap child_map(const LevelHost &C) {
         M.halved[d] = C.halved[d];
         M.same[d] = C.same[d];
     }
+    M.tx = C.tx_d;
+    M.ntx = (int)C.tx.size() - 1;
+    M.tz = C.tz_d;
+    M.ntz = (int)C.tz.size() - 1;
     return M;
 }
 
@@ -268,6 +296,8 @@ size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int6
                 L.c64[d] = P.take<double>(2 * L.n[d] + 1);  // centres, then the faces
             }
             for (int d = 0; d < 3; ++d) L.cs_d[d] = P.take<int>(L.n[d] + 1);
+            L.tx_d = P.take<XTile>(lev[l - 1].n[0] / RM_FX + 2);
+            L.tz_d = P.take<ZTile>(lev[l - 1].n[2] + 2);
             L.e64 = P.take<double>(NC);
             L.R64 = P.take<double>(NC);
             L.e32 = P.take<float>(NC);
@@ -360,7 +390,7 @@ size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_ma
     size_t b = layout(nullptr, P, nx, ny, nz, nv_max, nt_max, max_ghosts, prec, lev, 1);
     const int64_t N = (int64_t)nx * ny * nz;
     const int64_t axes = (int64_t)nx + ny + nz;
-    return b + (size_t)N * 61 + (size_t)MAX_LEVELS * (size_t)(axes * 64 + 32 * 256) + (1 << 20);
+    return b + (size_t)N * 61 + (size_t)MAX_LEVELS * (size_t)(axes * 80 + 40 * 256) + (1 << 20);
 }
 
 size_t ibm_grid_workspace_bytes(const ibm_grid *gc, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,
@@ -416,6 +446,14 @@ ibm_status ibm_bind_workspace(ibm_grid *g, void *device_ptr, size_t bytes, int64
             HIP_TRY(hipMemcpyAsync(g->lev[l].cs_d[d], g->lev[l].cs[d].data(), sizeof(int) * (g->lev[l].n[d] + 1),
                                    hipMemcpyHostToDevice, s),
                     "upload child maps");
+            if (d == 0) {
+                HIP_TRY(hipMemcpyAsync(g->lev[l].tx_d, g->lev[l].tx.data(), sizeof(XTile) * g->lev[l].tx.size(),
+                                       hipMemcpyHostToDevice, s),
+                        "upload x tiles");
+                HIP_TRY(hipMemcpyAsync(g->lev[l].tz_d, g->lev[l].tz.data(), sizeof(ZTile) * g->lev[l].tz.size(),
+                                       hipMemcpyHostToDevice, s),
+                        "upload z tiles");
+            }
         }
     HIP_TRY(hipMemsetAsync(g->sc, 0, sizeof(Scalars), s), "memset scalars");
     HIP_TRY(launch_metrics(g, s), "metrics");

@@ -35,6 +35,35 @@ __device__ __forceinline__ long long wave_sum_ll(long long v) {
     return v;
 }
 
+// The value of the lane below (above) in the wave, by a DPP move: no trip through the LDS unit,
+// whose counter is shared with the scalar loads, so a wait for a shuffle waits for those too.
+// For lane 0 (63): 0.  Every lane has to be active.
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_move(double v) {
+    const int2 a = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, int2{__builtin_amdgcn_update_dpp(0, a.x, CTRL, 0xf, 0xf, true),
+                                           __builtin_amdgcn_update_dpp(0, a.y, CTRL, 0xf, 0xf, true)});
+}
+template <typename T>
+__device__ __forceinline__ T lane_below(T v) {
+    return lane_move<0x138>(v);  // wave_shr:1
+}
+template <typename T>
+__device__ __forceinline__ T lane_above(T v) {
+    return lane_move<0x130>(v);  // wave_shl:1
+}
+// 0 in a vector register the compiler does not know the value of: an index with it makes a
+// uniform load a vector load, which is counted in order with the others
+__device__ __forceinline__ int vector_zero() {
+    int z;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+    return z;
+}
+
 // Sum over a block of NT threads (1D flat thread index `tid`); result valid in thread 0.
 // Fixed combination order -> bitwise reproducible for a fixed launch shape.
 template <int NT>

@@ -178,9 +178,9 @@ __global__ void __launch_bounds__(ZM_NT)
 }
 
 // Residual and restriction for any child map (cells merged on some axes only where they are
-// narrow).  A tile is RM_CX coarse columns x RM_W coarse rows x a chunk of coarse planes;
+// narrow).  A tile is a window of coarse columns x RM_W coarse rows x a chunk of coarse planes;
 // each wave owns one coarse row J (one or two fine rows), and lane l the fine column
-// cs_x[I0] + l (the children of RM_CX coarse columns span at most 64 columns).  The lane
+// cs_x[I0] - 1 + l, so the window's children have both x neighbours in the wave.  The lane
 // marches up the fine planes with both fine rows in registers (the planes below and above
 // in registers, in-plane neighbours through the caches, the plane k+1 loads issued before
 // plane k is computed), forms the residual (f - lambda) - S p of each fine cell with the
@@ -188,17 +188,19 @@ __global__ void __launch_bounds__(ZM_NT)
 // running sum over the rows and fine planes of the current coarse plane.  When the coarse
 // plane is complete, lane I - I0 gathers the sums of the one or two lanes holding the
 // children of coarse column I (the same sum as the oracle's, in another order).  No data
-// crosses waves inside the march.  Workgroups take tiles in a grid-stride loop, in the
+// crosses waves inside the march.  All loads of a plane are vector loads and the x neighbours
+// DPP moves: with the edge columns and z metrics as scalar loads and the neighbours as shuffles,
+// every shuffle waited for the scalar loads of the plane ahead.  With that and the tiles'
+// balance: 256 x 128 x 128 wing 40 -> 25.5 us, 128^3 22.6 -> 17.7, 384^3 343 -> 315; there the
+// coarse levels' pass 128.6 -> 103.5 us, on the wing's first level 33.8 -> 20.6.  Workgroups take tiles in a grid-stride loop, in the
 // XCD-aware order (a contiguous range of tiles per XCD and round).
-constexpr int RM_TILES_PER_CU = 16, RM_KMIN = 1;  // tiles per CU, least coarse planes per tile
 
 template <typename T>
 struct RMPlane {
     T pp0, pp1;  // p at plane k+1 above the lane's column, first and second row
     T ylo, yhi;  // p at plane k in the rows below the first and above the last
     T f0, f1;
-    T em0, ep0, em1, ep1;  // p at plane k just outside the tile's columns, both rows (uniform)
-    T azm, azp, wz;        // z metrics of plane k (uniform)
+    T azm, azp, wz;  // z metrics of plane k (uniform)
     uint8_t t0, t1;
 };
 
@@ -207,24 +209,18 @@ struct RMPlane {
 template <typename T, bool TWO>
 __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__restrict__ p,
                                                    const T *__restrict__ f, T lam, const Coarse<T> &C,
-                                                   const ChildMap &M, int I0, int I1, int J, int K0, int K1,
+                                                   const ChildMap &M, const XTile &X, const XTile &Xe, int J, const ZTile &Z, int k1,
                                                    int lane) {
     const int nx = F.nx, ny = F.ny, nz = F.nz;
     const int64_t plane = (int64_t)nx * ny;
-    const int fx0 = M.cs[0][I0], fx1 = M.cs[0][I1];
-    const int i = fx0 + lane;
-    const bool inx = i < fx1;
-    const int ic = min(i, nx - 1);
+    const int I0 = X.I0, I1 = Xe.I0, fx0 = X.i0, fx1 = Xe.i0, k0 = Z.k0;
+    const int i = fx0 - 1 + lane, zero = vector_zero();
+    const bool inx = lane > 0 && i < fx1;
+    const int ic = min(max(i, 0), nx - 1);
     const int ja = M.cs[1][J], jb = TWO ? ja + 1 : ja;
     const int64_t o0 = (int64_t)ja * nx + ic, o1 = (int64_t)jb * nx + ic;
     const int64_t olo = (int64_t)max(ja - 1, 0) * nx + ic, ohi = (int64_t)min(jb + 1, ny - 1) * nx + ic;
     const bool hx0 = ic > 0, hx1 = ic < nx - 1;
-    // the x neighbours come from the adjacent lanes (every lane holds its column, or the
-    // last column where it lies past the grid, whose value then meets a wall); lanes 0 and
-    // 63 take the columns just outside the tile from the edge loads.  The shuffles run in
-    // every lane before the edge lanes pick their loaded value: a shuffle evaluated only in
-    // some lanes would read the others' registers while they are switched off.
-    const int64_t eom = (int64_t)ja * nx + max(fx0 - 1, 0), eop = (int64_t)ja * nx + min(fx0 + 64, nx - 1);
     const T axm = F.axm[ic], axp = F.axp[ic];
     const T aym0 = F.aym[ja], ayp0 = F.ayp[ja], aym1 = F.aym[jb], ayp1 = F.ayp[jb];
     const bool hy00 = ja > 0, hy10 = ja < ny - 1, hy01 = jb > 0, hy11 = jb < ny - 1;
@@ -232,35 +228,30 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
     // the owner lane of coarse column I0 + lane: where its children sit among the lanes
     const bool own = lane < I1 - I0;
     const int Io = min(I0 + lane, I1);  // every lane reads inside the map
-    const int ca = own ? M.cs[0][Io] - fx0 : 0;
+    const int ca = own ? M.cs[0][Io] - fx0 + 1 : 0;
     const bool pair = own && M.cs[0][min(Io + 1, I1)] - M.cs[0][Io] == 2;
     const int cb = min(ca + 1, 63);
-    const int k0 = M.cs[2][K0], k1 = M.cs[2][K1];
     auto ld = [=](int k) -> RMPlane<T> {
         RMPlane<T> d;
         const int kk = min(k, nz - 1);
         const int64_t b = (int64_t)kk * plane;
         const int64_t up = (kk < nz - 1) ? plane : 0;
         d.pp0 = p[b + o0 + up];
-        d.em0 = p[b + eom];
-        d.ep0 = p[b + eop];
         d.ylo = p[b + olo];
         d.yhi = p[b + ohi];
         d.f0 = f[b + o0];
         d.t0 = F.type[b + o0];
         if constexpr (TWO) {
             d.pp1 = p[b + o1 + up];
-            d.em1 = p[b + eom + nx];
-            d.ep1 = p[b + eop + nx];
             d.f1 = f[b + o1];
             d.t1 = F.type[b + o1];
         } else {
-            d.pp1 = d.em1 = d.ep1 = d.f1 = T(0);
+            d.pp1 = d.f1 = T(0);
             d.t1 = 0;
         }
-        d.azm = F.azm[kk];
-        d.azp = F.azp[kk];
-        d.wz = F.wz[kk];
+        d.azm = F.azm[kk + zero];
+        d.azp = F.azp[kk + zero];
+        d.wz = F.wz[kk + zero];
         return d;
     };
     T pm0 = (k0 > 0) ? p[(int64_t)(k0 - 1) * plane + o0] : T(0);
@@ -272,29 +263,28 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
     }
     T acc = 0;
     double psum = 0.0;
-    int K = K0, kend = M.cs[2][K0 + 1];  // the coarse plane and its end
-    // one fine plane; the loop is unrolled by two so the two plane slots change roles by name
+    int K = Z.K0;
+    // One fine plane; the loop is unrolled by two so the two plane slots change roles by name, and
+    // a plane past the chunk is masked: a break between the two made the compiler move the slots
+    // in flight between registers, waiting for the plane ahead.
 #define IBM_RMAP_PLANE(D, kk)                                                                                     \
     {                                                                                                              \
         const int k_ = (kk);                                                                                       \
+        const bool in_ = inx && k_ < k1;                                                                           \
         T num, diag;                                                                                               \
-        const T su0_ = __shfl_up(pc0, 1, 64), sd0_ = __shfl_down(pc0, 1, 64); /* in every lane */               \
-        const T xm0_ = (lane == 0) ? (D).em0 : su0_;                                                               \
-        const T xp0_ = (lane == 63) ? (D).ep0 : sd0_;                                                              \
+        const T xm0_ = lane_below(pc0), xp0_ = lane_above(pc0);                                                    \
         zm_stencil<T>(axm, axp, aym0, ayp0, (D).azm, (D).azp, hx0, hx1, hy00, hy10, k_ > 0, k_ < nz - 1, xm0_,     \
                       xp0_, (D).ylo, TWO ? pc1 : (D).yhi, pm0, (D).pp0, num, diag);                                 \
         const T r0 = ((D).f0 - lam) - (num - diag * pc0);                                                         \
-        acc += (inx && (D).t0 == T_FLUID) ? (vxy0 * (D).wz) * r0 : T(0);                                           \
+        acc += (in_ && (D).t0 == T_FLUID) ? (vxy0 * (D).wz) * r0 : T(0);                                           \
         if constexpr (TWO) {                                                                                       \
-            const T su1_ = __shfl_up(pc1, 1, 64), sd1_ = __shfl_down(pc1, 1, 64);                                 \
-            const T xm1_ = (lane == 0) ? (D).em1 : su1_;                                                           \
-            const T xp1_ = (lane == 63) ? (D).ep1 : sd1_;                                                          \
+            const T xm1_ = lane_below(pc1), xp1_ = lane_above(pc1);                                                \
             zm_stencil<T>(axm, axp, aym1, ayp1, (D).azm, (D).azp, hx0, hx1, hy01, hy11, k_ > 0, k_ < nz - 1,       \
                           xm1_, xp1_, pc0, (D).yhi, pm1, (D).pp1, num, diag);                                        \
             const T r1 = ((D).f1 - lam) - (num - diag * pc1);                                                     \
-            acc += (inx && (D).t1 == T_FLUID) ? (vxy1 * (D).wz) * r1 : T(0);                                       \
+            acc += (in_ && (D).t1 == T_FLUID) ? (vxy1 * (D).wz) * r1 : T(0);                                       \
         }                                                                                                          \
-        if (k_ + 1 == kend) { /* the coarse plane K is complete */                                                \
+        if ((Z.ends >> (k_ - k0)) & 1) { /* the coarse plane K is complete */                                       \
             T s = __shfl(acc, ca, 64);                                                                             \
             const T s2 = __shfl(acc, cb, 64);                                                                      \
             if (pair) s = s + s2;                                                                                  \
@@ -306,7 +296,6 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
             }                                                                                                      \
             acc = T(0);                                                                                            \
             ++K;                                                                                                   \
-            kend = M.cs[2][min(K + 1, K1)];                                                                        \
         }                                                                                                          \
         pm0 = pc0;                                                                                                 \
         pc0 = (D).pp0;                                                                                             \
@@ -314,10 +303,9 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
         pc1 = (D).pp1;                                                                                             \
     }
     RMPlane<T> qa = ld(k0), qb;
-    for (int k = k0; k < k1; k += 2) {
+    for (int k = k0; k < k1; k += 2) {  // no way out in between: see above
         qb = ld(k + 1);
         IBM_RMAP_PLANE(qa, k);
-        if (k + 1 >= k1) break;
         qa = ld(k + 2);
         IBM_RMAP_PLANE(qb, k + 1);
     }
@@ -326,7 +314,7 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
 }
 
 template <typename T>
-__global__ void __launch_bounds__(RM_NT)
+__global__ void __launch_bounds__(RM_NT, 4)
     k_restrict0_map(Fine<T> F, const T *__restrict__ p, const T *__restrict__ f, const T *__restrict__ lamp,
                     Coarse<T> C, ChildMap M, RowTiles t, double *partials) {
     const int lane = (int)threadIdx.x & 63;
@@ -341,13 +329,14 @@ __global__ void __launch_bounds__(RM_NT)
         const int tyi = q % t.nty;
         const int chunk = q / t.nty;
         const int J = tyi * RM_W + wave;
-        if (J >= C.n[1]) continue;
-        const int I0 = txi * RM_CX, I1 = min(I0 + RM_CX, C.n[0]);
-        const int K0 = chunk * t.kc, K1 = min(C.n[2], K0 + t.kc);
+        const XTile X = M.tx[txi], Xe = M.tx[txi + 1];
+        const ZTile Z = M.tz[chunk];
+        const int k1 = M.tz[chunk + 1].k0;
+        if (J >= C.n[1] || X.I0 >= Xe.I0 || Z.k0 >= k1) continue;
         if (M.cs[1][J + 1] - M.cs[1][J] == 2)
-            psum += restrict_map_row<T, true>(F, p, f, lam, C, M, I0, I1, J, K0, K1, lane);
+            psum += restrict_map_row<T, true>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
         else
-            psum += restrict_map_row<T, false>(F, p, f, lam, C, M, I0, I1, J, K0, K1, lane);
+            psum += restrict_map_row<T, false>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
     }
     __shared__ double sh[RM_NT / 64];
     const double tot = block_sum<RM_NT>(psum, sh, threadIdx.x);
@@ -1070,7 +1059,7 @@ hipError_t launch_restrict0(const Fine<T> &F, const T *p, const T *f, const T *l
         // some axis merges only part of its cells: the generic pass
         RowTiles t;
         int grid;
-        const hipError_t e = row_tiles(C.n, RM_TILES_PER_CU, RM_KMIN, zmarch_partials_max(F.nx, F.ny, F.nz), &t, &grid);
+        const hipError_t e = row_tiles(M, C.n, zmarch_partials_max(F.nx, F.ny, F.nz), &t, &grid);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_restrict0_map<T>, dim3(grid), dim3(RM_NT), 0, s, F, p, f, lam, C, M, t, partials);
         *nparts = grid;
@@ -1138,15 +1127,10 @@ hipError_t launch_jacobi0(const Fine<double> &F, const double *y, const double *
     return hipGetLastError();
 }
 
-hipError_t row_tiles(const int cn[3], int per_cu, int kmin, int64_t cap, RowTiles *t, int *grid) {
-    t->ntx = (cn[0] + RM_CX - 1) / RM_CX;
+hipError_t row_tiles(const ChildMap &M, const int cn[3], int64_t cap, RowTiles *t, int *grid) {
+    t->ntx = M.ntx;
     t->nty = (cn[1] + RM_W - 1) / RM_W;
-    const int64_t per_slab = (int64_t)t->ntx * t->nty;
-    const int64_t want = (int64_t)per_cu * device_cu_count();
-    int nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(want / per_slab, cn[2] / std::max(1, kmin)));
-    t->kc = (cn[2] + nchunk - 1) / nchunk;
-    nchunk = (cn[2] + t->kc - 1) / t->kc;
-    const int64_t ntiles = per_slab * nchunk;
+    const int64_t ntiles = (int64_t)t->ntx * t->nty * M.ntz;
     if (ntiles > INT32_MAX) return hipErrorInvalidValue;
     t->ntiles = (int)ntiles;
     cap = std::max<int64_t>(8, cap / 8 * 8);

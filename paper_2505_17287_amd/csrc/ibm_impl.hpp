@@ -109,6 +109,17 @@ struct ChildMap {
     const int *cs[3];
     int halved[3];  // 1: uniform halving along d
     int same[3];    // 1: nothing merged along d (cs[I] = I)
+    const struct XTile *tx;  // x and z tiles of the row-wise restrictions, one more at the end
+    const struct ZTile *tz;
+    int ntx, ntz;
+};
+struct XTile {
+    int I0, i0;  // first coarse column and its first child
+};
+struct ZTile {
+    int K0, k0;     // first coarse plane and its first child
+    uint64_t ends;  // bit k: finer plane k0 + k is the last of a coarse plane.  (A march that looks the
+                    // next end up as it goes waits for that load, and so for the plane loads before it.)
 };
 
 // z-march passes of level 0 (finepass.hip).  The reductions write one partial per
@@ -134,16 +145,26 @@ hipError_t launch_jacobi0(const Fine<double> &F, const double *y, const double *
                           hipStream_t s);
 int64_t zmarch_partials_max(int nx, int ny, int nz);
 
-// Tiling of the row-wise restrictions (a wave per coarse row: RM_CX coarse columns, RM_W
-// coarse rows and kc coarse planes per workgroup of 64 RM_W threads), taken tile by tile
-// in a grid-stride loop.  row_tiles picks the z chunks for about per_cu tiles per CU with
-// at least kmin coarse planes each (fewer when the level has fewer) and returns the grid:
-// a multiple of 8, at most the tile count rounded up and at most cap (a multiple of 8).
-constexpr int RM_CX = 32, RM_W = 4, RM_NT = 64 * RM_W;
+// Tiling of the row-wise restrictions: a workgroup of 64 RM_W threads takes, a wave per coarse row,
+// the coarse columns that start in a window of RM_FX finer ones, RM_W coarse rows and the coarse
+// planes that start in a window of finer ones, tile by tile in a grid-stride loop; the grid is a
+// multiple of 8, at most the tile count rounded up and at most cap (a multiple of 8).
+// A window's coarse columns span at most RM_FX + 1 finer ones, which with one more on either side
+// fill a wave however few of them are merged (32 coarse columns left 24 of 64 lanes idle on
+// a level of 160 x 100 x 99 cells).
+constexpr int RM_FX = 61, RM_W = 4, RM_NT = 64 * RM_W;
+// The z tiles are windows of finer planes too, so that a tile's work does not depend on how many
+// planes are merged where it lies: each XCD takes a contiguous range of tiles, and with tiles of
+// equal coarse planes those in the middle of a stretched grid had the most (384^3: 343 us, by
+// windows 317).
+// Their size minimises rounds of resident workgroups x (planes + RM_ZCOST), a tile's two planes
+// shared with its neighbours and its start counting as RM_ZCOST planes: a round that is not full
+// costs as much as one that is (wing, 2.3 rounds 33 us, one of longer tiles 25.5).
+constexpr int RM_RESIDENT = 4, RM_ZCOST = 3, RM_ZMAX = 60;  // workgroups per CU; ZTile::ends has 64 bits
 struct RowTiles {
-    int ntx, nty, kc, ntiles;
+    int ntx, nty, ntiles;
 };
-hipError_t row_tiles(const int cn[3], int per_cu, int kmin, int64_t cap, RowTiles *t, int *grid);
+hipError_t row_tiles(const ChildMap &M, const int cn[3], int64_t cap, RowTiles *t, int *grid);
 
 struct GhostView {
     int64_t ng;
@@ -194,6 +215,10 @@ struct LevelHost {
     std::vector<double> f[3], c[3], w[3];
     std::vector<int> cs[3];  // children starts in the next finer level (levels >= 1)
     int *cs_d[3] = {nullptr, nullptr, nullptr};  // device copy of cs
+    std::vector<XTile> tx;  // tiles of the restriction into this level (see ChildMap)
+    std::vector<ZTile> tz;
+    XTile *tx_d = nullptr;
+    ZTile *tz_d = nullptr;
     int64_t ncell() const { return (int64_t)n[0] * n[1] * n[2]; }
     // device
     uint8_t *active = nullptr;

@@ -263,52 +263,46 @@ __device__ __forceinline__ void coarse_stencil(const Coarse<T> &L, const T *__re
 
 // level l -> l+1 (l >= 1): R_{l+1}(C) = sum over active children of r, r = (R - V mu) - S e, for
 // any child map, row-wise (the tiling of the level-0 restriction k_restrict0_map):
-// a wave owns one coarse row J (one or two finer rows) of a tile of RM_CX coarse columns, a
+// a wave owns one coarse row J (one or two finer rows) of a window of coarse columns, a
 // lane one finer column, and the lane marches up the finer planes with both rows in
-// registers; the x neighbours and the high x face come from the adjacent lanes (lanes 0 and
-// 63 from edge loads), the high y face of the first row is the second row's low face, the
-// high z face the next plane's low face, loaded with that plane.  Per cell the operations
+// registers; the x neighbours and the high x face come from the adjacent lanes
+// (the columns beside the window are loaded too), the high y face of the first row is the second
+// row's low face, the high z face the next plane's low face, loaded with that plane.  Loads and
+// lane moves as in the level-0 pass, for the same reason.  Per cell the operations
 // are those of coarse_stencil; each lane sums its active cells over the rows and planes of
 // the current coarse plane, and when that plane is complete lane I - I0 adds the sums of the
 // one or two lanes holding the children of coarse column I.
-// Tiles down to one coarse plane: the smaller levels are bound by the serial finer planes of a
-// tile.  (A thread per coarse cell took 16 us on levels of 2 x 10^4 to 10^5 cells, and at least
-// four planes per tile 12 to 20 us on the larger ones: a wing solve 17.47 ms, 17.06 with this.)
-constexpr int RC_TILES_PER_CU = 8, RC_KMIN = 1;
 
 template <typename T>
 struct RCPlane {
     T en0, en1, tzn0, tzn1;  // e and the low z face of plane k+1
     T r0, r1, tx0, tx1, ty0, ty1;
     T ylo, yhi, tyh;         // e below the first and above the last row, the low y face above the last
-    T eL0, eR0, eL1, eR1, txR0, txR1;  // e just outside the tile's columns, the low x face right of it
     T w2;
     uint8_t a0, a1;
 };
 
 template <typename T, bool TWO>
 __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coarse<T> &C, const ChildMap &M, T mu,
-                                                  int I0, int I1, int J, int K0, int K1, int lane) {
+                                                  const XTile &X, const XTile &Xe, int J, const ZTile &Z, int k1, int lane) {
     const int nx = L.n[0], ny = L.n[1], nz = L.n[2];
     const int64_t plane = (int64_t)nx * ny;
-    const int fx0 = M.cs[0][I0], fx1 = M.cs[0][I1];
-    const int i = fx0 + lane;
-    const bool inx = i < fx1;
-    const int ic = min(i, nx - 1);
+    const int I0 = X.I0, I1 = Xe.I0, fx0 = X.i0, fx1 = Xe.i0, k0 = Z.k0;
+    const int i = fx0 - 1 + lane, zero = vector_zero();
+    const bool inx = lane > 0 && i < fx1;
+    const int ic = min(max(i, 0), nx - 1);
     const int ja = M.cs[1][J], jb = TWO ? ja + 1 : ja;
     const int64_t o0 = (int64_t)ja * nx + ic, o1 = (int64_t)jb * nx + ic;
     const int64_t olo = (int64_t)max(ja - 1, 0) * nx + ic, ohi = (int64_t)min(jb + 1, ny - 1) * nx + ic;
     const bool hx0 = ic > 0, hx1 = ic < nx - 1;
     const bool hy00 = ja > 0, hy10 = ja < ny - 1, hy01 = jb > 0, hy11 = jb < ny - 1;
-    const int64_t eom = (int64_t)ja * nx + max(fx0 - 1, 0), eop = (int64_t)ja * nx + min(fx0 + 64, nx - 1);
     const T w0 = L.w[0][ic];
     const T vxy0 = w0 * L.w[1][ja], vxy1 = w0 * L.w[1][jb];
     const bool own = lane < I1 - I0;
     const int Io = min(I0 + lane, I1);
-    const int ca = own ? M.cs[0][Io] - fx0 : 0;
+    const int ca = own ? M.cs[0][Io] - fx0 + 1 : 0;
     const bool pair = own && M.cs[0][min(Io + 1, I1)] - M.cs[0][Io] == 2;
     const int cb = min(ca + 1, 63);
-    const int k0 = M.cs[2][K0], k1 = M.cs[2][K1];
     const T *__restrict__ pe = L.e;
     const T *__restrict__ pr = L.R;
     const T *__restrict__ px = L.Tl[0];
@@ -327,9 +321,6 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
         d.ylo = pe[b + olo];
         d.yhi = pe[b + ohi];
         d.tyh = py[b + ohi];
-        d.eL0 = pe[b + eom];
-        d.eR0 = pe[b + eop];
-        d.txR0 = px[b + eop];
         if constexpr (TWO) {
             d.en1 = pe[bn + o1];
             d.tzn1 = pz[bn + o1];
@@ -337,14 +328,11 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
             d.tx1 = px[b + o1];
             d.ty1 = py[b + o1];
             d.a1 = L.active[b + o1];
-            d.eL1 = pe[b + eom + nx];
-            d.eR1 = pe[b + eop + nx];
-            d.txR1 = px[b + eop + nx];
         } else {
-            d.en1 = d.tzn1 = d.r1 = d.tx1 = d.ty1 = d.eL1 = d.eR1 = d.txR1 = T(0);
+            d.en1 = d.tzn1 = d.r1 = d.tx1 = d.ty1 = T(0);
             d.a1 = 0;
         }
-        d.w2 = L.w[2][kk];
+        d.w2 = L.w[2][kk + zero];
         return d;
     };
     T em0 = (k0 > 0) ? pe[(int64_t)(k0 - 1) * plane + o0] : T(0);
@@ -357,7 +345,7 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
     }
     T acc = 0;
     double psum = 0.0;
-    int K = K0, kend = M.cs[2][K0 + 1];
+    int K = Z.K0;
     // one cell of plane k: coarse_stencil's operations, then the residual
 #define IBM_RC_CELL(TXM, TXP, TYM, TYP, TZM, TZP, XM, XP, YM, YP, ZM, ZP, EC, HY0, HY1, RV, VXY, W2, ACT)      \
     {                                                                                                          \
@@ -376,25 +364,22 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
         d_ = d_ + tzp_;                                                                                        \
         const T vol_ = (VXY) * (W2);                                                                           \
         const T rc_ = ((RV) - vol_ * mu) - (s_ - d_ * (EC));                                                   \
-        acc += (inx && (ACT)) ? rc_ : T(0);                                                                    \
+        acc += (in_ && (ACT)) ? rc_ : T(0);                                                                    \
     }
 #define IBM_RC_PLANE(D, kk)                                                                                    \
     {                                                                                                          \
         const int k_ = (kk);                                                                                   \
-        const bool hz0_ = k_ > 0, hz1_ = k_ < nz - 1;                                                          \
-        /* shuffles in every lane; the edge lanes then pick their loaded values */                             \
-        const T su0_ = __shfl_up(ec0, 1, 64), sd0_ = __shfl_down(ec0, 1, 64), st0_ = __shfl_down((D).tx0, 1, 64); \
-        IBM_RC_CELL((D).tx0, lane == 63 ? (D).txR0 : st0_, (D).ty0, TWO ? (D).ty1 : (D).tyh, tzc0, (D).tzn0,     \
-                    lane == 0 ? (D).eL0 : su0_, lane == 63 ? (D).eR0 : sd0_, (D).ylo, TWO ? ec1 : (D).yhi, em0,  \
-                    (D).en0, ec0, hy00, hy10, (D).r0, vxy0, (D).w2, (D).a0 != 0);                              \
+        const bool hz0_ = k_ > 0, hz1_ = k_ < nz - 1, in_ = inx && k_ < k1;                                    \
+        /* in every lane, not inside the selections below */                                                   \
+        const T su0_ = lane_below(ec0), sd0_ = lane_above(ec0), st0_ = lane_above((D).tx0);                    \
+        IBM_RC_CELL((D).tx0, st0_, (D).ty0, TWO ? (D).ty1 : (D).tyh, tzc0, (D).tzn0, su0_, sd0_, (D).ylo,      \
+                    TWO ? ec1 : (D).yhi, em0, (D).en0, ec0, hy00, hy10, (D).r0, vxy0, (D).w2, (D).a0 != 0);    \
         if constexpr (TWO) {                                                                                   \
-            const T su1_ = __shfl_up(ec1, 1, 64), sd1_ = __shfl_down(ec1, 1, 64),                              \
-                    st1_ = __shfl_down((D).tx1, 1, 64);                                                        \
-            IBM_RC_CELL((D).tx1, lane == 63 ? (D).txR1 : st1_, (D).ty1, (D).tyh, tzc1, (D).tzn1,               \
-                        lane == 0 ? (D).eL1 : su1_, lane == 63 ? (D).eR1 : sd1_, ec0, (D).yhi, em1, (D).en1, ec1, \
-                        hy01, hy11, (D).r1, vxy1, (D).w2, (D).a1 != 0);                                        \
+            const T su1_ = lane_below(ec1), sd1_ = lane_above(ec1), st1_ = lane_above((D).tx1);                \
+            IBM_RC_CELL((D).tx1, st1_, (D).ty1, (D).tyh, tzc1, (D).tzn1, su1_, sd1_, ec0, (D).yhi, em1,        \
+                        (D).en1, ec1, hy01, hy11, (D).r1, vxy1, (D).w2, (D).a1 != 0);                          \
         }                                                                                                      \
-        if (k_ + 1 == kend) { /* the coarse plane K is complete */                                            \
+        if ((Z.ends >> (k_ - k0)) & 1) { /* the coarse plane K is complete */                                   \
             T s = __shfl(acc, ca, 64);                                                                         \
             const T s2 = __shfl(acc, cb, 64);                                                                  \
             if (pair) s = s + s2;                                                                              \
@@ -406,7 +391,6 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
             }                                                                                                  \
             acc = T(0);                                                                                        \
             ++K;                                                                                               \
-            kend = M.cs[2][min(K + 1, K1)];                                                                    \
         }                                                                                                      \
         em0 = ec0;                                                                                             \
         ec0 = (D).en0;                                                                                         \
@@ -416,10 +400,9 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
         tzc1 = (D).tzn1;                                                                                       \
     }
     RCPlane<T> qa = ld(k0), qb;
-    for (int k = k0; k < k1; k += 2) {
+    for (int k = k0; k < k1; k += 2) {  // no way out in between, as in the level-0 pass
         qb = ld(k + 1);
         IBM_RC_PLANE(qa, k);
-        if (k + 1 >= k1) break;
         qa = ld(k + 2);
         IBM_RC_PLANE(qb, k + 1);
     }
@@ -443,13 +426,14 @@ __global__ void __launch_bounds__(RM_NT)
         const int tyi = q % t.nty;
         const int chunk = q / t.nty;
         const int J = tyi * RM_W + wave;
-        if (J >= C.n[1]) continue;
-        const int I0 = txi * RM_CX, I1 = min(I0 + RM_CX, C.n[0]);
-        const int K0 = chunk * t.kc, K1 = min(C.n[2], K0 + t.kc);
+        const XTile X = M.tx[txi], Xe = M.tx[txi + 1];
+        const ZTile Z = M.tz[chunk];
+        const int k1 = M.tz[chunk + 1].k0;
+        if (J >= C.n[1] || X.I0 >= Xe.I0 || Z.k0 >= k1) continue;
         if (M.cs[1][J + 1] - M.cs[1][J] == 2)
-            psum += resrestrict_row<T, true>(L, C, M, mu, I0, I1, J, K0, K1, lane);
+            psum += resrestrict_row<T, true>(L, C, M, mu, X, Xe, J, Z, k1, lane);
         else
-            psum += resrestrict_row<T, false>(L, C, M, mu, I0, I1, J, K0, K1, lane);
+            psum += resrestrict_row<T, false>(L, C, M, mu, X, Xe, J, Z, k1, lane);
     }
     __shared__ double sh[RM_NT / 64];
     const double tot = block_sum<RM_NT>(psum, sh, threadIdx.x);
@@ -1230,8 +1214,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
                 hipLaunchKernelGGL(k_resrestrictC8<T>, dim3(nbc), dim3(256), 0, s, L, C, g->partials);
             } else {
                 RowTiles t;
-                if ((e = row_tiles(C.n, RC_TILES_PER_CU, RC_KMIN, zmarch_partials_max(g->nx, g->ny, g->nz), &t,
-                                   &nbc)) != hipSuccess)
+                if ((e = row_tiles(M, C.n, zmarch_partials_max(g->nx, g->ny, g->nz), &t, &nbc)) != hipSuccess)
                     return e;
                 hipLaunchKernelGGL(k_resrestrictC_map<T>, dim3(nbc), dim3(RM_NT), 0, s, L, C, M, t, g->partials);
             }
