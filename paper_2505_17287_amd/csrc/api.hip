@@ -729,9 +729,9 @@ static hipError_t enqueue_begin(ibm_grid *g, const double *rhs, double *p, const
     return hipMemcpyAsync(g->sc_host, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s);
 }
 
-// first: the solve's first cycle
+// first: the solve's first cycle; swept: its first sweep is done (FP64 V-cycles)
 static hipError_t enqueue_cycle(ibm_grid *g, const double *rhs, double *p, const ibm_solve_opts *o, int *cur,
-                                bool first, hipStream_t s) {
+                                bool first, hipStream_t s, bool swept = false) {
     if (krylov_method(o->method)) {
         *cur = 1;  // the Krylov iterate lives in the second buffer
         return krylov_step(g, g->p2, o, first, s);
@@ -739,9 +739,33 @@ static hipError_t enqueue_cycle(ibm_grid *g, const double *rhs, double *p, const
     double *bufs[2] = {p, g->p2};
     hipError_t e;
     if (o->precision == IBM_MIXED) e = vcycle_mixed(g, bufs, cur, rhs, s, o);
-    else e = vcycle_f64(g, bufs, cur, rhs, s, o);
+    else e = vcycle_f64(g, bufs, cur, rhs, s, o, swept);
     if (e != hipSuccess) return e;
     return norm_pass(g, bufs[*cur], rhs, s, o->precision == IBM_MIXED, false);
+}
+
+// The host looks at the residual after every step.  While the copy, the wait and the next launch
+// take their 15 to 20 us the device would be idle, so on the grids where that shows the beginning
+// of the next step is enqueued behind the copy: its direction, on small grids also the first
+// sweep.  It writes scratch alone and is dropped if the step turns out to be the last; it is left
+// out where the reduction so far says so, as it is with the sweeps timed one by one.
+constexpr int64_t AHEAD_SWEEP_CELLS = 1 << 20, AHEAD_CELLS = 1 << 23;
+static Ahead ahead_part(const ibm_grid *g) {
+    if (g->prof.on || g->N > AHEAD_CELLS) return AHEAD_NONE;
+    return g->N <= AHEAD_SWEEP_CELLS ? AHEAD_SWEEP : AHEAD_P;
+}
+// likely to be at the tolerance after one more step (residuals before and after the last one)
+static bool last_step_likely(const ibm_solve_opts *o, double before, double after) {
+    return o->fixed_cycles <= 0 && before > 0.0 && after * (after / before) <= o->rel_tol;
+}
+static hipError_t mark_read(ibm_grid *g, hipStream_t s) {
+    hipError_t e;
+    if (!g->ev_read && (e = hipEventCreateWithFlags(&g->ev_read, hipEventDisableTiming)) != hipSuccess) return e;
+    return hipEventRecord(g->ev_read, s);
+}
+static hipError_t read_scalars(ibm_grid *g, hipStream_t s) {
+    const hipError_t e = hipMemcpyAsync(g->sc_host, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s);
+    return e != hipSuccess ? e : mark_read(g, s);
 }
 
 // accumulate the timed smoother launches of the batch that just completed
@@ -769,9 +793,15 @@ static ibm_status solve_krylov(ibm_grid *g, const double *rhs, double *p, const 
     HIP_TRY(init_solution(g, p, x, o->use_initial_guess, s), "init");
     HIP_TRY(krylov_residual(g, rhs, x, s), "residual");
     Scalars *hs = g->sc_host;
-    HIP_TRY(hipMemcpyAsync(hs, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s), "read");
-    HIP_TRY(hipStreamSynchronize(s), "sync");
-    if (hs->bad) return fail(g, IBM_E_NUMERIC, "non-finite right-hand side or initial guess");
+    HIP_TRY(read_scalars(g, s), "read");
+    const Ahead part = ahead_part(g);
+    Ahead ahead = part;
+    if (part != AHEAD_NONE) HIP_TRY(krylov_ahead(g, o, true, part, s), "first direction");
+    HIP_TRY(hipEventSynchronize(g->ev_read), "sync");
+    if (hs->bad) {
+        HIP_TRY(hipStreamSynchronize(s), "sync");
+        return fail(g, IBM_E_NUMERIC, "non-finite right-hand side or initial guess");
+    }
     const double r0 = hs->norm;
     if (!(hs->ref > 0.0)) {
         double ref = r0;
@@ -783,15 +813,24 @@ static ibm_status solve_krylov(ibm_grid *g, const double *rhs, double *p, const 
     int it = 0, restarts = 0;
     double rel = hs->ref > 0.0 ? r0 / hs->ref : 0.0;
     bool have_true = true;  // the scalars describe the true residual of x
+    bool gauged = false;    // the gauge and ghost residual of x are enqueued
+    double before = -1.0;
+    auto finish = [&]() {
+        const hipError_t e = gauge_pass(g, x, p, s);
+        return e != hipSuccess ? e : ghost_residual_pass(g, p, s);
+    };
     if (hs->ref > 0.0 && (o->fixed_cycles > 0 || rel > o->rel_tol)) {
         const int nit = o->fixed_cycles > 0 ? o->fixed_cycles : o->max_cycles;
         for (it = 1; it <= nit; ++it) {
             Range step_range("bicgstab step");
-            HIP_TRY(krylov_step(g, x, o, it == 1, s), "bicgstab step");
-            HIP_TRY(hipMemcpyAsync(hs, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s), "read");
-            HIP_TRY(hipStreamSynchronize(s), "step sync");
+            HIP_TRY(krylov_step(g, x, o, it == 1, s, ahead), "bicgstab step");
+            HIP_TRY(read_scalars(g, s), "read");
+            ahead = it < nit && !last_step_likely(o, before, rel) ? part : AHEAD_NONE;
+            if (ahead != AHEAD_NONE) HIP_TRY(krylov_ahead(g, o, false, part, s), "next direction");
+            HIP_TRY(hipEventSynchronize(g->ev_read), "step sync");
             if (g->prof.on) prof_collect(g);
             have_true = false;
+            before = rel;
             rel = hs->rel;
             if (hs->bad || !std::isfinite(hs->norm) || hs->norm > 1e6 * std::max(r0, hs->ref)) {
                 status = IBM_E_NUMERIC;
@@ -805,13 +844,20 @@ static ibm_status solve_krylov(ibm_grid *g, const double *rhs, double *p, const 
                 continue;
             }
             if (rel <= o->rel_tol) {
-                // confirm with the true residual (this also restarts the recurrences)
+                // confirm with the true residual (this also restarts the recurrences); the result
+                // is enqueued behind it, as it is most likely confirmed
                 HIP_TRY(krylov_residual(g, rhs, x, s), "true residual");
-                HIP_TRY(hipMemcpyAsync(hs, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s), "read");
-                HIP_TRY(hipStreamSynchronize(s), "sync");
+                HIP_TRY(read_scalars(g, s), "read");
+                if (part != AHEAD_NONE) HIP_TRY(finish(), "gauge");
+                HIP_TRY(hipEventSynchronize(g->ev_read), "sync");
+                ahead = AHEAD_NONE;
                 have_true = true;
+                before = -1.0;
                 rel = hs->rel;
-                if (rel <= o->rel_tol) break;
+                if (rel <= o->rel_tol) {
+                    gauged = part != AHEAD_NONE;
+                    break;
+                }
             } else if (hs->brk) {
                 HIP_TRY(krylov_restart(g, s), "restart");
                 ++restarts;
@@ -822,12 +868,11 @@ static ibm_status solve_krylov(ibm_grid *g, const double *rhs, double *p, const 
     }
     if (!have_true && status != IBM_E_NUMERIC) {
         HIP_TRY(krylov_residual(g, rhs, x, s), "final residual");
-        HIP_TRY(hipMemcpyAsync(hs, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s), "read");
-        HIP_TRY(hipStreamSynchronize(s), "sync");
+        HIP_TRY(read_scalars(g, s), "read");
+        HIP_TRY(hipEventSynchronize(g->ev_read), "sync");
         rel = hs->rel;
     }
-    HIP_TRY(gauge_pass(g, x, p, s), "gauge");
-    HIP_TRY(ghost_residual_pass(g, p, s), "ghost residual");
+    if (!gauged) HIP_TRY(finish(), "gauge");
     if (sync_end) {
         HIP_TRY(hipMemcpyAsync(&hs->ghost_res, &g->sc->ghost_res, sizeof(double), hipMemcpyDeviceToHost, s), "read");
         HIP_TRY(hipStreamSynchronize(s), "gauge sync");
@@ -861,9 +906,19 @@ static ibm_status solve_core(ibm_grid *g, const double *rhs, double *p, const ib
     double t0 = now_s();
     HIP_TRY(hipSetDevice(g->device), "hipSetDevice");
     HIP_TRY(enqueue_begin(g, rhs, p, o, s), "solve begin");
-    HIP_TRY(hipStreamSynchronize(s), "solve sync");
+    HIP_TRY(mark_read(g, s), "read");
+    double *bufs[2] = {p, g->p2};
+    int cur = 1, next = 1;
+    // the next cycle's first sweep goes to the buffer that does not hold the iterate
+    const bool part = o->precision == IBM_FP64 && o->nu1 > 0 && ahead_part(g) == AHEAD_SWEEP;
+    bool swept = part;
+    if (swept) HIP_TRY(vcycle_ahead(g, bufs, &next, rhs, s), "first sweep");
+    HIP_TRY(hipEventSynchronize(g->ev_read), "solve sync");
     Scalars *hs = g->sc_host;
-    if (hs->bad) return fail(g, IBM_E_NUMERIC, "non-finite right-hand side or initial guess");
+    if (hs->bad) {
+        HIP_TRY(hipStreamSynchronize(s), "sync");
+        return fail(g, IBM_E_NUMERIC, "non-finite right-hand side or initial guess");
+    }
     double r0 = hs->norm;
     if (!(hs->ref > 0.0)) {
         // zero-mean-free right-hand side: measure against the initial residual
@@ -871,18 +926,21 @@ static ibm_status solve_core(ibm_grid *g, const double *rhs, double *p, const ib
         HIP_TRY(hipMemcpyAsync(&g->sc->ref, &ref, sizeof(double), hipMemcpyHostToDevice, s), "set ref");
         hs->ref = ref;
     }
-    int cur = 1;
-    double *bufs[2] = {p, g->p2};
     int cycles = 0;
     ibm_status status = IBM_OK;
-    double rel = hs->ref > 0.0 ? r0 / hs->ref : 0.0;
+    double before = -1.0, rel = hs->ref > 0.0 ? r0 / hs->ref : 0.0;
     if (hs->ref > 0.0) {
         const int ncyc = o->fixed_cycles > 0 ? o->fixed_cycles : o->max_cycles;
         for (cycles = 1; cycles <= ncyc; ++cycles) {
-            HIP_TRY(enqueue_cycle(g, rhs, p, o, &cur, cycles == 1, s), "cycle");
-            HIP_TRY(hipMemcpyAsync(hs, g->sc, offsetof(Scalars, mu), hipMemcpyDeviceToHost, s), "read norm");
-            HIP_TRY(hipStreamSynchronize(s), "cycle sync");
+            if (swept) cur = next;
+            HIP_TRY(enqueue_cycle(g, rhs, p, o, &cur, cycles == 1, s, swept), "cycle");
+            HIP_TRY(read_scalars(g, s), "read norm");
+            swept = part && cycles < ncyc && !last_step_likely(o, before, rel);
+            next = cur;
+            if (swept) HIP_TRY(vcycle_ahead(g, bufs, &next, rhs, s), "next sweep");
+            HIP_TRY(hipEventSynchronize(g->ev_read), "cycle sync");
             if (g->prof.on) prof_collect(g);
+            before = rel;
             rel = hs->rel;
             if (hs->bad || !std::isfinite(hs->norm)) {
                 status = IBM_E_NUMERIC;
@@ -1443,6 +1501,7 @@ void ibm_destroy_grid(ibm_grid *g) {
     if (!g) return;
     for (auto &e : g->prof.ev) (void)hipEventDestroy(e);
     if (g->ss.ev) (void)hipEventDestroy(g->ss.ev);
+    if (g->ev_read) (void)hipEventDestroy(g->ev_read);
     if (g->sc_host) (void)hipHostFree(g->sc_host);
     delete g;
 }

@@ -294,6 +294,7 @@ struct Prof {
 }  // namespace ibm
 
 struct ibm_grid {
+    hipEvent_t ev_read = nullptr;  // the residual's copy to the host
     int nx, ny, nz;
     int64_t N;
     std::vector<double> xf, yf, zf;
@@ -447,7 +448,10 @@ hipError_t sweep0_f64(ibm_grid *g, const double *pin, double *pout, const double
                       hipStream_t s);
 hipError_t refresh_f64(ibm_grid *g, const double *src_ghost, double *dst, hipStream_t s);
 hipError_t apply0_f64(ibm_grid *g, const double *p, double *out, hipStream_t s);
-hipError_t vcycle_f64(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s, const ibm_solve_opts *o);
+// swept: vcycle_ahead, the cycle's first pre-smoothing sweep and ghost refresh, is done
+hipError_t vcycle_f64(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s, const ibm_solve_opts *o,
+                      bool swept = false);
+hipError_t vcycle_ahead(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s);
 hipError_t vcycle_mixed(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s,
                         const ibm_solve_opts *o);
 hipError_t norm_pass(ibm_grid *g, const double *p, const double *f, hipStream_t s, bool write_r32, bool first);
@@ -466,8 +470,12 @@ hipError_t divmax_pass(ibm_grid *g, const double *u, const double *v, const doub
 hipError_t init_solution(ibm_grid *g, double *p, double *p2, int use_guess, hipStream_t s);
 hipError_t krylov_setup(ibm_grid *g, hipStream_t s);
 hipError_t krylov_residual(ibm_grid *g, const double *f, const double *x, hipStream_t s);
+// what of a step is enqueued before the host has seen the residual of the one before
+enum Ahead { AHEAD_NONE, AHEAD_P, AHEAD_SWEEP };
 // first: the first step after krylov_residual of a new solve (p and v are not read)
-hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s);
+hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s,
+                       Ahead done = AHEAD_NONE);
+hipError_t krylov_ahead(ibm_grid *g, const ibm_solve_opts *o, bool first, Ahead what, hipStream_t s);
 // the handle's last geometry set-up time is g->t_setup (seconds, host wall clock)
 hipError_t krylov_restart(ibm_grid *g, hipStream_t s);
 

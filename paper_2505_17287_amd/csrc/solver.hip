@@ -1160,7 +1160,8 @@ static hipError_t smooth_level(ibm_grid *g, int l, int nsweeps, const MuSource &
 template <typename T>
 static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, const T *lam, const double *gh,
                               const ibm_solve_opts *o, hipStream_t s, const T *start = nullptr,
-                              double *wide = nullptr) {
+                              double *wide = nullptr, bool swept = false) {
+    // swept: the first pre-smoothing sweep and its ghost refresh are done, bufs[*cur] holds its result
     // start (requires nu1 > 0): the iterate the first pre-smoothing sweep reads instead of
     // bufs[*cur]; it is only read, and the sweeps continue in bufs
     // wide (FP32 cycle with nu2 > 0): the last post-smoothing sweep and its ghost refresh
@@ -1168,7 +1169,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
     // it moves 17 bytes per cell, not 13)
     const Fine<T> F = FineOf<T>::get(g);
     hipError_t e;
-    for (int q = 0; q < o->nu1; ++q) {
+    for (int q = swept ? 1 : 0; q < o->nu1; ++q) {
         T *pin = (q == 0 && start) ? const_cast<T *>(start) : bufs[*cur], *pout = bufs[1 - *cur];
         if ((e = timed_sweep<T>(g, F, pin, pout, rhs, lam, s)) != hipSuccess) return e;
         if ((e = launch_refresh<T>(g, pin, pout, gh, s)) != hipSuccess) return e;
@@ -1188,9 +1189,9 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
         }
         // mu of level l from the partials of the restriction into it: by its first sweep where one
         // follows, by the tail for its own levels, else by a launch
-        auto swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
+        auto level_swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
         auto finalize_mu = [&](int l) {
-            if (!swept(l) && !(tail && l == lt))
+            if (!level_swept(l) && !(tail && l == lt))
                 hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nparts, &g->sc->vol[l],
                                    &g->sc->mu[l]);
         };
@@ -1272,8 +1273,17 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
     return hipGetLastError();
 }
 
-hipError_t vcycle_f64(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s, const ibm_solve_opts *o) {
-    return vcycle_impl<double>(g, bufs, cur, f, &g->sc->lambda, g->g_h, o, s);
+hipError_t vcycle_f64(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s, const ibm_solve_opts *o,
+                      bool swept) {
+    return vcycle_impl<double>(g, bufs, cur, f, &g->sc->lambda, g->g_h, o, s, nullptr, nullptr, swept);
+}
+
+hipError_t vcycle_ahead(ibm_grid *g, double **bufs, int *cur, const double *f, hipStream_t s) {
+    double *pin = bufs[*cur], *pout = bufs[1 - *cur];
+    const hipError_t e = launch_sweep<double>(fine64(g), pin, pout, f, &g->sc->lambda, s);
+    if (e != hipSuccess) return e;
+    *cur = 1 - *cur;
+    return launch_refresh<double>(g, pin, pout, g->g_h, s);
 }
 
 // e32 := 0 (dead cells too), so the inner cycle starts from a zero correction
@@ -1894,21 +1904,45 @@ __global__ void k_widen(const uint8_t *__restrict__ type, int64_t N, const float
     y[id] = (type[id] == T_DEAD) ? 0.0 : (double)e[id];
 }
 
+// whether the next preconditioner application begins with a sweep of the fine level
+static bool precond_sweeps(ibm_grid *g, const ibm_solve_opts *o) {
+    return o->method == IBM_BICGSTAB_SRJ ? !g->srj_omega.empty() : o->nu1 > 0;
+}
+
 // The start iterate of the next preconditioner application (y in ya or yb), cleared if that is
 // one of its working buffers; its ghost values are the update kernel's to write (GhostStart).
+// begun: that has happened already
 template <typename T>
-static T *precond_start(ibm_grid *g, double *ya, double *yb, const ibm_solve_opts *o, hipStream_t s) {
+static T *precond_start(ibm_grid *g, double *ya, double *yb, const ibm_solve_opts *o, hipStream_t s, bool begun) {
     const unsigned nbN = (unsigned)nblk(g->N);
     if constexpr (sizeof(T) == 4) {
-        if (o->nu1 > 0) return g->pz32;
-        hipLaunchKernelGGL(k_precond_zero<float>, dim3(nbN), dim3(256), 0, s, g->N, g->e32a, g->e32b);
+        if (precond_sweeps(g, o)) return g->pz32;
+        if (!begun) hipLaunchKernelGGL(k_precond_zero<float>, dim3(nbN), dim3(256), 0, s, g->N, g->e32a, g->e32b);
         return g->e32a;
     } else {
-        const bool srj = o->method == IBM_BICGSTAB_SRJ;
-        if (srj ? !g->srj_omega.empty() : o->nu1 > 0) return g->pz;
-        hipLaunchKernelGGL(k_precond_zero<double>, dim3(nbN), dim3(256), 0, s, g->N, ya, srj ? (double *)nullptr : yb);
+        if (precond_sweeps(g, o)) return g->pz;
+        if (!begun)
+            hipLaunchKernelGGL(k_precond_zero<double>, dim3(nbN), dim3(256), 0, s, g->N, ya,
+                               o->method == IBM_BICGSTAB_SRJ ? (double *)nullptr : yb);
         return ya;
     }
+}
+
+// the first sweep of a preconditioner application (precond_sweeps) and its ghost refresh
+template <typename T>
+static hipError_t precond_sweep(ibm_grid *g, const double *r, const T *e0, double *yb, const ibm_solve_opts *o,
+                                hipStream_t s) {
+    hipError_t e;
+    T *out;
+    if constexpr (sizeof(T) == 4) {
+        out = g->e32b;
+        e = launch_sweep<float>(FineOf<float>::get(g), e0, out, g->r32, &g->sc->zero32, s);
+    } else {
+        out = yb;
+        if (o->method == IBM_BICGSTAB_SRJ) e = launch_jacobi0(fine64(g), e0, r, out, g->srj_omega[0], s);
+        else e = launch_sweep<double>(fine64(g), e0, out, r, &g->sc->zero, s);
+    }
+    return e != hipSuccess ? e : launch_refresh<T>(g, e0, out, g->g_rhs, s);
 }
 
 template <typename T>
@@ -1921,11 +1955,12 @@ static GhostStart<T> ghost_start(ibm_grid *g, T *e) {
 // written by the kernel that formed r).  FP64: the result lands in one of (ya, yb), returned.
 // Mixed: the cycle runs in FP32 on the workspace's FP32 buffers and is widened into ya.
 // IBM_BICGSTAB_SRJ: instead of the V-cycle, the scheduled relaxed Jacobi sweeps of the
-// grid's schedule, each followed by the ghost refresh (FP64).
+// grid's schedule, each followed by the ghost refresh (FP64).  swept: precond_sweep is done.
 template <typename T>
 static hipError_t precondition(ibm_grid *g, const double *r, const T *e0, double *ya, double *yb, double **out,
-                               const ibm_solve_opts *o, hipStream_t s) {
+                               const ibm_solve_opts *o, hipStream_t s, bool swept = false) {
     hipError_t e;
+    int cur = swept ? 1 : 0;
     // With pre-smoothing the cycle starts from the start iterate, which the first sweep only
     // reads: no field is cleared per call.
     const T *start = o->nu1 > 0 ? e0 : nullptr;
@@ -1933,23 +1968,22 @@ static hipError_t precondition(ibm_grid *g, const double *r, const T *e0, double
         // g->r32 already holds the FP32 fluid part of r: the update kernel that formed r
         // (k_p_update, k_s_update) wrote it beside r
         float *eb[2] = {g->e32a, g->e32b};
-        int ecur = 0;
         // with post-smoothing, the last sweep writes the FP64 result itself
         double *wide = o->nu2 > 0 ? ya : nullptr;
-        if ((e = vcycle_impl<float>(g, eb, &ecur, g->r32, &g->sc->zero32, g->g_rhs, o, s, start, wide)) != hipSuccess)
+        if ((e = vcycle_impl<float>(g, eb, &cur, g->r32, &g->sc->zero32, g->g_rhs, o, s, start, wide, swept)) !=
+            hipSuccess)
             return e;
         if (!wide)
-            hipLaunchKernelGGL(k_widen, dim3((unsigned)nblk(g->N)), dim3(256), 0, s, g->type, g->N, eb[ecur], ya);
+            hipLaunchKernelGGL(k_widen, dim3((unsigned)nblk(g->N)), dim3(256), 0, s, g->type, g->N, eb[cur], ya);
         *out = ya;
     } else if (o->method == IBM_BICGSTAB_SRJ) {
         // scheduled relaxed Jacobi: every sweep writes all cells of the other buffer; the first
         // one reads the start iterate (no sweep: the start iterate, in ya, is the result)
         double *bufs[2] = {ya, yb};
-        int cur = 0;
-        const double *pin = e0;
+        const double *pin = swept ? bufs[cur] : e0;
         const Fine<double> F = fine64(g);
-        for (double w : g->srj_omega) {
-            if ((e = launch_jacobi0(F, pin, r, bufs[1 - cur], w, s)) != hipSuccess) return e;
+        for (size_t q = swept ? 1 : 0; q < g->srj_omega.size(); ++q) {
+            if ((e = launch_jacobi0(F, pin, r, bufs[1 - cur], g->srj_omega[q], s)) != hipSuccess) return e;
             if ((e = launch_refresh<double>(g, pin, bufs[1 - cur], g->g_rhs, s)) != hipSuccess) return e;
             cur = 1 - cur;
             pin = bufs[cur];
@@ -1957,8 +1991,9 @@ static hipError_t precondition(ibm_grid *g, const double *r, const T *e0, double
         *out = bufs[cur];
     } else {
         double *bufs[2] = {ya, yb};
-        int cur = 0;
-        if ((e = vcycle_impl<double>(g, bufs, &cur, r, &g->sc->zero, g->g_rhs, o, s, start)) != hipSuccess) return e;
+        if ((e = vcycle_impl<double>(g, bufs, &cur, r, &g->sc->zero, g->g_rhs, o, s, start, nullptr, swept)) !=
+            hipSuccess)
+            return e;
         *out = bufs[cur];
     }
     return hipGetLastError();
@@ -2009,23 +2044,46 @@ hipError_t krylov_residual(ibm_grid *g, const double *f, const double *x, hipStr
     return hipGetLastError();
 }
 
-// one BiCGStab step on x (kv: r, rh, pd, v, s, t, ya, yb, za, zb); T: the preconditioner's type
+// The beginning of a BiCGStab step: the new direction, and with AHEAD_SWEEP the first sweep of its
+// preconditioner.  It writes the step's scratch vectors alone, so it may be enqueued before the
+// host has seen the residual of the step before, and dropped; a restart of the shadow residual
+// in between changes nothing either (beta is 0 then: the direction is the residual).
 template <typename T>
-static hipError_t krylov_step_t(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s) {
+static hipError_t krylov_ahead_t(ibm_grid *g, const ibm_solve_opts *o, bool first, Ahead what, hipStream_t s) {
+    double *r = g->kv[0], *pd = g->kv[2], *v = g->kv[3], *ya = g->kv[6], *yb = g->kv[7];
+    float *r32 = sizeof(T) == 4 ? g->r32 : nullptr;  // FP32 right-hand side of the mixed cycle
+    T *e0 = precond_start<T>(g, ya, yb, o, s, false);
+    const GhostStart<T> S = ghost_start<T>(g, e0);
+    hipLaunchKernelGGL(k_p_update<T>, dim3((unsigned)(nblk(g->N) + S.blocks)), dim3(256), 0, s, g->type, g->N, r, v, pd,
+                       g->sc, r32, first ? 1 : 0, S);
+    if (what == AHEAD_SWEEP && precond_sweeps(g, o)) return precond_sweep<T>(g, pd, e0, yb, o, s);
+    return hipGetLastError();
+}
+
+hipError_t krylov_ahead(ibm_grid *g, const ibm_solve_opts *o, bool first, Ahead what, hipStream_t s) {
+    return o->precision == IBM_MIXED ? krylov_ahead_t<float>(g, o, first, what, s)
+                                     : krylov_ahead_t<double>(g, o, first, what, s);
+}
+
+// one BiCGStab step on x (kv: r, rh, pd, v, s, t, ya, yb, za, zb), less what was enqueued ahead;
+// T: the preconditioner's type
+template <typename T>
+static hipError_t krylov_step_t(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, Ahead done,
+                                hipStream_t s) {
     double *r = g->kv[0], *rh = g->kv[1], *pd = g->kv[2], *v = g->kv[3], *sv = g->kv[4], *t = g->kv[5];
     double *ya = g->kv[6], *yb = g->kv[7], *za = g->kv[8], *zb = g->kv[9];
     hipError_t e;
     float *r32 = sizeof(T) == 4 ? g->r32 : nullptr;  // FP32 right-hand side of the mixed cycle
     double *y = nullptr, *z = nullptr;
-    T *e0 = precond_start<T>(g, ya, yb, o, s);
-    GhostStart<T> S = ghost_start<T>(g, e0);
-    const unsigned nb = (unsigned)(nblk(g->N) + S.blocks);
-    hipLaunchKernelGGL(k_p_update<T>, dim3(nb), dim3(256), 0, s, g->type, g->N, r, v, pd, g->sc, r32, first ? 1 : 0, S);
-    if ((e = precondition<T>(g, pd, e0, ya, yb, &y, o, s)) != hipSuccess) return e;
+    if (done == AHEAD_NONE && (e = krylov_ahead_t<T>(g, o, first, AHEAD_P, s)) != hipSuccess) return e;
+    T *e0 = precond_start<T>(g, ya, yb, o, s, true);
+    if ((e = precondition<T>(g, pd, e0, ya, yb, &y, o, s, done == AHEAD_SWEEP && precond_sweeps(g, o))) != hipSuccess)
+        return e;
     if ((e = apply_projected(g, y, v, rh, 0, K_ALPHA, o->breakdown_tol, s)) != hipSuccess) return e;
-    e0 = precond_start<T>(g, za, zb, o, s);
-    S = ghost_start<T>(g, e0);
-    hipLaunchKernelGGL(k_s_update<T>, dim3(nb), dim3(256), 0, s, g->type, g->N, r, v, sv, g->sc, r32, S);
+    e0 = precond_start<T>(g, za, zb, o, s, false);
+    const GhostStart<T> S = ghost_start<T>(g, e0);
+    hipLaunchKernelGGL(k_s_update<T>, dim3((unsigned)(nblk(g->N) + S.blocks)), dim3(256), 0, s, g->type, g->N, r, v, sv,
+                       g->sc, r32, S);
     if ((e = precondition<T>(g, sv, e0, za, zb, &z, o, s)) != hipSuccess) return e;
     if ((e = apply_projected(g, z, t, sv, 1, K_OMEGA, o->breakdown_tol, s)) != hipSuccess) return e;
     const int nxr = red_blocks(g->N, 2 * NORM_NT);
@@ -2036,8 +2094,9 @@ static hipError_t krylov_step_t(ibm_grid *g, double *x, const ibm_solve_opts *o,
     return hipGetLastError();
 }
 
-hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s) {
-    return o->precision == IBM_MIXED ? krylov_step_t<float>(g, x, o, first, s) : krylov_step_t<double>(g, x, o, first, s);
+hipError_t krylov_step(ibm_grid *g, double *x, const ibm_solve_opts *o, bool first, hipStream_t s, Ahead done) {
+    return o->precision == IBM_MIXED ? krylov_step_t<float>(g, x, o, first, done, s)
+                                     : krylov_step_t<double>(g, x, o, first, done, s);
 }
 
 // restart the shadow residual after a breakdown: rh = r, rho = r.r, beta = 0

@@ -72,3 +72,18 @@ def test_mixed_start(nu):
     b, sb = g.poisson_solve(r, precision="mixed", **kw)
     assert sa.status == 0 and sb.status == 0
     assert float((a - b).abs().max() / a.abs().max()) <= 1e-8
+
+
+@pytest.mark.parametrize("kw", [dict(method="bicgstab"), dict(method="bicgstab", precision="mixed"),
+                                dict(method="bicgstab_srj", srj_sweeps=4), dict(method="vcycle"),
+                                dict(method="bicgstab", nu1=0)], ids=str)
+def test_work_ahead_of_the_residual_changes_nothing(kw):
+    import torch
+
+    _, g, rhs = _problem((35, 33, 31), 7.3)
+    r = torch.from_numpy(rhs).cuda()
+    kw = dict(dict(rel_tol=1e-9, max_cycles=40), **kw)
+    a, sa = g.poisson_solve(r, **kw)
+    g.set_profiling(True)  # the sweeps are timed one by one: nothing is enqueued ahead
+    b, sb = g.poisson_solve(r, **kw)
+    assert torch.equal(a, b) and (sa.cycles, sa.status) == (sb.cycles, sb.status)
