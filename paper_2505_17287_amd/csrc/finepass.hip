@@ -87,7 +87,7 @@ __device__ __forceinline__ double mean_of(const MeanParts &m) {
 }
 
 // ---- residual + restriction --------------------------------------------------------------
-// R_1(C) = sum over fluid children c of V_c r_c with r = (f - lambda) - S p; e_1 = 0;
+// R_1(C) = sum over fluid children c of V_c r_c with r = (f - lambda) - S p; e_1 = 0 unless C.e is null;
 // partials[block] = sum of the R_1 written by the block.  The loads of plane k+1 are issued
 // before plane k is computed (two plane slots, alternating by name).
 template <typename T>
@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(ZM_NT)
             const int K_ = hz ? k_ >> 1 : k_;                                                                      \
             const int64_t cid = ((int64_t)K_ * C.n[1] + J) * C.n[0] + I;                                           \
             C.R[cid] = acc;                                                                                        \
-            C.e[cid] = T(0);                                                                                       \
+            if (C.e) C.e[cid] = T(0);                                                                              \
             psum += (double)acc;                                                                                   \
         }                                                                                                          \
         pm = pc;                                                                                                   \
@@ -291,7 +291,7 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
             if (own) {                                                                                             \
                 const int64_t cid = ((int64_t)K * C.n[1] + J) * C.n[0] + I0 + lane;                                \
                 C.R[cid] = s;                                                                                      \
-                C.e[cid] = T(0);                                                                                   \
+                if (C.e) C.e[cid] = T(0);                                                                          \
                 psum += (double)s;                                                                                 \
             }                                                                                                      \
             acc = T(0);                                                                                            \
@@ -938,11 +938,11 @@ __global__ void __launch_bounds__(ZP_NT)
             const int K_ = hz ? k_ >> 1 : k_;                                                                      \
             const int64_t cid = ((int64_t)K_ * C.n[1] + J) * C.n[0] + I;                                           \
             C.R[cid] = acc0;                                                                                       \
-            C.e[cid] = T(0);                                                                                       \
+            if (C.e) C.e[cid] = T(0);                                                                              \
             psum += (double)acc0;                                                                                  \
             if (!hx) {                                                                                             \
                 C.R[cid + 1] = acc1;                                                                               \
-                C.e[cid + 1] = T(0);                                                                               \
+                if (C.e) C.e[cid + 1] = T(0);                                                                      \
                 psum += (double)acc1;                                                                              \
             }                                                                                                      \
         }                                                                                                          \

@@ -386,7 +386,7 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
             if (own) {                                                                                         \
                 const int64_t cid = ((int64_t)K * C.n[1] + J) * C.n[0] + I0 + lane;                            \
                 C.R[cid] = s;                                                                                  \
-                C.e[cid] = T(0);                                                                               \
+                if (C.e) C.e[cid] = T(0);                                                                      \
                 psum += (double)s;                                                                             \
             }                                                                                                  \
             acc = T(0);                                                                                        \
@@ -532,7 +532,7 @@ __global__ void __launch_bounds__(256) k_resrestrictC8(Coarse<T> L, Coarse<T> C,
                     if (act) R += rc;
                 }
         C.R[cid] = R;
-        C.e[cid] = T(0);
+        if (C.e) C.e[cid] = T(0);
         Rsum = (double)R;
     }
     double s = block_sum<256>(Rsum, sh, threadIdx.x);
@@ -1181,15 +1181,17 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
         const bool tail = lt <= Lc;
         const int Lb = tail ? lt : Lc;  // levels 1 .. Lb-1 run level by level
         int nparts = 0;                 // restriction partials into level Lb
+        // levels whose first sweep takes a zero correction without reading it (not cleared then)
+        auto level_swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
         {
             Coarse<T> C1 = coarse_view<T>(g, 1);
+            if (level_swept(1)) C1.e = nullptr;
             if ((e = launch_restrict0<T>(F, bufs[*cur], rhs, lam, C1, child_map(g->lev[1]), g->partials, &nparts,
                                          s)) != hipSuccess)
                 return e;
         }
         // mu of level l from the partials of the restriction into it: by its first sweep where one
         // follows, by the tail for its own levels, else by a launch
-        auto level_swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
         auto finalize_mu = [&](int l) {
             if (!level_swept(l) && !(tail && l == lt))
                 hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nparts, &g->sc->vol[l],
@@ -1209,6 +1211,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
             }
             Coarse<T> L = coarse_view<T>(g, l);  // after the sweeps: the current error buffer
             Coarse<T> C = coarse_view<T>(g, l + 1);
+            if (level_swept(l + 1)) C.e = nullptr;
             const ChildMap M = child_map(g->lev[l + 1]);
             int nbc = nblk(g->lev[l + 1].ncell());
             if (M.halved[0] && M.halved[1] && M.halved[2]) {

@@ -91,3 +91,29 @@ def test_coarse_bricks(dims, nu):
         err = np.max(np.abs(p.cpu().numpy() - ref)[active]) / np.max(np.abs(ref[active]))
         print(dims, nu, precision, g.levels()[1:3], "err", err, flush=True)
         assert err <= tol
+
+
+@pytest.mark.parametrize("dims,precision,tol", [((160, 160, 160), "fp64", 1e-9), ((154, 160, 150), "fp64", 1e-9),
+                                                ((206, 204, 204), "mixed", 1e-4), ((208, 204, 204), "mixed", 1e-4)],
+                         ids=str)
+def test_large_first_level_from_zero(dims, precision, tol):
+    """First coarse levels swept by the z-march, even and odd rows, their correction not cleared."""
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    f = [np.linspace(0.0, n, n + 1) for n in dims]
+    v, t = I.icosphere(3)
+    v = v * 9.3 + np.array([0.5 * n for n in dims])
+    P = OracleProblem(*f)
+    P.set_mesh(v, t)
+    P.classify()
+    P.build_stencils()
+    rhs = np.random.default_rng(1).uniform(-1.0, 1.0, (dims[2], dims[1], dims[0]))
+    ref, _ = P.solve(rhs, fixed_cycles=1, method="bicgstab")
+    g = ibm.Grid(*f, precision=precision)
+    g.setup(v, t)
+    active = P.types() != 2
+    for _ in range(2):  # the second time on what the first has left in the level's buffers
+        p, _st = g.poisson_solve(torch.from_numpy(rhs).cuda(), fixed_cycles=1, method="bicgstab", precision=precision)
+        assert np.max(np.abs(p.cpu().numpy() - ref)[active]) <= tol * np.max(np.abs(ref[active]))
