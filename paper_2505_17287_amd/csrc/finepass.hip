@@ -807,20 +807,25 @@ __global__ void __launch_bounds__(JAC_NT)
 // columns and a wave holds two rows (lanes l and l + 32).  For the restriction a thread's
 // pair is exactly one coarse cell's x children and a wave's row pair its y children, so the
 // in-plane part of the sum needs no LDS and no barrier.
-constexpr int ZP_TX = 64, ZP_TY = 8, ZP_NT = 256;
+constexpr int ZP_TX = 64, ZP_TY = 8, ZP_NT = 256, ZP_KC_MAX = 64;
 
-ZTiles ztiles2(int nx, int ny, int nz) {
+// resident: workgroups a CU holds.  The chunk length minimises rounds of resident workgroups x
+// (planes + 3), a chunk's start and its two planes shared with others counting as three.
+ZTiles ztiles2(int nx, int ny, int nz, int resident) {
     ZTiles t;
     t.ntx = (nx + ZP_TX - 1) / ZP_TX;
     t.nty = (ny + ZP_TY - 1) / ZP_TY;
-    const int64_t per_slab = (int64_t)t.ntx * t.nty;
-    int nchunk = (int)std::max<int64_t>(1, (int64_t)8 * device_cu_count() / per_slab);
-    nchunk = std::min(nchunk, std::max(1, nz / 2));
-    int kc = (nz + nchunk - 1) / nchunk;
-    kc += kc & 1;
-    nchunk = (nz + kc - 1) / kc;
-    t.kc = kc;
-    t.ntiles = (int)(per_slab * nchunk);
+    const int64_t per_slab = (int64_t)t.ntx * t.nty, slots = (int64_t)resident * device_cu_count();
+    int64_t best = INT64_MAX;
+    t.kc = 2;
+    for (int kc = 2; kc <= ZP_KC_MAX; kc += 2) {
+        const int64_t rounds = (per_slab * ((nz + kc - 1) / kc) + slots - 1) / slots;
+        if (rounds * (kc + 3) < best) {
+            best = rounds * (kc + 3);
+            t.kc = kc;
+        }
+    }
+    t.ntiles = (int)(per_slab * ((nz + t.kc - 1) / t.kc));
     t.grid = ((t.ntiles + 7) / 8) * 8;
     return t;
 }
@@ -1067,7 +1072,7 @@ hipError_t launch_restrict0(const Fine<T> &F, const T *p, const T *f, const T *l
     }
     const int halved[3] = {M.halved[0], M.halved[1], M.halved[2]};
     if ((F.nx & 1) == 0 && F.nx >= 2) {
-        const ZTiles t = ztiles2(F.nx, F.ny, F.nz);
+        const ZTiles t = ztiles2(F.nx, F.ny, F.nz, sizeof(T) == 8 ? 4 : 7);
         hipLaunchKernelGGL(k_restrict0_zm2<T>, dim3(t.grid), dim3(ZP_NT), 0, s, F, p, f, lam, C, halved[0],
                            halved[1], halved[2], t, partials);
         *nparts = t.grid;
@@ -1095,7 +1100,7 @@ template <int DOTS>
 static hipError_t apply_fluid_dots(const Fine<double> &F, const double *y, double *w, const double *o,
                                    const MeanParts &mu, double *partials, int *nparts, hipStream_t s) {
     if ((F.nx & 1) == 0 && F.nx >= 2) {
-        const ZTiles t = ztiles2(F.nx, F.ny, F.nz);
+        const ZTiles t = ztiles2(F.nx, F.ny, F.nz, 4);
         hipLaunchKernelGGL(k_apply_fluid_zm2<DOTS>, dim3(t.grid), dim3(ZP_NT), 0, s, F, y, w, o, mu, t, partials);
         *nparts = t.grid;
         return hipGetLastError();
