@@ -390,6 +390,8 @@ size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_ma
     size_t b = layout(nullptr, P, nx, ny, nz, nv_max, nt_max, max_ghosts, prec, lev, 1);
     const int64_t N = (int64_t)nx * ny * nz;
     const int64_t axes = (int64_t)nx + ny + nz;
+    // the large coarse arrays' stagger
+    for (int64_t n = N / 2; n >= STAGGER_MIN; n /= 2) b += 16 * 15 * STAGGER;
     return b + (size_t)N * 61 + (size_t)MAX_LEVELS * (size_t)(axes * 80 + 40 * 256) + (1 << 20);
 }
 

@@ -378,14 +378,21 @@ struct ibm_grid {
 namespace ibm {
 
 // workspace planner: computes offsets (base == nullptr -> sizing only)
+// Large arrays start STAGGER further off the 4 KB grid each: fields of 2^24 doubles and the like lie
+// a large power of two apart otherwise, and the streams of a pass meet in the same channels (384^3:
+// fine sweep 340 -> 331 us, operator 315 -> 302; steps of 140 KB and 1 MB gave the same).
+constexpr int64_t STAGGER_MIN = 1 << 20;
+constexpr size_t STAGGER = 4096 + 256;
 struct Plan {
     size_t off = 0;
+    size_t large = 0;
     char *base = nullptr;
     // optional: (offset, bytes) of every floating-point sub-buffer, for the poisoned bind
     std::vector<std::pair<size_t, size_t>> *fp_spans = nullptr;
     template <typename T>
     T *take(int64_t count) {
         off = (off + 255) & ~size_t(255);
+        if (count >= STAGGER_MIN) off += STAGGER * (large++ % 16);
         T *p = base ? reinterpret_cast<T *>(base + off) : nullptr;
         const size_t bytes = sizeof(T) * (size_t)(count > 0 ? count : 1);
         if (fp_spans && std::is_floating_point<T>::value) fp_spans->emplace_back(off, bytes);
