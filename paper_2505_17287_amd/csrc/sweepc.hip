@@ -20,7 +20,7 @@ namespace ibm {
 // owns two adjacent columns, so it holds one red and one black cell per plane.
 // The coarse operator is not separable: each cell carries the transmissibilities of its
 // three low faces.  The high faces are the low faces of the +x, +y and +z neighbours: +x
-// from the neighbouring lane (one shuffle), +y from LDS, +z from the next plane in the
+// from the neighbouring lane (a DPP move), +y from LDS, +z from the next plane in the
 // queue.  A face is open only when the fine cells on both of its sides are active, so a
 // cell with an open face is active and an inactive cell has none: the test sum_f T_f > 0
 // already excludes inactive cells, and the activity mask is not read.  Wall faces hold 0.
@@ -187,7 +187,7 @@ __global__ void __launch_bounds__(32 * BY)
     const T *__restrict__ py = L.Tl[1];
     const T *__restrict__ pz = L.Tl[2];
     // the zero of ZERO, kept from the optimiser: as a known constant it made the compiler peel and
-    // rearrange the pipelined loop, with wrong results on even rows
+    // rearrange the pipelined loop (with the x neighbour by a shuffle, even rows then came out wrong)
     T z0 = T(0);
     asm volatile("" : "+v"(z0));
     auto load = [=](int k) -> PD {
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(32 * BY)
 #define IBMC_RED(q, M, C, P, OB, R0, R1, FR)                                                                       \
     {                                                                                                              \
         const int l_ = (FR) ? lc : lc + 1;                                                                         \
-        const T xn_ = __shfl_down((C).x.x, 1, 64);                                                                 \
+        const T xn_ = lane_above((C).x.x);                                                                         \
         const T txm_ = (FR) ? (C).x.x : (C).x.y;                                                                   \
         const T txp_ = (FR) ? (C).x.y : (hx1 ? xn_ : T(0));                                                        \
         const T tym_ = (FR) ? (C).y.x : (C).y.y;                                                                   \
@@ -259,7 +259,7 @@ __global__ void __launch_bounds__(32 * BY)
         T out0, out1;                                                                                              \
         {                                                                                                          \
             const int l_ = (FR) ? lc : lc + 1;                                                                     \
-            const T xn_ = __shfl_down((A).x.x, 1, 64);                                                             \
+            const T xn_ = lane_above((A).x.x);                                                                     \
             const T txm_ = (FR) ? (A).x.x : (A).x.y;                                                               \
             const T txp_ = (FR) ? (A).x.y : (hx1 ? xn_ : T(0));                                                    \
             const T tym_ = (FR) ? (A).y.x : (A).y.y;                                                               \
