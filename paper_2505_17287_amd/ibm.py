@@ -195,9 +195,16 @@ def _tptr(t):
 def estimate_max_ghosts(xf, yf, zf, verts, tris):
     """Capacity for the ghost list: four cells per finest-cell face of surface, plus slack."""
     v = np.ascontiguousarray(verts, dtype=np.float64)
-    t = np.ascontiguousarray(tris, dtype=np.int32)
-    area = lib().ibm_mesh_area(_dp(v), len(v), C.c_void_p(t.ctypes.data), len(t))
-    if area < 0.0:  # an index out of range: IndexError, or a wrapped index that ibm_set_geometry refuses
+    t = np.asarray(tris)
+    # the native pass reads three doubles a vertex and three int32 a triangle; whatever else is
+    # given, numpy refuses (or takes: negative indices, further columns)
+    if (v.ndim == 2 and v.shape[1] == 3 and t.ndim == 2 and t.shape[1] == 3 and t.dtype.kind in "iu"
+            and (t.dtype == np.int32 or t.size == 0 or (t.min() >= 0 and t.max() < len(v)))):
+        t = np.ascontiguousarray(t, dtype=np.int32)
+        area = lib().ibm_mesh_area(_dp(v), len(v), C.c_void_p(t.ctypes.data), len(t))
+    else:
+        area = -1.0
+    if area < 0.0:
         area = 0.5 * np.linalg.norm(np.cross(v[t[:, 1]] - v[t[:, 0]], v[t[:, 2]] - v[t[:, 0]]), axis=1).sum()
     h = [np.min(np.diff(f)) for f in (xf, yf, zf)]
     if len(zf) == 2:  # one cell thick: count per unit of the z extent inside the cell
@@ -208,6 +215,16 @@ def estimate_max_ghosts(xf, yf, zf, verts, tris):
         est = 4.0 * area / (hmin * hmin)
     n = (len(xf) - 1) * (len(yf) - 1) * (len(zf) - 1)
     return int(min(n, est + 4096))
+
+
+def _mesh_arrays(verts, tris):
+    """A mesh as the library reads it: 3 doubles a vertex, 3 int32 a triangle."""
+    v = np.ascontiguousarray(verts, dtype=np.float64)
+    t = np.ascontiguousarray(tris, dtype=np.int32)
+    for name, a in (("verts", v), ("tris", t)):
+        if a.ndim != 2 or a.shape[1] != 3:
+            raise ValueError("%s must have shape (n, 3), not %s" % (name, a.shape))
+    return v, t
 
 
 class Grid:
@@ -279,8 +296,7 @@ class Grid:
         return nbytes
 
     def set_geometry(self, verts, tris, max_ghosts=None):
-        self.verts = np.ascontiguousarray(verts, dtype=np.float64)
-        self.tris = np.ascontiguousarray(tris, dtype=np.int32)
+        self.verts, self.tris = _mesh_arrays(verts, tris)
         nv, nt = len(self.verts), len(self.tris)
         if max_ghosts is None:
             max_ghosts = estimate_max_ghosts(self.xf, self.yf, self.zf, self.verts, self.tris)
@@ -483,8 +499,7 @@ class Grid:
     def move_geometry(self, verts, tris):
         """New vertex positions (same or new triangles): re-classify, rebuild the stencils and
         list the fresh cells.  Returns (counts, n_fresh)."""
-        self.verts = np.ascontiguousarray(verts, dtype=np.float64)
-        self.tris = np.ascontiguousarray(tris, dtype=np.int32)
+        self.verts, self.tris = _mesh_arrays(verts, tris)
         counts = np.zeros(3, dtype=np.int64)
         nf = np.zeros(1, dtype=np.int64)
         with self.torch.cuda.device(self.device):

@@ -144,3 +144,58 @@ def test_mesh_area():
     bad[3, 1] = len(v)
     with pytest.raises(IndexError):
         ibm.estimate_max_ghosts(f, f, f, v, bad)
+
+
+def _numpy_estimate(f, v, t):
+    v, t = np.asarray(v, dtype=np.float64), np.asarray(t)
+    area = 0.5 * np.linalg.norm(np.cross(v[t[:, 1]] - v[t[:, 0]], v[t[:, 2]] - v[t[:, 0]]), axis=1).sum()
+    h = f[1] - f[0]
+    return int(min((len(f) - 1) ** 3, 4.0 * area / (h * h) + 4096))
+
+
+MESH_FORMS = {
+    "vertices (n, 2)": lambda v, t: (v[:, :2], t),
+    "vertices (n, 4)": lambda v, t: (np.c_[v, v[:, 0]], t),
+    "vertices flat": lambda v, t: (v.ravel(), t),
+    "triangles (n, 2)": lambda v, t: (v, t[:, :2]),
+    "triangles flat": lambda v, t: (v, t.ravel()),
+    "triangles (n, 4)": lambda v, t: (v, np.c_[t, t[:, 0]]),
+    "no triangle, no shape": lambda v, t: (v, []),
+    "no triangle": lambda v, t: (v, t[:0]),
+    "float indices": lambda v, t: (v, t.astype(np.float64)),
+    "index beyond 2^32": lambda v, t: (v, t.astype(np.int64) + (1 << 32)),
+    "int64": lambda v, t: (v, t.astype(np.int64)),
+    "uint16": lambda v, t: (v, t.astype(np.uint16)),
+    "lists": lambda v, t: (v.tolist(), t.tolist()),
+    "negative index": lambda v, t: (v, t.astype(np.int64) - len(v)),
+    "float32, transposed": lambda v, t: (np.asfortranarray(v, dtype=np.float32), np.asfortranarray(t)),
+}
+
+
+@pytest.mark.parametrize("form", MESH_FORMS)
+def test_ghost_estimate_takes_and_refuses_meshes_as_numpy_does(form):
+    from paper_2505_17287_amd import inputs as I
+
+    f = I.uniform_faces(-1.0, 1.0, 64)
+    v, t = MESH_FORMS[form](*I.aabb_mesh((-0.5, -0.25, -0.125), (0.5, 0.25, 0.375)))
+    try:
+        want = _numpy_estimate(f, v, t)
+    except (IndexError, ValueError):
+        with pytest.raises((IndexError, ValueError)):
+            ibm.estimate_max_ghosts(f, f, f, v, t)
+    else:
+        assert ibm.estimate_max_ghosts(f, f, f, v, t) == want
+
+
+@pytest.mark.parametrize("form", [k for k in MESH_FORMS if "(n, " in k or "flat" in k])
+def test_meshes_of_another_shape_are_refused_before_they_are_read(form):
+    from paper_2505_17287_amd import inputs as I
+
+    f = I.uniform_faces(-1.0, 1.0, 8)
+    v, t = MESH_FORMS[form](*I.aabb_mesh((-0.5, -0.25, -0.125), (0.5, 0.25, 0.375)))
+    g = ibm.Grid(f, f, f)
+    for call in (lambda: g.set_geometry(v, t), lambda: g.set_geometry(v, t, max_ghosts=512),
+                 lambda: g.move_geometry(v, t)):
+        with pytest.raises(ValueError, match="shape"):
+            call()
+    g.close()
