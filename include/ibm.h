@@ -119,7 +119,8 @@ size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_ma
 double ibm_mesh_area(const double *verts, int64_t nv, const int32_t *tris, int64_t nt);
 
 /* Exact workspace size for an existing handle (its multigrid plan depends on the face
-   coordinates).  ibm_workspace_bytes is an upper bound of this for any coordinates. */
+   coordinates).  ibm_workspace_bytes is an upper bound of this for all coordinates whose largest
+   cell is at most 10^4 times as wide as the smallest (axes of one cell aside). */
 size_t ibm_grid_workspace_bytes(const ibm_grid *g, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,
                                 ibm_precision prec);
 

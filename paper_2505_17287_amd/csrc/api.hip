@@ -206,6 +206,10 @@ ChildMap child_map(const LevelHost &C) {
     return M;
 }
 
+// per cell of a coarse level: activity, three transmissibilities, correction, right-hand side and
+// second correction, in both precisions
+constexpr size_t COARSE_CELL_BYTES = 1 + 6 * (sizeof(double) + sizeof(float));
+
 size_t layout(ibm_grid *g, Plan &P, int nx, int ny, int nz, int64_t nv_max, int64_t nt_max, int64_t gmax,
               ibm_precision prec, LevelHost *lev, int nlev) {
     const int64_t N = (int64_t)nx * ny * nz, ncol = (int64_t)nx * ny;
@@ -379,9 +383,13 @@ ibm_status ibm_create_grid(int nx, int ny, int nz, const double *xf, const doubl
 size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,
                            ibm_precision prec) {
     if (nx < 2 || ny < 2 || nz < 1) return 0;
-    // Upper bound for any face coordinates: the fine level exactly, plus coarse levels of at
-    // most half the previous level's cells each (their sum stays below N) at 61 B per coarse
-    // cell, plus per-level 1D arrays and alignment.
+    // The fine level exactly, plus coarse levels of at most half the previous level's cells each
+    // (their sum stays below N) at COARSE_CELL_BYTES per cell, plus per-level 1D arrays and
+    // alignment.  plan_levels stops raising its width limit at half the cells, or when every axis
+    // of at least four cells is halved: such a level holds at most half as many cells plus 4.5 (an
+    // odd axis beside two of three cells), 207 more over all levels.  The limit can be raised to
+    // 4.4e6 2^(l-1) h_min at level l, and merged cells grow by 2.5 a level at most, so for widths
+    // within 1e4 h_min one of the two always comes first.
     LevelHost lev[1];
     lev[0].n[0] = nx;
     lev[0].n[1] = ny;
@@ -392,7 +400,7 @@ size_t ibm_workspace_bytes(int nx, int ny, int nz, int64_t nv_max, int64_t nt_ma
     const int64_t axes = (int64_t)nx + ny + nz;
     // the large coarse arrays' stagger
     for (int64_t n = N / 2; n >= STAGGER_MIN; n /= 2) b += 16 * 15 * STAGGER;
-    return b + (size_t)N * 61 + (size_t)MAX_LEVELS * (size_t)(axes * 80 + 40 * 256) + (1 << 20);
+    return b + (size_t)N * COARSE_CELL_BYTES + (size_t)MAX_LEVELS * (size_t)(axes * 80 + 40 * 256) + (1 << 20);
 }
 
 size_t ibm_grid_workspace_bytes(const ibm_grid *gc, int64_t nv_max, int64_t nt_max, int64_t max_ghosts,

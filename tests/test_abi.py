@@ -199,3 +199,35 @@ def test_meshes_of_another_shape_are_refused_before_they_are_read(form):
         with pytest.raises(ValueError, match="shape"):
             call()
     g.close()
+
+
+def _widths(kind, n, q):
+    """Cell widths: uniform q, growing from the middle to q on either side, a ratio q from cell to
+    cell, or log-uniform over a factor q."""
+    if kind == "uniform":
+        return np.full(n, q)
+    if kind == "middle":
+        return np.exp(np.abs(np.linspace(-1.0, 1.0, n)) * np.log(q))
+    if kind == "growing":
+        return q ** np.arange(n)
+    return np.exp(np.random.default_rng(n).uniform(0.0, np.log(q), n))
+
+
+@pytest.mark.parametrize("axes", [
+    [("uniform", 64, 1.0)] * 2 + [("uniform", 64, 1 / 64)], [("uniform", 80, 1.0)] * 2 + [("uniform", 80, 1 / 64)],
+    [("uniform", 128, 1.0)] * 2 + [("uniform", 128, 1 / 16)], [("uniform", 256, 1.0)] * 2 + [("uniform", 256, 1 / 16)],
+    [("growing", 72, 1.1)] * 3, [("growing", 80, 1.1)] * 3, [("middle", 72, 1e3)] * 3, [("middle", 160, 1e2)] * 3,
+    [("middle", 96, 1e4)] * 3, [("log", 100, 1e4)] * 3, [("log", 300, 1e4)] * 2 + [("uniform", 40, 1.0)],
+    [("uniform", 2, 1.0)] * 2 + [("uniform", 1 << 20, 1.0)], [("uniform", 3, 1.0)] * 2 + [("uniform", 233017, 1.0)],
+    [("uniform", 65, 1e4), ("uniform", 67, 1e2), ("uniform", 129, 1.0)],
+], ids=str)
+def test_workspace_bound_covers_strong_gradings(axes):
+    L = ibm.lib()
+    f = [np.concatenate([[0.0], np.cumsum(_widths(*a))]) for a in axes]
+    nx, ny, nz = (len(a) - 1 for a in f)
+    code, h = _create(nx, ny, nz, *f)
+    assert code == 0
+    for prec in (ibm.IBM_FP64, ibm.IBM_MIXED):
+        for caps in ((3, 1, 0), (1000, 2000, 5000)):
+            assert 0 < L.ibm_grid_workspace_bytes(h, *caps, prec) <= L.ibm_workspace_bytes(nx, ny, nz, *caps, prec)
+    L.ibm_destroy_grid(h)
