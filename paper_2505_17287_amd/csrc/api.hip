@@ -919,13 +919,15 @@ static ibm_status solve_core(ibm_grid *g, const double *rhs, double *p, const ib
     HIP_TRY(mark_read(g, s), "read");
     double *bufs[2] = {p, g->p2};
     int cur = 1, next = 1;
-    // the next cycle's first sweep goes to the buffer that does not hold the iterate
+    // The next cycle's first sweep goes to the buffer that does not hold the iterate.  The first
+    // cycle's is p, which keeps the caller's guess until the right-hand side is known to be finite.
     const bool part = o->precision == IBM_FP64 && o->nu1 > 0 && ahead_part(g) == AHEAD_SWEEP;
-    bool swept = part;
+    bool swept = part && !o->use_initial_guess;
     if (swept) HIP_TRY(vcycle_ahead(g, bufs, &next, rhs, s), "first sweep");
     HIP_TRY(hipEventSynchronize(g->ev_read), "solve sync");
     Scalars *hs = g->sc_host;
     if (hs->bad) {
+        if (swept) HIP_TRY(init_solution(g, p, g->p2, 0, s), "init");
         HIP_TRY(hipStreamSynchronize(s), "sync");
         return fail(g, IBM_E_NUMERIC, "non-finite right-hand side or initial guess");
     }
