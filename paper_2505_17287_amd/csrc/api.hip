@@ -153,14 +153,34 @@ void plan_levels(int nx, int ny, int nz, const double *xf, const double *yf, con
                 C.w[d][i] = C.f[d][i + 1] - C.f[d][i];
             }
         }
-        // tiles of the restriction: the coarse columns and planes whose first child lies in a window
-        // of finer ones
+        // side rule of the prolongation table (k_prolong_tab) on uniformly halved axes: fine i
+        // takes I = i/2 and the coarse neighbour on the side of its centre
+        bool sides = true;
+        for (int d = 0; d < 3; ++d) {
+            if (!C.halved[d]) continue;
+            for (int i = 0; i < F.n[d]; ++i) {
+                const int I = i / 2, jn = (F.c[d][i] < C.c[d][I]) ? I - 1 : I + 1;
+                if (jn >= 0 && jn < C.n[d] && jn != ((i & 1) ? I + 1 : I - 1)) sides = false;
+            }
+        }
+        F.prolong_sides = sides;
+        ++n;
+    }
+    *nlev = n;
+}
+
+// Tiles of the restrictions: the coarse columns and planes whose first child lies in a window of
+// finer ones.  At bind, as they are sized by the device that will run them.
+static void plan_tiles(LevelHost *lev, int nlev) {
+    const int64_t resident = (int64_t)RM_RESIDENT * device_cu_count();
+    for (int l = 1; l < nlev; ++l) {
+        const LevelHost &F = lev[l - 1];
+        LevelHost &C = lev[l];
         C.tx.clear();
         for (int I = 0; I < C.n[0]; ++I)
             while ((int)C.tx.size() * RM_FX <= C.cs[0][I]) C.tx.push_back({I, C.cs[0][I]});
         C.tx.push_back({C.n[0], F.n[0]});
         const int64_t slab = (int64_t)(C.tx.size() - 1) * ((C.n[1] + RM_W - 1) / RM_W);
-        const int64_t resident = (int64_t)RM_RESIDENT * device_cu_count();
         int fz = 2;
         int64_t best = INT64_MAX;
         for (int z = 2; z <= RM_ZMAX; ++z) {
@@ -176,20 +196,7 @@ void plan_levels(int nx, int ny, int nz, const double *xf, const double *yf, con
             C.tz.back().ends |= uint64_t(1) << (C.cs[2][K + 1] - 1 - C.tz.back().k0);
         }
         C.tz.push_back({C.n[2], F.n[2], 0});
-        // side rule of the prolongation table (k_prolong_tab) on uniformly halved axes: fine i
-        // takes I = i/2 and the coarse neighbour on the side of its centre
-        bool sides = true;
-        for (int d = 0; d < 3; ++d) {
-            if (!C.halved[d]) continue;
-            for (int i = 0; i < F.n[d]; ++i) {
-                const int I = i / 2, jn = (F.c[d][i] < C.c[d][I]) ? I - 1 : I + 1;
-                if (jn >= 0 && jn < C.n[d] && jn != ((i & 1) ? I + 1 : I - 1)) sides = false;
-            }
-        }
-        F.prolong_sides = sides;
-        ++n;
     }
-    *nlev = n;
 }
 
 ChildMap child_map(const LevelHost &C) {
@@ -428,6 +435,7 @@ ibm_status ibm_bind_workspace(ibm_grid *g, void *device_ptr, size_t bytes, int64
         return fail(g, IBM_E_NOMEM, "workspace too small: need " + std::to_string(need) + " bytes");
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(hipGetDevice(&g->device), "hipGetDevice");
+    plan_tiles(g->lev, g->nlev);
     Plan P;
     P.base = (char *)device_ptr;
     std::vector<std::pair<size_t, size_t>> fp_spans;
