@@ -562,6 +562,7 @@ ibm_status ibm_set_geometry(ibm_grid *g, const double *verts, int64_t nv, const 
     g->nv = nv;
     g->nt = nt;
     HIP_TRY(launch_buckets(g, s), "bucket grid");
+    HIP_TRY(hipStreamSynchronize(s), "set_geometry sync");  // the next call may be on another stream
     g->stage = ST_GEOMETRY;
     g->ng = 0;
     g->t_setup = now_s() - t_in;

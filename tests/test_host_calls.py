@@ -60,6 +60,16 @@ def case_create():
     Handle()
 
 
+def case_waits():
+    H = Handle()
+    s = C.c_void_p(0x1000)
+    H.bind(s)
+    H.hip.fake_hip_mark()
+    for call in (H.set_geometry, H.classify, H.stencils, H.solve):
+        call(s)
+        H.hip.fake_hip_mark()
+
+
 @pytest.fixture(scope="module")
 def run(tmp_path_factory):
     d = tmp_path_factory.mktemp("fake_hip")
@@ -81,6 +91,19 @@ def run(tmp_path_factory):
 def test_grid_creation_does_no_device_work(run):
     """Planning needs no GPU: a process that only sizes a problem does not start the runtime."""
     assert run("create") == []
+
+
+def test_setup_and_solve_leave_nothing_in_flight(run):
+    """set_geometry, classify, build_ghost_stencils and poisson_solve return with their stream
+    idle: a program may go on with another stream, and the set-up time is the set-up's."""
+    log, calls = run("waits"), []
+    marks = [q for q, l in enumerate(log) if l[0] == "mark"]
+    for name, a, b in zip(("set_geometry", "classify", "build_ghost_stencils", "poisson_solve"), marks, marks[1:]):
+        work = [l for l in log[a + 1:b] if l[0] in ("kernel", "copy", "fill", "wait")]
+        assert {l[1] for l in work} == {"0x1000"}
+        if work[-1][0] != "wait":
+            calls.append(name)
+    assert len(marks) == 5 and not calls
 
 
 if __name__ == "__main__":
