@@ -435,6 +435,8 @@ ibm_status ibm_bind_workspace(ibm_grid *g, void *device_ptr, size_t bytes, int64
         return fail(g, IBM_E_NOMEM, "workspace too small: need " + std::to_string(need) + " bytes");
     hipStream_t s = (hipStream_t)stream;
     HIP_TRY(hipGetDevice(&g->device), "hipGetDevice");
+    if (g->ev_read) (void)hipEventDestroy(g->ev_read);  // of the device bound before
+    g->ev_read = nullptr;
     plan_tiles(g->lev, g->nlev);
     Plan P;
     P.base = (char *)device_ptr;

@@ -70,6 +70,17 @@ def case_waits():
         H.hip.fake_hip_mark()
 
 
+def case_second_device():
+    H = Handle()
+    for device in (0, 1, 1, 0):
+        H.hip.hipSetDevice(device)
+        H.bind()
+        for call in (H.set_geometry, H.classify, H.stencils, H.solve):
+            call()
+        H.solve(method="vcycle")
+    H.L.ibm_destroy_grid(H.h)
+
+
 @pytest.fixture(scope="module")
 def run(tmp_path_factory):
     d = tmp_path_factory.mktemp("fake_hip")
@@ -104,6 +115,14 @@ def test_setup_and_solve_leave_nothing_in_flight(run):
         if work[-1][0] != "wait":
             calls.append(name)
     assert len(marks) == 5 and not calls
+
+
+def test_events_live_on_the_device_of_the_workspace(run):
+    """A handle bound again on another device records none of the first one's events (the runtime
+    refuses that) and destroys what it has created."""
+    log = run("second_device")
+    assert any(l[0] == "record" for l in log)
+    assert sum(l[0] == "create" for l in log) == sum(l[0] == "destroy" for l in log)
 
 
 if __name__ == "__main__":
