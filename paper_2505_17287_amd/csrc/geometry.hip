@@ -339,8 +339,12 @@ __global__ void __launch_bounds__(64) k_mesh_final(const double *__restrict__ pa
 
 hipError_t launch_mesh_scan(ibm_grid *g, const double *V, int64_t nv, const int32_t *T, int64_t nt, MeshScan *out,
                             hipStream_t s) {
-    // the table lies in the crossing lists (4 nt_max entries and more), which the classification
-    // that has to follow writes anew; the summary in the reduction partials
+    // Scratch of the set-up alone, as a refused mesh leaves the handle's geometry in use, perhaps by
+    // a solve on another stream: the table lies in the crossing lists (4 nt_max entries and more),
+    // which the classification that has to follow writes anew, the summary in the bucket counts
+    // (NBUCKET_MAX of them), which launch_buckets does.
+    static_assert((9 * MESH_BLOCKS + 11) * sizeof(double) <= NBUCKET_MAX * sizeof(int32_t), "summary of the mesh check");
+    double *parts = reinterpret_cast<double *>(g->bucket_cnt), *res = parts + 9 * MESH_BLOCKS;
     unsigned long long *tab = reinterpret_cast<unsigned long long *>(g->crossings);
     unsigned long long *sums = reinterpret_cast<unsigned long long *>(g->counters + 8);
     const uint32_t slots = (uint32_t)(3 * nt + MESH_TAB_PAD);
@@ -348,9 +352,8 @@ hipError_t launch_mesh_scan(ibm_grid *g, const double *V, int64_t nv, const int3
     if ((e = hipMemsetAsync(tab, 0, sizeof(*tab) * slots, s)) != hipSuccess) return e;
     if ((e = hipMemsetAsync(sums, 0, 2 * sizeof(*sums), s)) != hipSuccess) return e;
     const int nb = (int)std::min<int64_t>((std::max(nv, nt) + MESH_NT - 1) / MESH_NT, MESH_BLOCKS);
-    hipLaunchKernelGGL(k_mesh_scan, dim3(nb), dim3(MESH_NT), 0, s, V, nv, T, nt, tab, slots, g->partials, sums);
-    double *res = g->partials + 9 * MESH_BLOCKS;
-    hipLaunchKernelGGL(k_mesh_final, dim3(1), dim3(64), 0, s, g->partials, nb, sums, res);
+    hipLaunchKernelGGL(k_mesh_scan, dim3(nb), dim3(MESH_NT), 0, s, V, nv, T, nt, tab, slots, parts, sums);
+    hipLaunchKernelGGL(k_mesh_final, dim3(1), dim3(64), 0, s, parts, nb, sums, res);
     double h[11];
     if ((e = hipMemcpyAsync(h, res, sizeof(h), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;

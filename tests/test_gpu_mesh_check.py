@@ -73,3 +73,27 @@ def test_refusals_keep_the_geometry(name):
     assert torch.equal(g.cell_types(), types)
     again, _ = g.poisson_solve(rhs)
     assert torch.equal(again, before)
+
+
+def test_refusals_leave_the_solver_memory_alone():
+    """A refused mesh is checked in scratch of the set-up: nothing that a solve in flight reads or
+    writes changes, the reduction partials (at the end of the workspace) among it."""
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    v, t = _meshes()["icosphere"]
+    f = I.uniform_faces(-1.0, 1.0, 20)
+    g = ibm.Grid(f, f, f)
+    g.bind(len(v), 2 * len(t), 8000)
+    g.set_geometry(v, t)
+    g.classify()
+    g.build_ghost_stencils()
+    g.poisson_solve(torch.rand(g.shape, dtype=torch.float64, device=g.device))
+    off = g._ws_ptr - g.ws.data_ptr()
+    tail = g.ws[off:off + g.workspace_bytes(*g._caps)][-131072:]
+    before = tail.clone()
+    for word, bv, bt in _broken(v, t):
+        with pytest.raises(ibm.IBMError, match=word):
+            g.set_geometry(bv, bt, max_ghosts=8000)
+        assert torch.equal(tail, before), word
