@@ -348,6 +348,8 @@ struct ibm_grid {
     double *g_betaDg = nullptr;            // per ghost: weight of the intercept value
     double *g_ubi = nullptr;               // 3 per ghost: velocity at the body intercept
     double *g_uscr = nullptr;              // 3 per ghost: held-back ghost values of an in-place pass
+    std::vector<int32_t> topo_tris;        // triangles of the last accepted mesh, if few, on the host
+    int64_t topo_nv = 0;                   // and its vertex count
     // fresh cells of the last move (capacity ghost_max)
     uint8_t *type_prev = nullptr;          // cell types before the move
     int64_t nfresh = 0;

@@ -97,3 +97,32 @@ def test_refusals_leave_the_solver_memory_alone():
         with pytest.raises(ibm.IBMError, match=word):
             g.set_geometry(bv, bt, max_ghosts=8000)
         assert torch.equal(tail, before), word
+
+
+@pytest.mark.parametrize("name", ["box", "icosphere", "many"])
+def test_moves_are_checked_as_new_meshes_are(name):
+    """A move takes what set_geometry takes and refuses what it refuses, with the triangles of the
+    last mesh (checked on the host if they are few) and with others; the result is a new handle's."""
+    from paper_2505_17287_amd import ibm
+
+    v, t = I.icosphere(6) if name == "many" else _meshes()[name]  # 81920: the device's check
+    if name == "many":
+        v = v * 0.55
+    f = I.uniform_faces(-1.0, 1.0, 20)
+    g = ibm.Grid(f, f, f)
+    g.bind(len(v), 2 * len(t), 8000)
+    g.setup(v, t)
+    shift = np.array([0.03, -0.02, 0.05])
+    for k, tris in enumerate((t, t, t[::-1], t)):
+        moved = v + (k + 1) * shift
+        for word, bv, bt in _broken(moved, tris):
+            if word == "non-finite" or k == 1:
+                with pytest.raises(ibm.IBMError, match=word):
+                    g.move_geometry(bv, bt)
+        g.move_geometry(moved, tris)
+        h = ibm.Grid(f, f, f)
+        h.setup(moved, tris)
+        assert np.array_equal(g.cell_types().cpu().numpy(), h.cell_types().cpu().numpy())
+        a, b = g.ghosts(), h.ghosts()
+        assert all(np.array_equal(a[q], b[q]) for q in a), (name, k)
+        h.close()
