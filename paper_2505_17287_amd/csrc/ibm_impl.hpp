@@ -78,7 +78,7 @@ hipError_t launch_sweep_widen(const Fine<float> &F, const float *pin, double *po
                               hipStream_t s);
 
 // the same sweep by bricks (sweepb.hip), which launch_sweep takes for small grids
-constexpr int64_t BRICK_LARGE_CELLS = 1 << 20;  // larger bricks from here
+constexpr int64_t BRICK_LARGE_CELLS = 1 << 20, BRICK_LARGE_ROWS = 1 << 15;  // larger bricks from either
 template <typename T, typename TO>
 hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T *f, const T *lam, hipStream_t s,
                               hipEvent_t ev0, hipEvent_t ev1);
@@ -94,6 +94,11 @@ struct MuSource {
 // distinct; zero: L.e counts as zero and need not be read
 template <typename T>
 hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s);
+// levels that take a launch per colour instead (launch_sweepC_colours): in place, mu and the
+// correction there before
+bool sweepC_by_colours(const int n[3]);
+template <typename T>
+hipError_t launch_sweepC_colours(const Coarse<T> &L, hipStream_t s);
 
 // fine index -> (lo, hi, weight of hi) per axis; lo is always the parent (the coarse cell
 // holding the fine one)

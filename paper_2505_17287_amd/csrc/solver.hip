@@ -1145,9 +1145,17 @@ static hipError_t timed_sweep(ibm_grid *g, const Fine<T> &F, const T *pin, T *po
 // nsweeps red-black sweeps of coarse level l (more than SMALL_LEVEL cells), out of place between
 // its two error buffers, which are swapped after each (every later view of the level sees the
 // current one).  The first sweep forms mu when ms has its partials; zero: the correction is 0.
+// (Levels swept by colours work in place, on a cleared correction, with mu formed by a launch.)
 template <typename T>
 static hipError_t smooth_level(ibm_grid *g, int l, int nsweeps, const MuSource &ms, bool zero, hipStream_t s) {
     LevelHost &H = g->lev[l];
+    if (sweepC_by_colours(H.n)) {
+        for (int q = 0; q < nsweeps; ++q) {
+            const hipError_t e = launch_sweepC_colours<T>(coarse_view<T>(g, l), s);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     for (int q = 0; q < nsweeps; ++q) {
         const hipError_t e = launch_sweepC<T>(coarse_view<T>(g, l), level_e2<T>(H), q == 0 ? ms : MuSource{},
                                               zero && q == 0, s);
@@ -1182,7 +1190,9 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
         const int Lb = tail ? lt : Lc;  // levels 1 .. Lb-1 run level by level
         int nparts = 0;                 // restriction partials into level Lb
         // levels whose first sweep takes a zero correction without reading it (not cleared then)
-        auto level_swept = [&](int l) { return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0; };
+        auto level_swept = [&](int l) {
+            return l < Lb && g->lev[l].ncell() > SMALL_LEVEL && o->nu1 > 0 && !sweepC_by_colours(g->lev[l].n);
+        };
         {
             Coarse<T> C1 = coarse_view<T>(g, 1);
             if (level_swept(1)) C1.e = nullptr;

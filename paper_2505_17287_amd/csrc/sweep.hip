@@ -374,10 +374,17 @@ static hipError_t launch_sweep_tiles(const Fine<T> &F, const T *pin, TO *pout, c
 // 32.5, 192^3 44 / 42, 128 x 128 3.5 / 6.3; odd rows (the z-march's unpaired loads) 97 x 83 x 71
 // 8.7 / 17.6, 161 x 159 x 157 27.9 / 36.5, 211^3 56 / 67.  FP32, five BiCGStab steps: 128^3 3.02 /
 // 3.22 ms, 160^3 4.62 / 4.41; odd 161 x 159 x 157 5.08 / 5.18, 189^3 6.27 / 6.27.
+// A brick holds whole rows of up to 64 columns and costs the same however short they are, as does a
+// tile of the z-march (of 60 columns), so shorter rows count as 64 (one plane aside, where bricks
+// have no z halo; and odd rows in FP64, which the z-march takes slowly).  Us of a V(2,2) cycle that
+// bricks cost more than the z-march (FP64; FP32, two cycles): 12 x 200 x 200 -22; -10, 12 x 256 x 256
+// -1; 12, 12 x 320 x 320 40; 86, 40 x 320 x 320 32; 87, 2 x 512 x 512 92; 186, 13 x 320 x 320 -7; 54,
+// 13 x 512 x 512 -35; 119, 63 x 320 x 320 (two tiles of the z-march) -136; -142.
 template <typename T>
 static bool by_bricks(int nx, int ny, int nz) {
     const int64_t even = sizeof(T) == 8 ? 5 << 20 : 3 << 20, odd = sizeof(T) == 8 ? 12 << 20 : 6 << 20;
-    return (int64_t)nx * ny * nz <= ((nx & 1) ? odd : even);  // at most 2^24: the bricks' index arithmetic
+    const bool pad = nz > 1 && nx <= 60 && (sizeof(T) == 4 || (nx & 1) == 0);
+    return (int64_t)(pad ? 64 : nx) * ny * nz <= ((nx & 1) ? odd : even);  // at most 2^24: the bricks' index arithmetic
 }
 
 template <typename T>

@@ -205,13 +205,14 @@ static hipError_t launch_brick(const Fine<T> &F, const T *pin, TO *pout, const T
 // of them), 8 x 8 rows from about 10^6 cells, where the halo's work outweighs the parallelism
 // (96^3 11.8 with the small ones); rows of 128 columns where they waste fewer columns
 // than tiles of 64 (128^3: 15.7, against 21 with small bricks); 16 waves of 9 rows against 8 of 18:
-// 15.7 / 16.4.
+// 15.7 / 16.4.  Short rows: by their number (a V(2,2) cycle with 8 x 8 rows against 4 x 4: 13 x 160 x 160
+// 213 / 230 us in FP64 but two of them 418 / 413 in FP32, 13 x 256 x 256 330 / 379 and 604 / 625).
 template <typename T, typename TO>
 hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T *f, const T *lam, hipStream_t s,
                               hipEvent_t ev0, hipEvent_t ev1) {
-    const int64_t n = (int64_t)F.nx * F.ny * F.nz;
+    const int64_t rows = (int64_t)F.ny * F.nz, n = F.nx * rows;
     if (F.nz == 1) return launch_brick<T, TO, 2, 8, 1, 4>(F, pin, pout, f, lam, s, ev0, ev1);
-    if (n < BRICK_LARGE_CELLS) return launch_brick<T, TO, 2, 4, 4, 8>(F, pin, pout, f, lam, s, ev0, ev1);
+    if (n < BRICK_LARGE_CELLS && rows < BRICK_LARGE_ROWS) return launch_brick<T, TO, 2, 4, 4, 8>(F, pin, pout, f, lam, s, ev0, ev1);
     // wide rows (128 columns) where they waste fewer columns than two or more of 64
     if (F.nx > 64 && F.nx <= 128 && 128 < 64 * ((F.nx + 59) / 60))
         return launch_brick<T, TO, 1, 8, 8, 16>(F, pin, pout, f, lam, s, ev0, ev1);

@@ -368,6 +368,23 @@ struct SwcRows<float> {
     static constexpr int BY = 32, QD = 4;
 };
 
+// Bricks hold SWB_Y x SWB_Z rows of up to SWB_COLS columns.
+constexpr int SWB_Y = 4, SWB_Z = 4, SWB_W = 8, SWB_COLS = 64;
+static int sweepC_brick_tiles(int nx) {  // one tile needs no halo
+    return nx <= SWB_COLS ? 1 : (nx + SWB_COLS - 5) / (SWB_COLS - 4);
+}
+
+// Levels whose bricks are a quarter full at most (16 columns, or one plane), where there are many
+// bricks: a brick's cost does not depend on how full it is.  Such levels take a launch per colour or,
+// from 393k cells, the z-march.  Us that bricks on all of a grid's levels add to a V(2,2) cycle with
+// those: 3 x 360 x 360 (level 1 of 2025 bricks) 531 + 68, 3 x 512 x 512 (4096) 840 + 147,
+// 2 x 40000 x 1 (5000) 388 + 304, 1500^2 in FP32 (2444) 371 + 29, 512^2 (1152) 181 + 1, 559^2 (1400) 355 - 23.
+static bool sweepC_narrow(const int n[3]) {
+    const int64_t bricks =
+        (int64_t)sweepC_brick_tiles(n[0]) * ((n[1] + SWB_Y - 1) / SWB_Y) * ((n[2] + SWB_Z - 1) / SWB_Z);
+    return bricks > 1536 && (int64_t)n[0] * n[1] * n[2] <= 256 * bricks;
+}
+
 // The sweep of a smaller level by bricks: the scheme of the fine level's bricks (sweepb.hip) with
 // the coarse operator.  Half a wave takes a row of 64 columns, a lane two adjacent columns; each
 // of the NT row takers updates NI rows of the brick's BY x BZ and NH of the ring around them, and
@@ -532,16 +549,51 @@ __global__ void __launch_bounds__(64 * NW, 4)
     }
 }
 
+// One colour of a sweep, in place: a thread per cell of that colour (in each x pair of a row exactly
+// one cell has it), every load issued before the test.  For levels of many short rows.
+template <typename T>
+__global__ void k_sweepC(Coarse<T> L, int colour) {
+    const int nx = L.n[0], ny = L.n[1], nz = L.n[2], hx = (nx + 1) >> 1;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)hx * ny * nz) return;
+    int P, J, K;
+    unflatten(t, hx, ny, P, J, K);
+    const int I = 2 * P + ((J + K + colour) & 1);
+    if (I >= nx) return;
+    const int64_t sy = nx, sz = (int64_t)nx * ny, id = (int64_t)K * sz + (int64_t)J * sy + I;
+    // places clamped into the level: a neighbour beyond a wall meets a zero transmissibility
+    const int64_t xm = id - (I > 0), xp = id + (I < nx - 1), ym = id - (J > 0 ? sy : 0), yp = id + (J < ny - 1 ? sy : 0),
+                  zm = id - (K > 0 ? sz : 0), zp = id + (K < nz - 1 ? sz : 0);
+    const T *Tx = L.Tl[0], *Ty = L.Tl[1], *Tz = L.Tl[2];
+    const T txp = I < nx - 1 ? Tx[xp] : T(0), typ = J < ny - 1 ? Ty[yp] : T(0), tzp = K < nz - 1 ? Tz[zp] : T(0);
+    const T vol = (L.w[0][I] * L.w[1][J]) * L.w[2][K];
+    T d;
+    const T v = rbc_update<T>(Tx[id], txp, Ty[id], typ, Tz[id], tzp, L.e[xm], L.e[xp], L.e[ym], L.e[yp], L.e[zm],
+                              L.e[zp], L.R[id], vol, (T)(*L.mu), d);
+    if (d > T(0)) L.e[id] = v;
+}
+
+bool sweepC_by_colours(const int n[3]) {
+    return sweepC_narrow(n) && (int64_t)n[0] * n[1] * n[2] < SWC_MIN_CELLS<double>;
+}
+
+template <typename T>
+hipError_t launch_sweepC_colours(const Coarse<T> &L, hipStream_t s) {
+    const int64_t np = (int64_t)((L.n[0] + 1) / 2) * L.n[1] * L.n[2];
+    for (int colour = 0; colour < 2; ++colour)
+        hipLaunchKernelGGL(k_sweepC<T>, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, L, colour);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s) {
     if (L.n[0] < 2) return hipErrorInvalidValue;
-    if ((int64_t)L.n[0] * L.n[1] * L.n[2] < SWC_MIN_CELLS<T>) {
-        constexpr int BY = 4, BZ = 4, NW = 8, COLS = 64;
-        const int ntx = L.n[0] <= COLS ? 1 : (L.n[0] + COLS - 5) / (COLS - 4);  // one tile needs no halo
-        const int xoff = ntx == 1 ? 0 : 2, bx = ntx == 1 ? COLS : (((L.n[0] + ntx - 1) / ntx + 1) & ~1);
-        const int nty = (L.n[1] + BY - 1) / BY, ntiles = ntx * nty * ((L.n[2] + BZ - 1) / BZ);
-        hipLaunchKernelGGL((k_rbgsC_brick<T, BY, BZ, NW>), dim3((ntiles + 7) / 8 * 8), dim3(64 * NW), 0, s, L, eout, ms,
-                           zero ? 1 : 0, ntx, nty, bx, xoff, ntiles);
+    if ((int64_t)L.n[0] * L.n[1] * L.n[2] < SWC_MIN_CELLS<T> && !sweepC_narrow(L.n)) {
+        const int ntx = sweepC_brick_tiles(L.n[0]);
+        const int xoff = ntx == 1 ? 0 : 2, bx = ntx == 1 ? SWB_COLS : (((L.n[0] + ntx - 1) / ntx + 1) & ~1);
+        const int nty = (L.n[1] + SWB_Y - 1) / SWB_Y, ntiles = ntx * nty * ((L.n[2] + SWB_Z - 1) / SWB_Z);
+        hipLaunchKernelGGL((k_rbgsC_brick<T, SWB_Y, SWB_Z, SWB_W>), dim3((ntiles + 7) / 8 * 8), dim3(64 * SWB_W), 0, s,
+                           L, eout, ms, zero ? 1 : 0, ntx, nty, bx, xoff, ntiles);
         return hipGetLastError();
     }
     constexpr int BY = SwcRows<T>::BY, QD = SwcRows<T>::QD;
@@ -568,5 +620,7 @@ hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool z
 
 template hipError_t launch_sweepC<double>(const Coarse<double> &, double *, const MuSource &, bool, hipStream_t);
 template hipError_t launch_sweepC<float>(const Coarse<float> &, float *, const MuSource &, bool, hipStream_t);
+template hipError_t launch_sweepC_colours<double>(const Coarse<double> &, hipStream_t);
+template hipError_t launch_sweepC_colours<float>(const Coarse<float> &, hipStream_t);
 
 }  // namespace ibm

@@ -117,3 +117,46 @@ def test_large_first_level_from_zero(dims, precision, tol):
     for _ in range(2):  # the second time on what the first has left in the level's buffers
         p, _st = g.poisson_solve(torch.from_numpy(rhs).cuda(), fixed_cycles=1, method="bicgstab", precision=precision)
         assert np.max(np.abs(p.cpu().numpy() - ref)[active]) <= tol * np.max(np.abs(ref[active]))
+
+
+@pytest.mark.parametrize("dims", [(2, 300, 300), (3, 182, 181), (5, 200, 170), (60, 290, 290), (17, 260, 130)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_short_rows_are_bitwise_the_two_pass_sweep(dims):
+    """Many short rows, by larger bricks or by the z-march."""
+    test_brick_sweep_is_bitwise_the_two_pass_sweep(dims)
+
+
+@pytest.mark.parametrize("nu", [(2, 2), (1, 0), (0, 3)])
+@pytest.mark.parametrize("dims", [(3, 13000, 1), (3, 330, 324), (8, 326, 318), (13, 318, 320), (32, 320, 320)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_coarse_levels_of_short_rows(dims, nu):
+    """Level 1 by a launch per colour or, the last one, by the z-march: two BiCGStab steps as the
+    oracle's.  Random widths within 5 %, so that nothing is symmetric."""
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    rng = np.random.default_rng(sum(dims))
+    f = [np.concatenate([[0.0], np.cumsum(rng.uniform(1.0, 1.05, n))]) if n > 1 else np.array([-0.5, 0.5]) for n in dims]
+    c = [0.46 * a[-1] for a in f]
+    if dims[2] == 1:
+        v, t = I.prism_mesh(1.1, 64, -1.0, 1.0, center=(c[0], c[1]))
+    else:
+        v, t = I.icosphere(3)
+        v = v * 0.3 * min(a[-1] for a in f) + np.array(c)
+    P = OracleProblem(*f)
+    P.set_mesh(v, t)
+    P.classify()
+    P.build_stencils()
+    rhs = rng.uniform(-1.0, 1.0, (dims[2], dims[1], dims[0]))
+    kw = dict(fixed_cycles=2, method="bicgstab", nu1=nu[0], nu2=nu[1])
+    ref, _ = P.solve(rhs, **kw)
+    active = P.types() != 2
+    for precision, tol in (("fp64", 1e-9), ("mixed", 1e-4)):  # mixed: two steps of an FP32 preconditioner
+        g = ibm.Grid(*f, precision=precision)
+        g.setup(v, t)
+        for _ in range(2):  # the second time on what the first has left in the levels' buffers
+            p, _st = g.poisson_solve(torch.from_numpy(rhs).cuda(), precision=precision, **kw)
+            err = np.max(np.abs(p.cpu().numpy() - ref)[active]) / np.max(np.abs(ref[active]))
+            print(dims, nu, precision, g.levels()[1:3], "err", err, flush=True)
+            assert err <= tol
