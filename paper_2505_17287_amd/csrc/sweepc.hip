@@ -186,21 +186,17 @@ __global__ void __launch_bounds__(32 * BY)
     const T *__restrict__ px = L.Tl[0];
     const T *__restrict__ py = L.Tl[1];
     const T *__restrict__ pz = L.Tl[2];
-    // the zero of ZERO, kept from the optimiser: as a known constant it made the compiler peel and
-    // rearrange the pipelined loop (with the x neighbour by a shuffle, even rows then came out wrong)
-    T z0 = T(0);
-    asm volatile("" : "+v"(z0));
     auto load = [=](int k) -> PD {
         PD d;
         const uint32_t base = (uint32_t)min(max(k, 0), klast) * plane;
         if constexpr (VEC) {
-            d.e = ZERO ? V{z0, z0} : *reinterpret_cast<const V *>(pe + base + rowoff);
+            d.e = ZERO ? V{T(0), T(0)} : *reinterpret_cast<const V *>(pe + base + rowoff);
             d.r = *reinterpret_cast<const V *>(pr + base + roff);
             d.x = *reinterpret_cast<const V *>(px + base + roff);
             d.y = *reinterpret_cast<const V *>(py + base + yoff);
             d.z = *reinterpret_cast<const V *>(pz + base + roff);
         } else {
-            const U e2 = ZERO ? U{z0, z0} : *reinterpret_cast<const U *>(pe + base + rowoff);
+            const U e2 = ZERO ? U{T(0), T(0)} : *reinterpret_cast<const U *>(pe + base + rowoff);
             const U r2 = *reinterpret_cast<const U *>(pr + base + roff);
             const U x2 = *reinterpret_cast<const U *>(px + base + roff);
             const U y2 = *reinterpret_cast<const U *>(py + base + yoff);
@@ -244,7 +240,10 @@ __global__ void __launch_bounds__(32 * BY)
 
     // One plane step: A = plane k, B = k+1, C = k+2 (QD - 3 more planes in flight);
     // afterwards the slot A receives plane k + QD.  Steps past the chunk end compute from clamped data
-    // and store nothing.
+    // and store nothing.  The lanes meet again after the store: without that, and with ZERO's values
+    // known, the compiler made the store's branch the end of an inner loop over the plane steps, in
+    // which the lanes that store nothing (the halo) went on through barriers and lane moves of later
+    // steps while the others were switched off, and even rows came out wrong by 1e-3.
 #define IBMC_STEP(A, B, C, k, FR)                                                                                  \
     {                                                                                                              \
         so[buf][ty][lc] = (B).e.x;                                                                                 \
@@ -298,6 +297,7 @@ __global__ void __launch_bounds__(32 * BY)
         pb0 = pc0;                                                                                                 \
         pb1 = pc1;                                                                                                 \
         buf ^= 1;                                                                                                  \
+        __builtin_amdgcn_wave_barrier();                                                                           \
         A = load((k) + QD);                                                                                        \
     }
 
