@@ -552,18 +552,13 @@ __global__ void k_finalize_mu(const double *partials, int n, const double *vol, 
 // coarse levels: red-black GS on  sum_F T_F (e_NB - e_C) = R_C - V_C mu
 // =======================================================================================
 
-// coarsest level in one workgroup: e = 0 (set by the restriction), n sweeps, then removal
-// of the volume-weighted mean over the active cells
 // nsweeps red-black sweeps of a level of at most SMALL_LEVEL cells in one workgroup of 1024
 // threads: each thread keeps the coefficients of up to SMALL_CPT cells in registers and the
 // iterate lives in LDS, so a colour costs one LDS pass and one barrier instead of a launch.
-// remove_mean != 0 (coarsest level): afterwards subtract the volume-weighted mean over the
-// active cells.  The arithmetic of every cell is that of launch_sweepC.
+// The arithmetic of every cell is that of launch_sweepC.
 template <typename T, int NT>
-__global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps, const double *vol, int remove_mean) {
-    __shared__ double sh[NT / 64];
+__global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps) {
     __shared__ T es[NT * SMALL_CPT];
-    __shared__ double mean_s;
     const int NC = L.n[0] * L.n[1] * L.n[2];
     const int sy = L.n[0], sz = L.n[0] * L.n[1];
     const T mu = (T)(*L.mu);
@@ -619,40 +614,23 @@ __global__ void __launch_bounds__(NT) k_smallC(Coarse<T> L, int nsweeps, const d
             __syncthreads();
         }
     }
-    double mean = 0.0;
-    if (remove_mean) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < SMALL_CPT; ++c) {
-            const int id = (int)threadIdx.x + NT * c;
-            if (fl[c] & 2u) {
-                const int I = id % L.n[0], J = (id / L.n[0]) % L.n[1], K = id / sz;
-                acc += (double)((L.w[0][I] * L.w[1][J]) * L.w[2][K]) * (double)es[id];
-            }
-        }
-        const double tot = block_sum<NT>(acc, sh, threadIdx.x);
-        if (threadIdx.x == 0) mean_s = (*vol > 0.0) ? tot / *vol : 0.0;
-        __syncthreads();
-        mean = mean_s;
-    }
 #pragma unroll
     for (int c = 0; c < SMALL_CPT; ++c) {
         const int id = (int)threadIdx.x + NT * c;
-        if (fl[c] & 1u) L.e[id] = (remove_mean && (fl[c] & 2u)) ? es[id] - (T)mean : es[id];
+        if (fl[c] & 1u) L.e[id] = es[id];
     }
 }
 
 // the smallest workgroup that holds the level (one wave for the tiny levels, where barriers
 // are nearly free)
 template <typename T>
-static void launch_smallC(const Coarse<T> &L, int64_t ncell, int nsweeps, const double *vol, int remove_mean,
-                          hipStream_t s) {
+static void launch_smallC(const Coarse<T> &L, int64_t ncell, int nsweeps, hipStream_t s) {
     if (ncell <= 64 * SMALL_CPT)
-        hipLaunchKernelGGL((k_smallC<T, 64>), dim3(1), dim3(64), 0, s, L, nsweeps, vol, remove_mean);
+        hipLaunchKernelGGL((k_smallC<T, 64>), dim3(1), dim3(64), 0, s, L, nsweeps);
     else if (ncell <= 256 * SMALL_CPT)
-        hipLaunchKernelGGL((k_smallC<T, 256>), dim3(1), dim3(256), 0, s, L, nsweeps, vol, remove_mean);
+        hipLaunchKernelGGL((k_smallC<T, 256>), dim3(1), dim3(256), 0, s, L, nsweeps);
     else
-        hipLaunchKernelGGL((k_smallC<T, 1024>), dim3(1), dim3(1024), 0, s, L, nsweeps, vol, remove_mean);
+        hipLaunchKernelGGL((k_smallC<T, 1024>), dim3(1), dim3(1024), 0, s, L, nsweeps);
 }
 
 template <typename T>
@@ -1210,7 +1188,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
         finalize_mu(1);
         for (int l = 1; l < Lb; ++l) {
             if (g->lev[l].ncell() <= SMALL_LEVEL) {
-                if (o->nu1 > 0) launch_smallC<T>(coarse_view<T>(g, l), g->lev[l].ncell(), o->nu1, &g->sc->vol[l], 0, s);
+                if (o->nu1 > 0) launch_smallC<T>(coarse_view<T>(g, l), g->lev[l].ncell(), o->nu1, s);
             } else {
                 MuSource ms;
                 ms.partials = g->partials;
@@ -1237,9 +1215,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
         }
         if (tail) {
             if ((e = launch_tail<T>(g, lt, coarse_view<T>(g, lt), nparts, o, s)) != hipSuccess) return e;
-        } else if (g->lev[Lc].ncell() <= SMALL_LEVEL) {
-            launch_smallC<T>(coarse_view<T>(g, Lc), g->lev[Lc].ncell(), o->coarsest_sweeps, &g->sc->vol[Lc], 1, s);
-        } else {
+        } else {  // a coarsest level of more than SMALL_LEVEL cells
             hipLaunchKernelGGL(k_coarsest<T>, dim3(1), dim3(1024), 0, s, coarse_view<T>(g, Lc), o->coarsest_sweeps,
                                &g->sc->vol[Lc]);
         }
@@ -1258,7 +1234,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
             } else
                 hipLaunchKernelGGL(k_prolongC<T>, dim3(nb), dim3(256), 0, s, L, coarse_view<T>(g, l + 1), PT);
             if (g->lev[l].ncell() <= SMALL_LEVEL) {
-                if (o->nu2 > 0) launch_smallC<T>(L, g->lev[l].ncell(), o->nu2, &g->sc->vol[l], 0, s);
+                if (o->nu2 > 0) launch_smallC<T>(L, g->lev[l].ncell(), o->nu2, s);
             } else if ((e = smooth_level<T>(g, l, o->nu2, MuSource{}, false, s)) != hipSuccess) {
                 return e;
             }
@@ -1741,8 +1717,6 @@ __global__ void __launch_bounds__(FIN_NT) k_krylov_finalize(const double *partia
     const double a = s[0], b = s[1 % NS], c = s[2 % NS];
     switch (op) {
         case K_MU: sc->mu_v = a / sc->vol[0]; break;
-        case K_ALPHA:
-        case K_OMEGA: break;  // formed by k_krylov_finalize_dots
         case K_RHO:
         case K_INIT:
         case K_RESTART: {
