@@ -87,3 +87,40 @@ def test_work_ahead_of_the_residual_changes_nothing(kw):
     g.set_profiling(True)  # the sweeps are timed one by one: nothing is enqueued ahead
     b, sb = g.poisson_solve(r, **kw)
     assert torch.equal(a, b) and (sa.cycles, sa.status) == (sb.cycles, sb.status)
+
+
+AHEAD = {
+    # 1.06e6 cells: the direction alone goes ahead, the step runs the first sweep itself
+    "direction": ((104, 102, 100), dict(method="bicgstab")),
+    "direction, mixed": ((104, 102, 100), dict(method="bicgstab", precision="mixed")),
+    "direction, jacobi": ((104, 102, 100), dict(method="bicgstab_srj", srj_sweeps=4, max_cycles=12)),
+    "set steps": ((35, 33, 31), dict(method="bicgstab", fixed_cycles=5)),
+    "set cycles": ((35, 33, 31), dict(method="vcycle", fixed_cycles=5)),
+    "one step": ((35, 33, 31), dict(method="bicgstab", max_cycles=1)),
+    # the shadow residual is restarted between the work ahead and its step
+    "restarts": ((35, 33, 31), dict(method="bicgstab_srj", srj_sweeps=2, breakdown_tol=0.3, max_cycles=60)),
+    "restarts, mixed": ((35, 33, 31), dict(method="bicgstab", precision="mixed", breakdown_tol=0.9, max_cycles=60)),
+    # the recurrence gets below a tolerance that the true residual does not: the solve goes on
+    # after the result has been enqueued behind the residual that fails to confirm
+    "not confirmed": ((35, 33, 31), dict(method="bicgstab", rel_tol=2e-15)),
+}
+
+
+@pytest.mark.parametrize("name", AHEAD)
+def test_work_ahead_is_dropped_or_used_without_a_trace(name):
+    import torch
+
+    dims, kw = AHEAD[name]
+    _, g, rhs = _problem(dims, 7.3)
+    r = torch.from_numpy(rhs).cuda()
+    kw = dict(dict(rel_tol=1e-9, max_cycles=40), **kw)
+    a, sa = g.poisson_solve(r, **kw)
+    g.set_profiling(True)  # nothing is enqueued ahead
+    b, sb = g.poisson_solve(r, **kw)
+    print(name, sa.cycles, sa.restarts, sa.status, sa.rel_residual)
+    assert torch.equal(a, b)
+    assert (sa.cycles, sa.status, sa.restarts, sa.rel_residual) == (sb.cycles, sb.status, sb.restarts, sb.rel_residual)
+    assert sa.restarts > 0 or "restarts" not in name
+    if name == "not confirmed":  # which restarts the recurrences: as many steps without are others
+        _, sc = g.poisson_solve(r, **dict(kw, fixed_cycles=sa.cycles))
+        assert sa.status == 0 and sa.rel_residual != sc.rel_residual
