@@ -135,7 +135,7 @@ __global__ void k_ghost_scatter(int64_t ng, const int32_t *__restrict__ gcell, c
 // a wave's reads are contiguous; one barrier a plane, double-buffered), so nothing is loaded
 // twice but the halo.  Both passes are bound by HBM (73 and 97 bytes per cell).  With one column per
 // thread and every neighbour loaded (26 and 39 loads a plane, 150 and 208 registers) they took 314 and
-// 540 us at 256^3; this way about 248 and 405 us.
+// 540 us at 256^3; this way 267 and 408 us.
 struct MTiles {
     int ntx, nty, bx, kc, ntiles, grid;
 };

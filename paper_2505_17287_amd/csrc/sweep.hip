@@ -371,8 +371,8 @@ static hipError_t launch_sweep_tiles(const Fine<T> &F, const T *pin, TO *pout, c
 
 // Grids that the bricks of sweepb.hip sweep faster than this z-march.  us per sweep, bricks
 // against z-march: FP64, even rows 64^3 4.6 / 21, 128^3 15.7 / 26, 160^3 27.9 / 30.5, 176^3 33.1 /
-// 32.5, 192^3 44 / 42, 128 x 128 3.5 / 6.3; odd rows (the z-march's unpaired loads) 97 x 83 x 71
-// 8.7 / 17.6, 161 x 159 x 157 27.9 / 36.5, 211^3 56 / 67.  FP32, five BiCGStab steps: 128^3 3.02 /
+// 32.5, 192^3 44 / 42, 256 x 128 x 128 29.0 / 31.0, 128 x 128 3.5 / 6.3; odd rows (the z-march's unpaired loads) 97 x 83 x 71
+// 8.7 / 17.6, 161 x 159 x 157 27.9 / 36.5, 211^3 57 / 69, 227^3 77 / 81.  FP32, five BiCGStab steps: 128^3 3.02 /
 // 3.22 ms, 160^3 4.62 / 4.41; odd 161 x 159 x 157 5.08 / 5.18, 189^3 6.27 / 6.27.
 // A brick holds whole rows of up to 64 columns and costs the same however short they are, as does a
 // tile of the z-march (of 60 columns), so shorter rows count as 64 (one plane aside, where bricks

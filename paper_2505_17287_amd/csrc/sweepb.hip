@@ -203,9 +203,9 @@ static hipError_t launch_brick(const Fine<T> &F, const T *pin, TO *pout, const T
 
 // Brick shapes (FP64 us per sweep): small bricks while they give each compute unit a few (64^3: 256
 // of them), 8 x 8 rows from about 10^6 cells, where the halo's work outweighs the parallelism
-// (96^3 11.8 with the small ones); rows of 128 columns where they waste fewer columns
-// than tiles of 64 (128^3: 15.7, against 21 with small bricks); 16 waves of 9 rows against 8 of 18:
-// 15.7 / 16.4.  Short rows: by their number (a V(2,2) cycle with 8 x 8 rows against 4 x 4: 13 x 160 x 160
+// (96^3 11.8 with the small ones); one row of 128 columns where it takes the place of three tiles of
+// 64, 121 to 128 columns (128^3 15.9 / 18.2, 122 x 120 x 130 14.9 / 17.8, 126 x 160 x 160 26.9 / 25.9; two
+// for five tiles are slower, 244 x 128 x 128 30.8 / 28.1); 16 waves of 9 rows against 8 of 18: 15.7 / 16.4.  Short rows: by their number (a V(2,2) cycle with 8 x 8 rows against 4 x 4: 13 x 160 x 160
 // 213 / 230 us in FP64 but two of them 418 / 413 in FP32, 13 x 256 x 256 330 / 379 and 604 / 625).
 template <typename T, typename TO>
 hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T *f, const T *lam, hipStream_t s,
@@ -213,7 +213,6 @@ hipError_t launch_sweep_brick(const Fine<T> &F, const T *pin, TO *pout, const T 
     const int64_t rows = (int64_t)F.ny * F.nz, n = F.nx * rows;
     if (F.nz == 1) return launch_brick<T, TO, 2, 8, 1, 4>(F, pin, pout, f, lam, s, ev0, ev1);
     if (n < BRICK_LARGE_CELLS && rows < BRICK_LARGE_ROWS) return launch_brick<T, TO, 2, 4, 4, 8>(F, pin, pout, f, lam, s, ev0, ev1);
-    // wide rows (128 columns) where they waste fewer columns than two or more of 64
     if (F.nx > 64 && F.nx <= 128 && 128 < 64 * ((F.nx + 59) / 60))
         return launch_brick<T, TO, 1, 8, 8, 16>(F, pin, pout, f, lam, s, ev0, ev1);
     return launch_brick<T, TO, 2, 8, 8, 8>(F, pin, pout, f, lam, s, ev0, ev1);
