@@ -133,7 +133,8 @@ ibm_status ibm_bind_workspace(ibm_grid *g, void *device_ptr, size_t bytes, int64
 /* Set the immersed body: verts[nv][3] (host, FP64), tris[nt][3] (host, int32, outward
    counter-clockwise).  The mesh must be closed and consistently oriented (every directed
    edge once, its reverse once) -> else IBM_E_GEOMETRY.  Several disjoint closed bodies may
-   be passed as one mesh.  Uploads the mesh and builds the triangle bucket grid on the GPU. */
+   be passed as one mesh.  Uploads the mesh and builds the triangle bucket grid on the GPU.  A
+   refused mesh leaves the one in use, and solves on it, as they were.  Synchronises `stream`. */
 ibm_status ibm_set_geometry(ibm_grid *g, const double *verts, int64_t nv, const int32_t *tris, int64_t nt,
                             void *stream);
 
