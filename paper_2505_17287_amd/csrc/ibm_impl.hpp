@@ -94,6 +94,9 @@ struct MuSource {
 // distinct; zero: L.e counts as zero and need not be read
 template <typename T>
 hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s);
+// whether a level's first sweep had better form mu from nparts partials than a launch before it
+template <typename T>
+bool sweepC_forms_mu(const int n[3], int nparts);
 // levels that take a launch per colour instead (launch_sweepC_colours): in place, mu and the
 // correction there before
 bool sweepC_by_colours(const int n[3]);

@@ -1179,9 +1179,10 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
                 return e;
         }
         // mu of level l from the partials of the restriction into it: by its first sweep where one
-        // follows, by the tail for its own levels, else by a launch
+        // follows and the partials are few for it, by the tail for its own levels, else by a launch
+        auto mu_by_sweep = [&](int l) { return level_swept(l) && sweepC_forms_mu<T>(g->lev[l].n, nparts); };
         auto finalize_mu = [&](int l) {
-            if (!level_swept(l) && !(tail && l == lt))
+            if (!mu_by_sweep(l) && !(tail && l == lt))
                 hipLaunchKernelGGL(k_finalize_mu, dim3(1), dim3(256), 0, s, g->partials, nparts, &g->sc->vol[l],
                                    &g->sc->mu[l]);
         };
@@ -1192,7 +1193,7 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
             } else {
                 MuSource ms;
                 ms.partials = g->partials;
-                ms.n = nparts;
+                ms.n = mu_by_sweep(l) ? nparts : 0;
                 ms.vol = &g->sc->vol[l];
                 ms.mu = &g->sc->mu[l];
                 if ((e = smooth_level<T>(g, l, o->nu1, ms, true, s)) != hipSuccess) return e;

@@ -585,39 +585,72 @@ hipError_t launch_sweepC_colours(const Coarse<T> &L, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Launch of a sweep: bricks, or the z-march in chunks of kc planes; rounds of workgroups that run at once
+struct SweepCTiles {
+    bool bricks;
+    int ntx, nty, kc, ntiles;
+    int64_t rounds;
+};
 template <typename T>
-hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s) {
-    if (L.n[0] < 2) return hipErrorInvalidValue;
-    if ((int64_t)L.n[0] * L.n[1] * L.n[2] < SWC_MIN_CELLS<T> && !sweepC_narrow(L.n)) {
-        const int ntx = sweepC_brick_tiles(L.n[0]);
-        const int xoff = ntx == 1 ? 0 : 2, bx = ntx == 1 ? SWB_COLS : (((L.n[0] + ntx - 1) / ntx + 1) & ~1);
-        const int nty = (L.n[1] + SWB_Y - 1) / SWB_Y, ntiles = ntx * nty * ((L.n[2] + SWB_Z - 1) / SWB_Z);
-        hipLaunchKernelGGL((k_rbgsC_brick<T, SWB_Y, SWB_Z, SWB_W>), dim3((ntiles + 7) / 8 * 8), dim3(64 * SWB_W), 0, s,
-                           L, eout, ms, zero ? 1 : 0, ntx, nty, bx, xoff, ntiles);
-        return hipGetLastError();
+static SweepCTiles sweepC_tiles(const int n[3]) {
+    SweepCTiles t;
+    t.bricks = (int64_t)n[0] * n[1] * n[2] < SWC_MIN_CELLS<T> && !sweepC_narrow(n);
+    const int slots = device_cu_count();
+    if (t.bricks) {
+        t.ntx = sweepC_brick_tiles(n[0]);
+        t.nty = (n[1] + SWB_Y - 1) / SWB_Y;
+        t.kc = SWB_Z;
+        t.ntiles = t.ntx * t.nty * ((n[2] + SWB_Z - 1) / SWB_Z);
+        t.rounds = (t.ntiles + 2 * slots - 1) / (2 * slots);  // two of 512 threads at its register count
+        return t;
     }
-    constexpr int BY = SwcRows<T>::BY, QD = SwcRows<T>::QD;
-    constexpr int TXC = SWC_NC - 4, TY = BY - 4;
-    const int ntx = (L.n[0] + TXC - 1) / TXC, nty = (L.n[1] + TY - 1) / TY;
-    const int64_t per_slab = (int64_t)ntx * nty;
+    constexpr int TXC = SWC_NC - 4, TY = SwcRows<T>::BY - 4;
+    t.ntx = (n[0] + TXC - 1) / TXC;
+    t.nty = (n[1] + TY - 1) / TY;
+    const int64_t per_slab = (int64_t)t.ntx * t.nty;
     // one workgroup per CU; chunks as long as that residency allows, but no shorter than
     // kcmin planes (each chunk re-reads four planes of its neighbours)
     const int kcmin = SWC_KC_MIN;
-    const int slots = device_cu_count();
-    int nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(slots / per_slab, L.n[2]));
-    int kc = (L.n[2] + nchunk - 1) / nchunk;
-    kc = std::max(kc, std::min(kcmin, L.n[2]));
+    int nchunk = (int)std::max<int64_t>(1, std::min<int64_t>(slots / per_slab, n[2]));
+    int kc = (n[2] + nchunk - 1) / nchunk;
+    kc = std::max(kc, std::min(kcmin, n[2]));
     kc = std::min(kc, SWC_KC_MAX);
-    nchunk = (L.n[2] + kc - 1) / kc;
-    const int ntiles = (int)(per_slab * nchunk);
-    const int grid = ((ntiles + 7) / 8) * 8;
+    nchunk = (n[2] + kc - 1) / kc;
+    t.kc = kc;
+    t.ntiles = (int)(per_slab * nchunk);
+    t.rounds = (t.ntiles + slots - 1) / slots;
+    return t;
+}
+
+// Every workgroup sums all partials, about 17 us for 65536 of them, one round of workgroups after the
+// other; a launch that sums them once takes 5 us and 12 us for 32768.  On levels of 2048^2 cells (32768
+// partials, 24 rounds) the first sweep took 282 us instead of 87.
+template <typename T>
+bool sweepC_forms_mu(const int n[3], int nparts) {
+    return sweepC_tiles<T>(n).rounds * nparts <= 24576;
+}
+
+template <typename T>
+hipError_t launch_sweepC(const Coarse<T> &L, T *eout, const MuSource &ms, bool zero, hipStream_t s) {
+    if (L.n[0] < 2) return hipErrorInvalidValue;
+    const SweepCTiles t = sweepC_tiles<T>(L.n);
+    const int grid = (t.ntiles + 7) / 8 * 8;
+    if (t.bricks) {
+        const int xoff = t.ntx == 1 ? 0 : 2, bx = t.ntx == 1 ? SWB_COLS : (((L.n[0] + t.ntx - 1) / t.ntx + 1) & ~1);
+        hipLaunchKernelGGL((k_rbgsC_brick<T, SWB_Y, SWB_Z, SWB_W>), dim3(grid), dim3(64 * SWB_W), 0, s, L, eout, ms,
+                           zero ? 1 : 0, t.ntx, t.nty, bx, xoff, t.ntiles);
+        return hipGetLastError();
+    }
+    constexpr int BY = SwcRows<T>::BY, QD = SwcRows<T>::QD;
     const bool vec = (L.n[0] & 1) == 0;
     auto k = vec ? (zero ? k_rbgsC_fused<T, BY, QD, true, true> : k_rbgsC_fused<T, BY, QD, true, false>)
                  : (zero ? k_rbgsC_fused<T, BY, QD, false, true> : k_rbgsC_fused<T, BY, QD, false, false>);
-    hipLaunchKernelGGL(k, dim3(grid), dim3(32 * BY), 0, s, L, eout, ms, ntx, nty, kc, ntiles);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(32 * BY), 0, s, L, eout, ms, t.ntx, t.nty, t.kc, t.ntiles);
     return hipGetLastError();
 }
 
+template bool sweepC_forms_mu<double>(const int[3], int);
+template bool sweepC_forms_mu<float>(const int[3], int);
 template hipError_t launch_sweepC<double>(const Coarse<double> &, double *, const MuSource &, bool, hipStream_t);
 template hipError_t launch_sweepC<float>(const Coarse<float> &, float *, const MuSource &, bool, hipStream_t);
 template hipError_t launch_sweepC_colours<double>(const Coarse<double> &, hipStream_t);

@@ -160,3 +160,26 @@ def test_coarse_levels_of_short_rows(dims, nu):
             err = np.max(np.abs(p.cpu().numpy() - ref)[active]) / np.max(np.abs(ref[active]))
             print(dims, nu, precision, g.levels()[1:3], "err", err, flush=True)
             assert err <= tol
+
+
+@pytest.mark.parametrize("dims,precision,tol", [((2048, 2048, 1), "fp64", 1e-9), ((2047, 2050, 1), "mixed", 1e-4)], ids=str)
+def test_many_partials_of_mu(dims, precision, tol):
+    """First coarse levels with more restriction partials than their sweep's workgroups had better
+    sum up each for itself: a launch forms mu.  A BiCGStab step as the oracle's."""
+    import torch
+
+    from paper_2505_17287_amd import ibm
+
+    f = [np.linspace(0.0, n, n + 1) if n > 1 else np.array([-0.5, 0.5]) for n in dims]
+    v, t = I.prism_mesh(300.3, 64, -1.0, 1.0, center=(0.46 * dims[0], 0.52 * dims[1]))
+    P = OracleProblem(*f)
+    P.set_mesh(v, t)
+    P.classify()
+    P.build_stencils()
+    rhs = np.random.default_rng(1).uniform(-1.0, 1.0, (dims[2], dims[1], dims[0]))
+    ref, _ = P.solve(rhs, fixed_cycles=1, method="bicgstab")
+    g = ibm.Grid(*f, precision=precision)
+    g.setup(v, t)
+    active = P.types() != 2
+    p, _ = g.poisson_solve(torch.from_numpy(rhs).cuda(), fixed_cycles=1, method="bicgstab", precision=precision)
+    assert np.max(np.abs(p.cpu().numpy() - ref)[active]) <= tol * np.max(np.abs(ref[active]))
