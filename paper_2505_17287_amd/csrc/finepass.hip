@@ -206,7 +206,9 @@ struct RMPlane {
 
 // One wave's coarse row J of the tile (I0..I1-1, K0..K1-1); TWO: the row has two fine rows.
 // Returns the sum of the R_1 values the wave stored (valid in every lane that stored one).
-template <typename T, bool TWO>
+// ONE: a grid of one plane, where the second of the two planes of a trip would be work for nothing
+// (V-cycle of 8192 x 4096 stretched: 4.92 ms, 5.17 with it; 2048 x 2048: 0.61 and 0.66).
+template <typename T, bool TWO, bool ONE>
 __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__restrict__ p,
                                                    const T *__restrict__ f, T lam, const Coarse<T> &C,
                                                    const ChildMap &M, const XTile &X, const XTile &Xe, int J, const ZTile &Z, int k1,
@@ -302,7 +304,12 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
         pm1 = pc1;                                                                                                 \
         pc1 = (D).pp1;                                                                                             \
     }
-    RMPlane<T> qa = ld(k0), qb;
+    RMPlane<T> qa = ld(k0);
+    if constexpr (ONE) {
+        IBM_RMAP_PLANE(qa, k0);
+        return psum;
+    }
+    RMPlane<T> qb;
     for (int k = k0; k < k1; k += 2) {  // no way out in between: see above
         qb = ld(k + 1);
         IBM_RMAP_PLANE(qa, k);
@@ -313,7 +320,7 @@ __device__ __forceinline__ double restrict_map_row(const Fine<T> &F, const T *__
     return psum;
 }
 
-template <typename T>
+template <typename T, bool ONE>
 __global__ void __launch_bounds__(RM_NT, 4)
     k_restrict0_map(Fine<T> F, const T *__restrict__ p, const T *__restrict__ f, const T *__restrict__ lamp,
                     Coarse<T> C, ChildMap M, RowTiles t, double *partials) {
@@ -334,9 +341,9 @@ __global__ void __launch_bounds__(RM_NT, 4)
         const int k1 = M.tz[chunk + 1].k0;
         if (J >= C.n[1] || X.I0 >= Xe.I0 || Z.k0 >= k1) continue;
         if (M.cs[1][J + 1] - M.cs[1][J] == 2)
-            psum += restrict_map_row<T, true>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
+            psum += restrict_map_row<T, true, ONE>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
         else
-            psum += restrict_map_row<T, false>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
+            psum += restrict_map_row<T, false, ONE>(F, p, f, lam, C, M, X, Xe, J, Z, k1, lane);
     }
     __shared__ double sh[RM_NT / 64];
     const double tot = block_sum<RM_NT>(psum, sh, threadIdx.x);
@@ -1066,7 +1073,8 @@ hipError_t launch_restrict0(const Fine<T> &F, const T *p, const T *f, const T *l
         int grid;
         const hipError_t e = row_tiles(M, C.n, zmarch_partials_max(F.nx, F.ny, F.nz), &t, &grid);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_restrict0_map<T>, dim3(grid), dim3(RM_NT), 0, s, F, p, f, lam, C, M, t, partials);
+        auto k = F.nz == 1 ? k_restrict0_map<T, true> : k_restrict0_map<T, false>;
+        hipLaunchKernelGGL(k, dim3(grid), dim3(RM_NT), 0, s, F, p, f, lam, C, M, t, partials);
         *nparts = grid;
         return hipGetLastError();
     }

@@ -282,7 +282,7 @@ struct RCPlane {
     uint8_t a0, a1;
 };
 
-template <typename T, bool TWO>
+template <typename T, bool TWO, bool ONE>
 __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coarse<T> &C, const ChildMap &M, T mu,
                                                   const XTile &X, const XTile &Xe, int J, const ZTile &Z, int k1, int lane) {
     const int nx = L.n[0], ny = L.n[1], nz = L.n[2];
@@ -399,7 +399,12 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
         ec1 = (D).en1;                                                                                         \
         tzc1 = (D).tzn1;                                                                                       \
     }
-    RCPlane<T> qa = ld(k0), qb;
+    RCPlane<T> qa = ld(k0);
+    if constexpr (ONE) {  // a level of one plane
+        IBM_RC_PLANE(qa, k0);
+        return psum;
+    }
+    RCPlane<T> qb;
     for (int k = k0; k < k1; k += 2) {  // no way out in between, as in the level-0 pass
         qb = ld(k + 1);
         IBM_RC_PLANE(qa, k);
@@ -411,7 +416,7 @@ __device__ __forceinline__ double resrestrict_row(const Coarse<T> &L, const Coar
     return psum;
 }
 
-template <typename T>
+template <typename T, bool ONE>
 __global__ void __launch_bounds__(RM_NT)
     k_resrestrictC_map(Coarse<T> L, Coarse<T> C, ChildMap M, RowTiles t, double *partials) {
     const int lane = (int)threadIdx.x & 63;
@@ -431,9 +436,9 @@ __global__ void __launch_bounds__(RM_NT)
         const int k1 = M.tz[chunk + 1].k0;
         if (J >= C.n[1] || X.I0 >= Xe.I0 || Z.k0 >= k1) continue;
         if (M.cs[1][J + 1] - M.cs[1][J] == 2)
-            psum += resrestrict_row<T, true>(L, C, M, mu, X, Xe, J, Z, k1, lane);
+            psum += resrestrict_row<T, true, ONE>(L, C, M, mu, X, Xe, J, Z, k1, lane);
         else
-            psum += resrestrict_row<T, false>(L, C, M, mu, X, Xe, J, Z, k1, lane);
+            psum += resrestrict_row<T, false, ONE>(L, C, M, mu, X, Xe, J, Z, k1, lane);
     }
     __shared__ double sh[RM_NT / 64];
     const double tot = block_sum<RM_NT>(psum, sh, threadIdx.x);
@@ -1209,7 +1214,8 @@ static hipError_t vcycle_impl(ibm_grid *g, T **bufs, int *cur, const T *rhs, con
                 RowTiles t;
                 if ((e = row_tiles(M, C.n, zmarch_partials_max(g->nx, g->ny, g->nz), &t, &nbc)) != hipSuccess)
                     return e;
-                hipLaunchKernelGGL(k_resrestrictC_map<T>, dim3(nbc), dim3(RM_NT), 0, s, L, C, M, t, g->partials);
+                auto k = L.n[2] == 1 ? k_resrestrictC_map<T, true> : k_resrestrictC_map<T, false>;
+                hipLaunchKernelGGL(k, dim3(nbc), dim3(RM_NT), 0, s, L, C, M, t, g->partials);
             }
             nparts = nbc;
             finalize_mu(l + 1);

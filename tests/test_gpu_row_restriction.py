@@ -46,3 +46,11 @@ def test_step(dims, ratios):
         g.setup(v, t)
         p, _ = g.poisson_solve(torch.from_numpy(rhs).cuda(), precision=precision, **kw)
         assert np.max(np.abs(p.cpu().numpy() - ref)[active]) <= tol * np.max(np.abs(ref[active])), precision
+
+
+@pytest.mark.parametrize("dims,ratios", [((61, 47, 1), (3, 1, 1)), ((62, 90, 1), (1, 4, 1)), ((261, 190, 1), (5, 7, 1)),
+                                         ((700, 333, 1), (12, 3, 1)), ((150, 130, 2), (6, 4, 1))],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_grids_of_one_plane(dims, ratios):
+    """One plane (levels of one plane too) and, next to it, two."""
+    test_step(dims, ratios)
